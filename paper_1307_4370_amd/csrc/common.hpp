@@ -271,7 +271,7 @@ template <typename R> struct CgFuse {
     int nred = 0, slot_old = 0, slot_new = 0, slot_pq = 0;
 };
 // Whether the column passes fold in the CG steps of CgFuse with nred partials
-// per slot (the power-of-two kernel with at most nred column blocks).
+// per slot (the compile-time kernel with at most nred column blocks).
 bool fft_folds_cg(const riop_plan *p, int nred);
 // Forward FFT passes; returns whether cg->r's direction update was folded in
 // (false: the caller must apply it first; nothing was done).

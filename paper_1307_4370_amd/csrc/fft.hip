@@ -28,11 +28,11 @@ template <typename R> struct FftArgs {
     const R *dbt;        // factor along the batch axis (nbatch entries), nullable
     long in_ts, in_es;   // strides (in complex elements) between transforms / elements
     long out_ts, out_es;
-    // Adjoint row pass of the power-of-two kernel: gridding halos to add on
+    // Adjoint row pass of the compile-time kernel: gridding halos to add on
     // load (nullptr: none), with the gridding tile side, J and tiles per side.
     const C<R> *halo;
     int hT, hJ, htps;
-    // CG steps folded into the column passes (power-of-two kernel).  Forward:
+    // CG steps folded into the column passes (compile-time kernel).  Forward:
     // with cg_r set, the input p is replaced by r + beta p first and written
     // back, beta = sum(cg_part[cg_new]) / sum(cg_part[cg_old]).  Adjoint: with
     // cg_p set, the output q becomes q + 2 p and each block leaves its part of
@@ -110,7 +110,30 @@ template <typename R, int SGN> struct Dft<R, 3, SGN> {
     }
 };
 
-// One Stockham stage of radix RR on the thread's E registers.
+// Radix 12 by the prime-factor map (Good 1958): inputs s = (4 s1 + 3 s2) mod 12
+// and outputs r = (4 r1 + 9 r2) mod 12 split the transform into 3 of length 4
+// and 4 of length 3 with no twiddles between them.
+template <typename R, int SGN> struct Dft<R, 12, SGN> {
+    __device__ static void run(C<R> *x) {
+        C<R> t[3][4];
+#pragma unroll
+        for (int s1 = 0; s1 < 3; ++s1) {
+#pragma unroll
+            for (int s2 = 0; s2 < 4; ++s2) t[s1][s2] = x[(4 * s1 + 3 * s2) % 12];
+            Dft<R, 4, SGN>::run(t[s1]);
+        }
+#pragma unroll
+        for (int r2 = 0; r2 < 4; ++r2) {
+            C<R> u[3] = {t[0][r2], t[1][r2], t[2][r2]};
+            Dft<R, 3, SGN>::run(u);
+#pragma unroll
+            for (int r1 = 0; r1 < 3; ++r1) x[(4 * r1 + 9 * r2) % 12] = u[r1];
+        }
+    }
+};
+
+// One Stockham stage of radix RR on the thread's E registers (radix 12
+// only as a first stage, Ns = 1, which has no twiddles).
 template <typename R, int E, int RR, int SGN>
 __device__ inline void stage(C<R> (&v)[E], int jt, int NE, int N, int Ns, const C<R> *tw) {
     constexpr int B = E / RR;
@@ -121,7 +144,7 @@ __device__ inline void stage(C<R> (&v)[E], int jt, int NE, int N, int Ns, const 
         C<R> x[RR];
 #pragma unroll
         for (int r = 0; r < RR; ++r) x[r] = v[b + r * B];
-        if (Ns > 1) {
+        if (RR <= 8 && Ns > 1) {
             // One table twiddle per butterfly, w = exp(SGN 2 pi i k / (Ns RR));
             // the others are its powers (products at most three deep), which
             // spares the memory pipeline RR - 2 gathers per butterfly.
@@ -145,12 +168,15 @@ __device__ inline void stage(C<R> (&v)[E], int jt, int NE, int N, int Ns, const 
     }
 }
 
-// LDS slot of line position a.  SWZ (lines a multiple of 32 long): the low
-// five bits are XORed with bits 3..7, which spreads both the stride-RR
-// writes and the unit-stride reads of every exchange over all banks.
-template <bool SWZ> __device__ inline int lds_slot(int a) { return SWZ ? a ^ ((a >> 3) & 31) : a; }
+// LDS slot of line position a.  SWZ = 3 (lines a multiple of 32 long): the
+// low five bits are XORed with bits 3..7, which spreads both the stride-RR
+// writes and the unit-stride reads of every exchange over all banks in the
+// radix-8 sequences.  SWZ = 2: with bits 2..6, for a radix-12 stage followed by
+// radix-4 stages (1.2 to 1.3 passes per LDS access by a bank model, against 2
+// to 4 without).  SWZ = 0: no change.
+template <int SWZ> __device__ inline int lds_slot(int a) { return SWZ ? a ^ ((a >> SWZ) & 31) : a; }
 
-template <typename R, int E, bool SWZ = false>
+template <typename R, int E, int SWZ = 0>
 __device__ inline void exchange(C<R> (&v)[E], C<R> *lds, int ls, int jt, int NE, int Ns, int RR) {
     // v[b + r*B] holds output r of butterfly j = jt + b*NE, destined for
     // position (j - k) * RR + k + r * Ns with k = j mod Ns.
@@ -195,16 +221,13 @@ __device__ inline int band_index(int i, int N, int n) {
     return -1;
 }
 
-// Row passes run 256-thread blocks, at least 4 (radix-2^k lines) or 2 (wider
-// register sets) resident per CU.
-template <typename R, int E> constexpr int fft_row_blocks() { return E == 8 ? 4 : 2; }
-// Column blocks: up to 1024 threads, 512 for the 24-element lines, whose
-// register sets would otherwise spill at 1024 threads (128 registers).
-template <int E> constexpr int fft_col_threads() { return E == 24 ? 512 : 1024; }
+// Generic lengths 2^a 3^b, 24 elements per thread: column blocks of up to 512
+// threads (the register sets would spill at 1024).
+constexpr int fft_col_threads = 512;
 
-template <typename R, int E, int SGN, bool COLS>
-__global__ void __launch_bounds__(COLS ? fft_col_threads<E>() : 256, COLS ? 1 : (fft_row_blocks<R, E>()))
-    fft_pass(FftArgs<R> a) {
+template <typename R, int SGN, bool COLS>
+__global__ void __launch_bounds__(COLS ? fft_col_threads : 256, COLS ? 1 : 2) fft_pass(FftArgs<R> a) {
+    constexpr int E = 24;
     extern __shared__ unsigned char smem_raw[];
     C<R> *smem = reinterpret_cast<C<R> *>(smem_raw);
     const int N = a.N;
@@ -253,10 +276,10 @@ __global__ void __launch_bounds__(COLS ? fft_col_threads<E>() : 256, COLS ? 1 : 
         if (s > 0) exchange<R, E>(v, lds, ls, jt, NE, Ns, a.radix[s - 1]);
         if (s > 0) Ns *= a.radix[s - 1];
         switch (RR) {
-            case 8: if constexpr (E % 8 == 0) stage<R, E, 8, SGN>(v, jt, NE, N, Ns, a.tw); break;
-            case 4: if constexpr (E % 4 == 0) stage<R, E, 4, SGN>(v, jt, NE, N, Ns, a.tw); break;
-            case 3: if constexpr (E % 3 == 0) stage<R, E, 3, SGN>(v, jt, NE, N, Ns, a.tw); break;
-            default: if constexpr (E % 2 == 0) stage<R, E, 2, SGN>(v, jt, NE, N, Ns, a.tw); break;
+            case 8: stage<R, E, 8, SGN>(v, jt, NE, N, Ns, a.tw); break;
+            case 4: stage<R, E, 4, SGN>(v, jt, NE, N, Ns, a.tw); break;
+            case 3: stage<R, E, 3, SGN>(v, jt, NE, N, Ns, a.tw); break;
+            default: stage<R, E, 2, SGN>(v, jt, NE, N, Ns, a.tw); break;
         }
     }
 
@@ -278,36 +301,49 @@ __global__ void __launch_bounds__(COLS ? fft_col_threads<E>() : 256, COLS ? 1 : 
 }
 
 // ---------------------------------------------------------------------------
-// Power-of-two lengths, N = 2^LOGN, 16 <= N <= 16384: the same pass with the
-// stage sequence fixed at compile time (radix 8 while 8 divides what is left,
-// then one radix-4 or radix-2 stage), so every index, stride and twiddle step
-// is a constant and k = j mod Ns is a mask.
+// Lengths N = 2^a and 3 2^a: the same pass with the stage sequence fixed at
+// compile time, so every index, stride and twiddle step is a constant and
+// k = j mod Ns is a mask or a division by a constant.  Powers of two: E = 8
+// elements per thread, radix 8 while 8 divides what is left, then one radix-4
+// or radix-2 stage.  3 2^a: E = 12, a radix-12 first stage (no twiddles), then
+// radix 4 and at most one radix 2.  E = 24 (radix 24, then 8) needs two
+// exchanges fewer at N = 1536 but has half the wavefronts: at N = 768 / 3072 in
+// single precision its four passes took 47 / 132 us against 36 / 124 us.  The
+// generic kernel above took 90 / 312 us there: its stage radix, and with it
+// every index of the 24 elements, is a run-time value.
+// What bounds the passes: latency (load, exchanges and store of a block run
+// back to back) at small N, at large N the 32 B column pieces and HBM.
 
-template <int N, int Ns> __host__ __device__ constexpr int p2_radix() {
-    return (N / Ns) % 8 == 0 ? 8 : (N / Ns) % 4 == 0 ? 4 : 2;
+template <int N, int E, int Ns> __host__ __device__ constexpr int ct_radix() {
+    constexpr int rest = N / Ns;
+    return E == 12 && Ns == 1 ? 12 : E == 8 && rest % 8 == 0 ? 8 : rest % 4 == 0 ? 4 : 2;
 }
 template <typename R, int E, int SGN, int N, int Ns>
-__device__ inline void p2_stages(C<R> (&v)[E], int jt, C<R> *lds, int ls, const C<R> *tw) {
-    constexpr int RR = p2_radix<N, Ns>(), NE = N / E;
+__device__ inline void ct_stages(C<R> (&v)[E], int jt, C<R> *lds, int ls, const C<R> *tw) {
+    constexpr int RR = ct_radix<N, E, Ns>(), NE = N / E;
     stage<R, E, RR, SGN>(v, jt, NE, N, Ns, tw);
     if constexpr (Ns * RR < N) {
-        exchange<R, E, (N % 32 == 0)>(v, lds, ls, jt, NE, Ns, RR);
-        p2_stages<R, E, SGN, N, Ns * RR>(v, jt, lds, ls, tw);
+        exchange<R, E, N % 32 ? 0 : E == 12 ? 2 : 3>(v, lds, ls, jt, NE, Ns, RR);
+        ct_stages<R, E, SGN, N, Ns * RR>(v, jt, lds, ls, tw);
     }
 }
+// Threads of a row block: whole lines, 256 unless one line needs more.
+template <int N, int E> constexpr int ct_row_threads() { return N / E > 256 ? N / E : 256; }
+// Resident wavefronts per SIMD that a row block's registers leave room for.
+template <typename R, int E> constexpr int ct_row_waves() { return E == 12 && sizeof(R) == 8 ? 2 : 4; }
 
-// The operator's four passes are fixed by (SGN, COLS), and the p2 kernel
+// The operator's four passes are fixed by (SGN, COLS), and the kernel
 // specialises to them: forward passes read the padded line, whose n = N/2
-// inputs sit at line positions [0, N/4) and [3N/4, N), i.e. elements e < 2
-// and e >= 6 of every thread (elements 2..5 are zero and not loaded);
+// inputs sit at line positions [0, N/4) and [3N/4, N), i.e. elements e < E/4
+// and e >= 3E/4 of every thread (the others are zero and not loaded);
 // adjoint passes write only those positions; column passes carry the
 // gridding correction and 1/K (forward: on input, adjoint: on output).  Rows
 // are contiguous (element stride 1), columns adjacent (transform stride 1),
 // so every element offset is a 32-bit index.
-template <typename R, int LOGN, int SGN, bool COLS>
-__global__ void __launch_bounds__(COLS ? 1024 : 256, COLS ? 1 : (fft_row_blocks<R, 8>()))
-fft_pass_p2(FftArgs<R> a) {
-    constexpr int N = 1 << LOGN, E = 8, NE = N / E;
+template <typename R, int N, int E, int SGN, bool COLS>
+__global__ void __launch_bounds__(COLS ? 1024 : (ct_row_threads<N, E>()), COLS ? 1 : (ct_row_waves<R, E>()))
+fft_pass_ct(FftArgs<R> a) {
+    constexpr int NE = N / E, E1 = E / 4, E3 = 3 * E / 4;
     constexpr bool FWD = SGN < 0;
     extern __shared__ unsigned char smem_raw[];
     C<R> *smem = reinterpret_cast<C<R> *>(smem_raw);
@@ -328,8 +364,8 @@ fft_pass_p2(FftArgs<R> a) {
     const bool active = t < a.nbatch;
     C<R> *lds = COLS ? smem + c : smem + (long)c * N;
     const int ls = COLS ? a.C : 1;
-    // Pixel index of band element e (e < 2 or e >= 6) of this thread.
-    auto band = [&](int e) { return e < 2 ? jt + e * NE + N / 4 : jt + e * NE - 3 * N / 4; };
+    // Pixel index of band element e (e < E1 or e >= E3) of this thread.
+    auto band = [&](int e) { return e < E1 ? jt + e * NE + N / 4 : jt + e * NE - 3 * N / 4; };
 
     const C<R> *src = COLS ? a.in + t : a.in + t * a.in_ts;
     const int ies = COLS ? (int)a.in_es : 1;
@@ -339,7 +375,7 @@ fft_pass_p2(FftArgs<R> a) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             v[e] = mk<R>(0, 0);
-            if ((e < 2 || e >= 6) && active) v[e] = src[band(e) * ies];
+            if ((e < E1 || e >= E3) && active) v[e] = src[band(e) * ies];
         }
         if constexpr (COLS) {
             if (a.cg_r) {
@@ -348,7 +384,7 @@ fft_pass_p2(FftArgs<R> a) {
                 C<R> rv[E];
 #pragma unroll
                 for (int e = 0; e < E; ++e)
-                    rv[e] = ((e < 2 || e >= 6) && active) ? a.cg_r[t + (long)band(e) * ies] : mk<R>(0, 0);
+                    rv[e] = ((e < E1 || e >= E3) && active) ? a.cg_r[t + (long)band(e) * ies] : mk<R>(0, 0);
                 // Each wavefront sums the partials itself (no barrier): lane
                 // strides, then an XOR butterfly, whose partner lanes add the
                 // same two values, so every wavefront gets the identical sums.
@@ -365,7 +401,7 @@ fft_pass_p2(FftArgs<R> a) {
                 const double beta = so == 0.0 ? 0.0 : sn / so;
 #pragma unroll
                 for (int e = 0; e < E; ++e) {
-                    if ((e < 2 || e >= 6) && active) {
+                    if ((e < E1 || e >= E3) && active) {
                         const C<R> z = v[e];
                         v[e] = mk<R>((R)((double)rv[e].x + beta * z.x), (R)((double)rv[e].y + beta * z.y));
                         const_cast<C<R> *>(a.in)[t + (long)band(e) * ies] = v[e];
@@ -374,7 +410,7 @@ fft_pass_p2(FftArgs<R> a) {
             }
 #pragma unroll
             for (int e = 0; e < E; ++e)
-                if ((e < 2 || e >= 6) && active) v[e] = cscale<R>(v[e], f0 * a.dax[band(e)]);
+                if ((e < E1 || e >= E3) && active) v[e] = cscale<R>(v[e], f0 * a.dax[band(e)]);
         }
     } else {
 #pragma unroll
@@ -386,7 +422,7 @@ fft_pass_p2(FftArgs<R> a) {
             // parts (J - 1 values per tile) are first gathered into this
             // row's LDS line at a stride W = 8 or 16 per tile, which the
             // first exchange overwrites only after its leading barrier; host
-            // side: 2 W tps <= N, so each thread gathers at most 4.
+            // side: 2 W tps <= N, so each thread gathers at most E / 2.
             if (a.halo) {
                 const int T = a.hT, J1 = a.hJ - 1, tps = a.htps, lt = __builtin_ctz(T);
                 const int lw = J1 <= 8 ? 3 : 4, NL = tps << lw;
@@ -408,9 +444,9 @@ fft_pass_p2(FftArgs<R> a) {
                     const int k2 = jt + e * NE, dc = k2 >> lt, j = k2 & (T - 1);
                     up[e] = (active && i < J1) ? hup[dc * BC + j] : mk<R>(0, 0);
                 }
-                C<R> hl[4], hu[4];
+                C<R> hl[E / 2], hu[E / 2];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
+                for (int q = 0; q < E / 2; ++q) {
                     const int f = jt + q * NE, dc = f >> lw, j = f & ((1 << lw) - 1);
                     const int lc = dc == 0 ? tps - 1 : dc - 1;
                     const bool use = active && f < NL && j < J1;
@@ -418,7 +454,7 @@ fft_pass_p2(FftArgs<R> a) {
                     hu[q] = (use && i < J1) ? hup[lc * BC + T + j] : mk<R>(0, 0);
                 }
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
+                for (int q = 0; q < E / 2; ++q) {
                     const int f = jt + q * NE;
                     if (f < NL) {
                         lds[f] = hl[q];
@@ -438,7 +474,7 @@ fft_pass_p2(FftArgs<R> a) {
             }
         }
     }
-    p2_stages<R, E, SGN, N, 1>(v, jt, lds, ls, a.tw);
+    ct_stages<R, E, SGN, N, 1>(v, jt, lds, ls, a.tw);
     C<R> *dst = COLS ? a.out + t : a.out + t * a.out_ts;
     const int oes = COLS ? (int)a.out_es : 1;
     if constexpr (FWD) {
@@ -451,7 +487,7 @@ fft_pass_p2(FftArgs<R> a) {
             const R f0 = COLS ? a.scale * a.dbt[t] : R(1);
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                if (e >= 2 && e < 6) continue;
+                if (e >= E1 && e < E3) continue;
                 const int j = band(e);
                 C<R> z = v[e];
                 if constexpr (COLS) {
@@ -481,14 +517,31 @@ fft_pass_p2(FftArgs<R> a) {
 // ---------------------------------------------------------------------------
 // Host side.
 
-static int elems_per_thread(const FftPlan &f) { return f.E; }
+// Elements per thread of the compile-time kernel for lines of N points, 0 where
+// there is none (the generic kernel serves those: N = 24 and more than one
+// factor of 3).
+static int ct_elems(int N) {
+    if ((N & (N - 1)) == 0) return 8;
+    const int m = N / 3;
+    return N % 3 == 0 && (m & (m - 1)) == 0 && N >= 48 ? 12 : 0;
+}
 
-// Transforms per column-pass block: as many as 64 KB of LDS and 1024 threads
-// allow, at most 16.
-static int col_block_transforms(const FftPlan &f, size_t cbytes) {
-    const int threads = f.E == 24 ? fft_col_threads<24>() : fft_col_threads<8>();
-    const int Cb = (int)std::min<size_t>((64 * 1024) / (cbytes * (size_t)f.N), threads / (f.N / f.E));
-    return std::max(1, std::min(Cb, 16));
+// Transforms per column-pass block: as many as 64 KB of LDS and the block's
+// threads allow, at most 16.  Short lines would then leave most of the 256 CUs
+// without a block (16 blocks at N = 512), so the compile-time kernel takes fewer
+// columns per block, down to 4 (32 B pieces in single precision), until there
+// are 256: with CG's steps folded in, N = 512 forward 11.1 -> 9.2 us, adjoint
+// 7.5 -> 5.8 us (two columns 9.5 / 5.6, at N = 128 10.8 against 7.6 us).
+static int col_block_transforms(const FftPlan &f, size_t cbytes, int nbatch) {
+    const int ct = ct_elems(f.N);
+    const int threads = ct ? 1024 : fft_col_threads, E = ct ? ct : f.E;
+    int Cb = (int)std::min<size_t>((64 * 1024) / (cbytes * (size_t)f.N), threads / (f.N / E));
+    Cb = std::max(1, std::min(Cb, 16));
+    if (ct) {
+        while (Cb & (Cb - 1)) Cb &= Cb - 1;  // a power of two: the block's sums halve it
+        while (Cb > 4 && (nbatch + Cb - 1) / Cb < 256) Cb /= 2;
+    }
+    return Cb;
 }
 
 void build_fft_plan(riop_plan *p, hipStream_t st) {
@@ -549,52 +602,49 @@ static bool launch_pass(riop_plan *p, FftArgs<R> a, int kind, hipStream_t st) {
     a.nstages = f.nstages;
     for (int i = 0; i < f.nstages; ++i) a.radix[i] = f.radix[i];
     a.tw = f.twiddle.as<C<R>>();
-    const int E = elems_per_thread(f);
-    const int NE = f.N / E;
+    const int N = f.N, ct = ct_elems(N), NE = N / (ct ? ct : f.E);
     const size_t lds_budget = 64 * 1024;
-    const size_t line = sizeof(C<R>) * (size_t)f.N;
+    const size_t line = sizeof(C<R>) * (size_t)N;
     int Cb;
     if (COLS) {
-        Cb = col_block_transforms(f, sizeof(C<R>));
+        Cb = col_block_transforms(f, sizeof(C<R>), a.nbatch);
     } else {
         Cb = std::max(1, 256 / NE);
         Cb = (int)std::max<size_t>(1, std::min<size_t>(Cb, lds_budget / line));
     }
-    RIOP_REQUIRE(COLS || Cb * NE <= 256, RIOP_ENOTSUP, "FFT row block too large");
+    RIOP_REQUIRE(COLS || Cb * NE <= (ct ? 512 : 256), RIOP_ENOTSUP, "FFT row block too large");
     a.C = Cb;
     const int threads = Cb * NE;
     RIOP_REQUIRE(threads <= 1024, RIOP_ENOTSUP, "FFT block too large");
-    const int N = f.N;
-    const bool pow2 = (N & (N - 1)) == 0 && N >= 16 && N <= 16384;
     const int blocks = (a.nbatch + Cb - 1) / Cb;
     const size_t lds = line * Cb;
-    // CG steps ride only on the power-of-two column kernel, with at most one
+    // CG steps ride only on the compile-time column kernel, with at most one
     // partial per block.
     bool fused = false;
     if (a.cg_r || a.cg_p) {
-        fused = COLS && pow2 && E == 8 && blocks <= a.cg_nred && (threads & (threads - 1)) == 0;
+        fused = COLS && ct && blocks <= a.cg_nred && (threads & (threads - 1)) == 0;
         if (!fused) a.cg_r = a.cg_p = nullptr;
     }
     TimedScope ts(p, kind, st);
-    if (pow2 && E == 8) {
+    if (ct) {
         // The specialised kernel's layout and band assumptions (see above).
         const bool fwd = SGN < 0;
         RIOP_REQUIRE(2 * a.n == N && a.pad_in == (fwd ? 1 : 0) && a.crop_out == (fwd ? 0 : 1) &&
                          (COLS ? (a.in_ts == 1 && a.out_ts == 1 && a.dax && a.dbt)
                                : (a.in_es == 1 && a.out_es == 1 && !a.dax && !a.dbt && a.scale == R(1))),
-                     RIOP_EINVAL, "FFT pass layout not supported by the power-of-two kernel");
+                     RIOP_EINVAL, "FFT pass layout not supported by the compile-time kernel");
         switch (N) {
-#define P2(LG)                                                                                        \
-    case 1 << LG:                                                                                     \
-        hipLaunchKernelGGL((fft_pass_p2<R, LG, SGN, COLS>), dim3(blocks), dim3(threads), lds, st, a); \
+#define CT(NN, EE)                                                                                         \
+    case NN:                                                                                               \
+        hipLaunchKernelGGL((fft_pass_ct<R, NN, EE, SGN, COLS>), dim3(blocks), dim3(threads), lds, st, a);  \
         break;
-            P2(4) P2(5) P2(6) P2(7) P2(8) P2(9) P2(10) P2(11) P2(12) P2(13) P2(14)
-#undef P2
+            CT(16, 8) CT(32, 8) CT(64, 8) CT(128, 8) CT(256, 8) CT(512, 8) CT(1024, 8) CT(2048, 8)
+            CT(48, 12) CT(96, 12) CT(192, 12) CT(384, 12) CT(768, 12) CT(1536, 12) CT(3072, 12) CT(6144, 12)
+#undef CT
+            default: throw Error{RIOP_ENOTSUP, "FFT length not supported"};
         }
-    } else if (E == 8) {
-        hipLaunchKernelGGL((fft_pass<R, 8, SGN, COLS>), dim3(blocks), dim3(threads), lds, st, a);
     } else {
-        hipLaunchKernelGGL((fft_pass<R, 24, SGN, COLS>), dim3(blocks), dim3(threads), lds, st, a);
+        hipLaunchKernelGGL((fft_pass<R, SGN, COLS>), dim3(blocks), dim3(threads), lds, st, a);
     }
     RIOP_HIP(hipGetLastError());
     return fused;
@@ -602,9 +652,8 @@ static bool launch_pass(riop_plan *p, FftArgs<R> a, int kind, hipStream_t st) {
 
 bool fft_folds_cg(const riop_plan *p, int nred) {
     const FftPlan &f = p->fft;
-    const int N = f.N;
-    if ((N & (N - 1)) != 0 || N < 16 || N > 16384 || f.E != 8) return false;
-    const int Cb = col_block_transforms(f, cbytes(p));
+    if (!ct_elems(f.N)) return false;
+    const int Cb = col_block_transforms(f, cbytes(p), p->n);
     return (p->n + Cb - 1) / Cb <= nred;
 }
 
@@ -665,9 +714,9 @@ bool launch_phi_fft_adjoint(riop_plan *p, void *x, hipStream_t st, const void *g
     // specialised row pass adds them on load, otherwise they are merged first.
     if (p->halo_pending) {
         const int N = p->fft.N;
-        const bool p2 = (N & (N - 1)) == 0 && N >= 16 && N <= 16384 && p->fft.E == 8;
+        const bool ct = ct_elems(N) != 0;
         const int w = p->J - 1 <= 8 ? 8 : 16;
-        if (p2 && p->halo_pending == a.in && 2 * w * p->tiles_per_side <= N) {
+        if (ct && p->halo_pending == a.in && 2 * w * p->tiles_per_side <= N) {
             a.halo = p->halo.as<C<R>>();
             a.hT = p->tile;
             a.hJ = p->J;
