@@ -285,11 +285,10 @@ constexpr int kUnit = 1024;           // visibilities per work unit
 constexpr int kDegridThreads = 256;
 constexpr int kPerThread = kUnit / kDegridThreads;
 
-template <typename R, int J, bool USER>
+template <typename R, int J>
 __device__ inline void degrid_one(const GridArgs<R> &a, const R *kc, const C<R> *reg, int W, int ta, int tb,
-                                  int v) {
-    const uint32_t cv = a.cell[v];
-    const R fu = a.frac[2 * (int64_t)v], fv = a.frac[2 * (int64_t)v + 1];
+                                  uint32_t cv, C<R> rho, int64_t dst) {
+    const R fu = rho.x, fv = rho.y;
     const int la = (int)(cv & 0xffffu) - ta, lb = (int)(cv >> 16) - tb;
     R wu_[J], wv_[J];
     kb_weights_ptr<R, J>(fu, kc, wu_);
@@ -310,14 +309,22 @@ __device__ inline void degrid_one(const GridArgs<R> &a, const R *kc, const C<R> 
         // Scheduling fence: one window row of loads in flight at a time.
         __builtin_amdgcn_sched_barrier(0);
     }
-    const int64_t dst = USER ? (int64_t)a.perm[v] : (int64_t)v;
     a.vout[dst] = mk<R>(ar, ai);
 }
 
-// Each thread handles a fixed number of visibilities, each in its own guarded
+// Each thread handles a fixed number PT of visibilities, each in its own guarded
 // block: a rolled loop gets rotated so that all J*J window loads of the next
 // visibility stay live across the back edge, which halves occupancy.
-template <typename R, int J, bool USER>
+// PT = kPerThread: one block per work unit.  PT = 1: kPerThread blocks per unit
+// (blockIdx.y), each staging the region again (see degrid_split).
+//
+// Bound by the vector unit on large plans (2 J^2 FMAs and 2 J weights per
+// visibility), by latency on small ones, so every load that can be is issued
+// before the first wait: the visibilities' cells and offsets, then
+// kStageRows region rows per wavefront at once (one row at a time before).
+// J = 8, FP32: M = 4194304 at 1024^2 51.3 -> 50.0 us (caller order, cold
+// caches 135 -> 104 us), M = 131072 at 256^2 11.8 -> 7.0 us; FP64 there 16.9 -> 9.9 us.
+template <typename R, int J, bool USER, int PT>
 __global__ void __launch_bounds__(kDegridThreads) degrid_kernel(GridArgs<R> a) {
     extern __shared__ unsigned char smem_raw[];
     C<R> *reg = reinterpret_cast<C<R> *>(smem_raw);
@@ -325,17 +332,41 @@ __global__ void __launch_bounds__(kDegridThreads) degrid_kernel(GridArgs<R> a) {
     const int W = a.T + J - 1;
     const int ta = (wu.tile / a.tps) * a.T, tb = (wu.tile % a.tps) * a.T;
     const int K = a.K;
+    // The thread's visibilities (cell, offsets, destination) are loaded first:
+    // their latency then overlaps the region's.
+    const int begin = wu.start + blockIdx.y * PT * kDegridThreads, end = wu.start + wu.count;
+    if (begin >= end) return;
+    uint32_t cv[PT];
+    C<R> rho[PT];
+    int dst[PT];
+#pragma unroll
+    for (int k = 0; k < PT; ++k) {
+        const int v = begin + threadIdx.x + k * kDegridThreads;
+        if (v < end) {
+            cv[k] = a.cell[v];
+            rho[k] = reinterpret_cast<const C<R> *>(a.frac)[v];
+            dst[k] = USER ? a.perm[v] : v;
+        }
+    }
     // Region rows by wavefront (a wave-uniform row and row address), columns
-    // by lane (no divisions).
-    for (int i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); i < W; i += kDegridThreads >> 6) {
-        int gi = ta + i;
-        if (gi >= K) gi -= K;
-        const C<R> *grow = a.grid + (int64_t)gi * K;
-        C<R> *lrow = reg + i * W;
-        for (int j = threadIdx.x & 63; j < W; j += 64) {
-            int gj = tb + j;
-            if (gj >= K) gj -= K;
-            lrow[j] = grow[gj];
+    // by lane (no divisions); kStageRows rows' loads in flight per wavefront.
+    constexpr int kStageRows = 5 * (sizeof(R) == 4 ? 2 : 1), kWaves = kDegridThreads >> 6;
+    for (int j = threadIdx.x & 63; j < W; j += 64) {
+        int gj = tb + j;
+        if (gj >= K) gj -= K;
+        for (int i0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); i0 < W; i0 += kStageRows * kWaves) {
+            C<R> g[kStageRows];
+#pragma unroll
+            for (int r = 0; r < kStageRows; ++r) {
+                int gi = ta + min(i0 + r * kWaves, W - 1);
+                if (gi >= K) gi -= K;
+                g[r] = a.grid[(int64_t)gi * K + gj];
+            }
+#pragma unroll
+            for (int r = 0; r < kStageRows; ++r) {
+                const int i = i0 + r * kWaves;
+                if (i < W) reg[i * W + j] = g[r];
+            }
         }
     }
     // Single precision: the coefficient table (32 values at J = 8) in
@@ -349,11 +380,10 @@ __global__ void __launch_bounds__(kDegridThreads) degrid_kernel(GridArgs<R> a) {
         kc = kcr;
     }
     __syncthreads();
-    const int end = wu.start + wu.count;
 #pragma unroll
-    for (int k = 0; k < kPerThread; ++k) {
-        const int v = wu.start + threadIdx.x + k * kDegridThreads;
-        if (v < end) degrid_one<R, J, USER>(a, kc, reg, W, ta, tb, v);
+    for (int k = 0; k < PT; ++k) {
+        const int v = begin + threadIdx.x + k * kDegridThreads;
+        if (v < end) degrid_one<R, J>(a, kc, reg, W, ta, tb, cv[k], rho[k], dst[k]);
     }
 }
 
@@ -1046,6 +1076,14 @@ template <typename R> static GridArgs<R> grid_args(riop_plan *p) {
 
 #define RIOP_J_CASES(MACRO) MACRO(2) MACRO(4) MACRO(6) MACRO(8) MACRO(10) MACRO(12) MACRO(14) MACRO(16)
 
+// Whether a unit's visibilities are spread over kPerThread blocks.  Restaging
+// the region costs less than idle compute units do while there are few units:
+// J = 8, FP32, 1500 units 17.7 -> 14.8 us, 6900 units 53.5 -> 58.2 us, 9000
+// units 52.0 -> 53.1 us.  In double precision always: the registers of
+// kPerThread visibilities leave 3 wavefronts per SIMD instead of 8 (6900 units
+// 140 against 115 us).
+template <typename R> static bool degrid_split(int nunits) { return sizeof(R) == 8 || nunits < 4096; }
+
 template <typename R>
 static void launch_degrid_from(riop_plan *p, const void *grid, void *y, int order_user, hipStream_t st) {
     if (p->nunits == 0) return;
@@ -1055,15 +1093,22 @@ static void launch_degrid_from(riop_plan *p, const void *grid, void *y, int orde
     a.order_user = order_user;
     const int W = p->tile + p->J - 1;
     const size_t lds = sizeof(C<R>) * W * W;
+    const bool split = degrid_split<R>(p->nunits);
+    const dim3 g(p->nunits, split ? kPerThread : 1), t(kDegridThreads);
     TimedScope ts(p, KK_DEGRID, st);
     switch (p->J) {
-#define DG(JJ) \
-    case JJ:                                                                                          \
-        if (order_user)                                                                               \
-            hipLaunchKernelGGL((degrid_kernel<R, JJ, true>), dim3(p->nunits), dim3(kDegridThreads), lds, st, a); \
-        else                                                                                          \
-            hipLaunchKernelGGL((degrid_kernel<R, JJ, false>), dim3(p->nunits), dim3(kDegridThreads), lds, st, a); \
-        break;
+#define DG(JJ)                                                                                         \
+    case JJ: {                                                                                         \
+        constexpr int PT = sizeof(R) == 4 ? kPerThread : 1;                                            \
+        if (split) {                                                                                   \
+            if (order_user) hipLaunchKernelGGL((degrid_kernel<R, JJ, true, 1>), g, t, lds, st, a);     \
+            else hipLaunchKernelGGL((degrid_kernel<R, JJ, false, 1>), g, t, lds, st, a);               \
+        } else {                                                                                       \
+            if (order_user) hipLaunchKernelGGL((degrid_kernel<R, JJ, true, PT>), g, t, lds, st, a);    \
+            else hipLaunchKernelGGL((degrid_kernel<R, JJ, false, PT>), g, t, lds, st, a);              \
+        }                                                                                              \
+        break;                                                                                         \
+    }
         RIOP_J_CASES(DG)
 #undef DG
         default: throw Error{RIOP_ENOTSUP, "unsupported kernel width"};
