@@ -256,6 +256,10 @@ namespace riop {
 inline size_t cbytes(const riop_plan *p) { return p->prec == RIOP_F64 ? 16 : 8; }
 inline size_t rbytes(const riop_plan *p) { return p->prec == RIOP_F64 ? 8 : 4; }
 
+// Doubles per partial-sum slot of the device reductions (kernels that fill a
+// slot run at most this many blocks and zero the rest).
+constexpr int kRedBlocks = 512;
+
 // Launch helpers implemented in the kernel translation units.  All take the
 // plan's real type as a template parameter and enqueue on `st`.
 // CG steps the column FFT passes can fold in (CG on Q = Phi^dagger Phi + 2 I,
@@ -263,16 +267,16 @@ inline size_t rbytes(const riop_plan *p) { return p->prec == RIOP_F64 ? 8 : 4; }
 // p <- r + beta p with beta = sum(part[slot_new]) / sum(part[slot_old]) (0 when
 // the old sum is 0); after an adjoint transform into q, q <- q + 2 p with the
 // per-block partials of sum Re(conj(p) q) left in part[slot_pq].  `part` holds
-// nred doubles per slot.
+// kRedBlocks doubles per slot.
 template <typename R> struct CgFuse {
     const C<R> *r = nullptr;  // residual (direction update), nullable
     const C<R> *p = nullptr;  // direction (p.q), nullable
     double *part = nullptr;
-    int nred = 0, slot_old = 0, slot_new = 0, slot_pq = 0;
+    int slot_old = 0, slot_new = 0, slot_pq = 0;
 };
-// Whether the column passes fold in the CG steps of CgFuse with nred partials
-// per slot (the compile-time kernel with at most nred column blocks).
-bool fft_folds_cg(const riop_plan *p, int nred);
+// Whether the column passes fold in the CG steps of CgFuse (the compile-time
+// kernel with at most kRedBlocks column blocks).
+bool fft_folds_cg(const riop_plan *p);
 // Forward FFT passes; returns whether cg->r's direction update was folded in
 // (false: the caller must apply it first; nothing was done).
 template <typename R>

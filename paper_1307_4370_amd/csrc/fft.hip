@@ -36,10 +36,10 @@ template <typename R> struct FftArgs {
     // with cg_r set, the input p is replaced by r + beta p first and written
     // back, beta = sum(cg_part[cg_new]) / sum(cg_part[cg_old]).  Adjoint: with
     // cg_p set, the output q becomes q + 2 p and each block leaves its part of
-    // sum Re(conj(p) q) in cg_part[cg_pq] (cg_nred doubles per slot).
+    // sum Re(conj(p) q) in cg_part[cg_pq] (kRedBlocks doubles per slot).
     const C<R> *cg_r, *cg_p;
     double *cg_part;
-    int cg_nred, cg_old, cg_new, cg_pq;
+    int cg_old, cg_new, cg_pq;
     int N, nbatch, C, n;
     int pad_in, crop_out;
     int factors_at_input;
@@ -386,13 +386,30 @@ fft_pass_ct(FftArgs<R> a) {
                 for (int e = 0; e < E; ++e)
                     rv[e] = ((e < E1 || e >= E3) && active) ? a.cg_r[t + (long)band(e) * ies] : mk<R>(0, 0);
                 // Each wavefront sums the partials itself (no barrier): lane
-                // strides, then an XOR butterfly, whose partner lanes add the
-                // same two values, so every wavefront gets the identical sums.
+                // strides, all loads issued together (a loop of run-time length
+                // waited for each: 4 us of a 9 us pass at N = 512), then an XOR
+                // butterfly, whose partner lanes add the same two values, so
+                // every wavefront gets the identical sums.
                 const int width = blockDim.x < 64 ? (int)blockDim.x : 64;
+                const double *po = a.cg_part + a.cg_old * kRedBlocks, *pn = a.cg_part + a.cg_new * kRedBlocks;
                 double so = 0.0, sn = 0.0;
-                for (int i = threadIdx.x & 63; i < a.cg_nred; i += width) {
-                    so += a.cg_part[a.cg_old * a.cg_nred + i];
-                    sn += a.cg_part[a.cg_new * a.cg_nred + i];
+                if (width == 64) {
+                    double vo[kRedBlocks / 64], vn[kRedBlocks / 64];
+#pragma unroll
+                    for (int i = 0; i < kRedBlocks / 64; ++i) {
+                        vo[i] = po[(threadIdx.x & 63) + 64 * i];
+                        vn[i] = pn[(threadIdx.x & 63) + 64 * i];
+                    }
+#pragma unroll
+                    for (int i = 0; i < kRedBlocks / 64; ++i) {
+                        so += vo[i];
+                        sn += vn[i];
+                    }
+                } else {
+                    for (int i = threadIdx.x & 63; i < kRedBlocks; i += width) {
+                        so += po[i];
+                        sn += pn[i];
+                    }
                 }
                 for (int o = width >> 1; o > 0; o >>= 1) {
                     so += __shfl_xor(so, o);
@@ -505,10 +522,10 @@ fft_pass_ct(FftArgs<R> a) {
         if constexpr (COLS) {
             if (a.cg_p) {
                 acc = block_sum_all(acc, reinterpret_cast<double *>(smem));
-                double *slot = a.cg_part + (long)a.cg_pq * a.cg_nred;
+                double *slot = a.cg_part + (long)a.cg_pq * kRedBlocks;
                 if (threadIdx.x == 0) slot[blockIdx.x] = acc;
                 if (blockIdx.x == 0)  // entries past the grid's blocks
-                    for (int i = gridDim.x + threadIdx.x; i < a.cg_nred; i += blockDim.x) slot[i] = 0.0;
+                    for (int i = gridDim.x + threadIdx.x; i < kRedBlocks; i += blockDim.x) slot[i] = 0.0;
             }
         }
     }
@@ -622,7 +639,7 @@ static bool launch_pass(riop_plan *p, FftArgs<R> a, int kind, hipStream_t st) {
     // partial per block.
     bool fused = false;
     if (a.cg_r || a.cg_p) {
-        fused = COLS && ct && blocks <= a.cg_nred && (threads & (threads - 1)) == 0;
+        fused = COLS && ct && blocks <= kRedBlocks && (threads & (threads - 1)) == 0;
         if (!fused) a.cg_r = a.cg_p = nullptr;
     }
     TimedScope ts(p, kind, st);
@@ -650,11 +667,11 @@ static bool launch_pass(riop_plan *p, FftArgs<R> a, int kind, hipStream_t st) {
     return fused;
 }
 
-bool fft_folds_cg(const riop_plan *p, int nred) {
+bool fft_folds_cg(const riop_plan *p) {
     const FftPlan &f = p->fft;
     if (!ct_elems(f.N)) return false;
     const int Cb = col_block_transforms(f, cbytes(p), p->n);
-    return (p->n + Cb - 1) / Cb <= nred;
+    return (p->n + Cb - 1) / Cb <= kRedBlocks;
 }
 
 template <typename R>
@@ -680,7 +697,6 @@ bool launch_phi_fft_forward(riop_plan *p, const void *x, hipStream_t st, const C
     if (cg && cg->r) {
         a.cg_r = cg->r;
         a.cg_part = cg->part;
-        a.cg_nred = cg->nred;
         a.cg_old = cg->slot_old;
         a.cg_new = cg->slot_new;
     }
@@ -757,7 +773,6 @@ bool launch_phi_fft_adjoint(riop_plan *p, void *x, hipStream_t st, const void *g
     if (cg && cg->p) {
         b.cg_p = cg->p;
         b.cg_part = cg->part;
-        b.cg_nred = cg->nred;
         b.cg_pq = cg->slot_pq;
     }
     return launch_pass<R, +1, true>(p, b, KK_FFT_ADJ_COL, st);

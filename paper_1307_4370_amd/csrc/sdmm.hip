@@ -27,8 +27,6 @@
 
 namespace riop {
 
-
-constexpr int kRedBlocks = 512;
 constexpr int kRedThreads = 256;
 
 // Partial-sum slots (each kRedBlocks doubles).
@@ -41,42 +39,59 @@ enum Slot { SLOT_RR0 = 0, SLOT_RR1, SLOT_PQ, SLOT_E, SLOT_NU, SLOT_MAX, SLOT_F1,
 enum Scalar { SC_GAMMA = 0, SC_F1ACC, SC_F1PREV, SC_EPS, SC_RRFINAL, SC_ITER, SC_GAMMA_Q, SC_P2SCALE, SC_RR0, SC_CGIT,
               kScalars };
 
-__device__ inline double block_sum(double v) {
-    __shared__ double red[kRedThreads];
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = kRedThreads / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-        __syncthreads();
+// Block sums of two values (or the sum of one), returned to every thread:
+// lane shuffles inside each wavefront, then one barrier and a sum of the four
+// wavefronts' values in a fixed order.  `red` is LDS of its own for each use in
+// a kernel, so no second barrier guards it.
+struct Red2 {
+    double a[kRedThreads / 64], b[kRedThreads / 64];
+};
+__device__ inline void block_sum2(double &a, double &b, Red2 &red) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o);
+        b += __shfl_xor(b, o);
     }
-    const double r = red[0];
+    if ((threadIdx.x & 63) == 0) {
+        red.a[threadIdx.x >> 6] = a;
+        red.b[threadIdx.x >> 6] = b;
+    }
+    __syncthreads();
+    a = (red.a[0] + red.a[1]) + (red.a[2] + red.a[3]);
+    b = (red.b[0] + red.b[1]) + (red.b[2] + red.b[3]);
+}
+
+__device__ inline double block_sum(double v) {
+    __shared__ double red[kRedThreads / 64];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    const double r = (red[0] + red[1]) + (red[2] + red[3]);
     __syncthreads();
     return r;
 }
 
 __device__ inline double block_max(double v) {
-    __shared__ double red[kRedThreads];
-    red[threadIdx.x] = v;
+    __shared__ double red[kRedThreads / 64];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int off = kRedThreads / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + off]);
-        __syncthreads();
-    }
-    const double r = red[0];
+    const double r = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
     __syncthreads();
     return r;
 }
 
-// Sum of one slot's partials, in a fixed order, computed by the whole block.
-__device__ inline double slot_sum(const double *partials, int slot) {
-    __shared__ double tot;
+// This thread's part of one slot's partials (kRedBlocks / kRedThreads of them),
+// in a fixed order; block_sum of it is the slot's sum.
+__device__ inline double slot_part(const double *partials, int slot) {
     double v = 0;
-    for (int i = threadIdx.x; i < kRedBlocks; i += kRedThreads) v += partials[slot * kRedBlocks + i];
-    const double s = block_sum(v);
-    if (threadIdx.x == 0) tot = s;
-    __syncthreads();
-    return tot;
+#pragma unroll
+    for (int i = 0; i < kRedBlocks; i += kRedThreads) v += partials[slot * kRedBlocks + i + threadIdx.x];
+    return v;
 }
+__device__ inline double slot_sum(const double *partials, int slot) { return block_sum(slot_part(partials, slot)); }
 
 #define GRID_LOOP(i, n) for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < (n); i += (long)gridDim.x * blockDim.x)
 
@@ -163,8 +178,9 @@ __global__ void cg_update(C<R> *x, C<R> *r, const C<R> *p, const C<R> *qp, long 
         }
     };
     load(i0);
-    const double rr = slot_sum(partials, slot_old);
-    const double pq = slot_sum(partials, slot_pq);
+    __shared__ Red2 red;
+    double rr = slot_part(partials, slot_old), pq = slot_part(partials, slot_pq);
+    block_sum2(rr, pq, red);
     const double rr0 = first ? rr : scalars[SC_RR0];
     const bool converged = tol2 > 0.0 && rr <= tol2 * rr0;
     const double alpha = (rr == 0.0 || pq == 0.0 || converged) ? 0.0 : rr / pq;
@@ -187,7 +203,6 @@ __global__ void cg_update(C<R> *x, C<R> *r, const C<R> *p, const C<R> *qp, long 
             acc += abs2<R>(ri);
         }
     }
-    __syncthreads();
     const double s = block_sum(acc);
     if (threadIdx.x == 0) partials[slot_new * kRedBlocks + blockIdx.x] = s;
 }
@@ -195,8 +210,9 @@ __global__ void cg_update(C<R> *x, C<R> *r, const C<R> *p, const C<R> *qp, long 
 // beta = rr_new / rr_old ; p = r + beta p
 template <typename R>
 __global__ void cg_direction(const C<R> *r, C<R> *p, long N, const double *partials, int slot_old, int slot_new) {
-    const double rr_old = slot_sum(partials, slot_old);
-    const double rr_new = slot_sum(partials, slot_new);
+    __shared__ Red2 red;
+    double rr_old = slot_part(partials, slot_old), rr_new = slot_part(partials, slot_new);
+    block_sum2(rr_old, rr_new, red);
     const double beta = rr_old == 0.0 ? 0.0 : rr_new / rr_old;
     CHUNK_LOOP(i0, st, N) {
         C<R> rv[kU], pv[kU];
@@ -272,11 +288,11 @@ __global__ void prox2_norms(const C<R> *s, const C<R> *z2, const C<R> *y, long M
             nu += fr * fr + fi * fi;
         }
     }
-    const double se = block_sum(e);
-    const double sn = block_sum(nu);
+    __shared__ Red2 red;
+    block_sum2(e, nu, red);
     if (threadIdx.x == 0) {
-        partials[SLOT_E * kRedBlocks + blockIdx.x] = se;
-        partials[SLOT_NU * kRedBlocks + blockIdx.x] = sn;
+        partials[SLOT_E * kRedBlocks + blockIdx.x] = e;
+        partials[SLOT_NU * kRedBlocks + blockIdx.x] = nu;
     }
 }
 
@@ -340,9 +356,11 @@ __global__ void f1_partials(const double *f1part, int f1_count, double *partials
 // iteration counter (so a captured graph can be replayed); f1_prev <- f1;
 // t <- t + 1.
 __global__ void record_stats(const double *partials, double *scalars, double *hist, int cap, int rr_slot) {
-    const double nu2 = slot_sum(partials, SLOT_NU);
-    const double rr = slot_sum(partials, rr_slot);
-    const double f1 = slot_sum(partials, SLOT_F1);
+    __shared__ Red2 red;
+    double nu2 = slot_part(partials, SLOT_NU), rr = slot_part(partials, rr_slot);
+    const double f1v = slot_part(partials, SLOT_F1);
+    block_sum2(nu2, rr, red);
+    const double f1 = block_sum(f1v);
     if (threadIdx.x == 0) {
         const int t = (int)scalars[SC_ITER];
         scalars[SC_F1ACC] = f1;
@@ -708,13 +726,12 @@ static void cg_run(riop_plan *p, const void *b, void *x, int n_iter, double tol,
     // (before transforming p) and form q + 2 p with its p.q partials (after);
     // otherwise the vector kernels do.  The direction of the last iteration is
     // never needed and is not formed.
-    const bool fold = fft_folds_cg(p, kRedBlocks);
+    const bool fold = fft_folds_cg(p);
     int cur = SLOT_RR0;
     for (int k = 0; k < n_iter; ++k) {
         const int nxt = cur == SLOT_RR0 ? SLOT_RR1 : SLOT_RR0;
         CgFuse<R> cg;
         cg.part = part;
-        cg.nred = kRedBlocks;
         cg.slot_pq = SLOT_PQ;
         if (k > 0) {  // p = r + beta p, beta = rr[cur] / rr[previous]
             if (fold) {
