@@ -501,7 +501,6 @@ riop_status riop_plan_create(const riop_desc *desc, const void *uv, void *stream
         p->tmp.alloc(cb * (size_t)p->K * p->n);
         p->grid.alloc(cb * (size_t)p->K * p->K);
         p->grid2.alloc(cb * (size_t)p->K * p->K);
-        p->halo.alloc(cb * (size_t)p->ntiles * grid_halo_cells(p->tile, p->J));
         p->vis.alloc(cb * (size_t)std::max<int64_t>(1, p->M));
         p->img.alloc(cb * N);
         size_t lls = 0;

@@ -197,9 +197,10 @@ struct riop_plan {
     riop::DevBuf tile_start;  // int32[ntiles + 1]
     riop::DevBuf units;       // WorkUnit[nunits] (degridding)
     riop::DevBuf cell_start;  // int32[K^2 + 1]: plan-order start of each cell key
-    riop::DevBuf tile_order;  // WorkUnit[ntiles]: tiles with their visibility ranges, heaviest first (gridding)
-    riop::DevBuf halo;        // per tile: region cells outside the tile (gridding)
-    void *halo_pending = nullptr;  // grid last written by gridding, its tiles' halos not yet added
+    int band = 0, nbands = 0;   // gridding: rows of a band of a tile, bands in all
+    riop::DevBuf tile_order;  // WorkUnit[nbands]: bands with their visibility ranges, heaviest first (gridding)
+    riop::DevBuf halo;        // per band: region cells outside it (gridding)
+    void *halo_pending = nullptr;  // grid last written by gridding, its bands' halos not yet added
     int nunits = 0;
     int max_unit = 0;
 
@@ -289,8 +290,6 @@ bool launch_phi_fft_adjoint(riop_plan *p, void *x, hipStream_t st, const void *g
 // out_grid = G^T G in_grid (fused degrid + grid, the Gram part of Phi^dagger Phi).
 // Throws RIOP_ENOTSUP if the plan's gridding tile needs more LDS than the device has.
 void check_grid_lds(riop_plan *p);
-// Complex halo cells of one gridding tile (right strip and bottom strip).
-inline int grid_halo_cells(int T, int J) { return T * (J - 1) + (J - 1) * (T + J - 1); }
 template <typename R> void launch_gram(riop_plan *p, const void *in_grid, void *out_grid, hipStream_t st);
 // Precomputed G^T G: planes per offset for width J, build (synchronises) and apply.
 int gram_planes(int J);

@@ -29,9 +29,9 @@ template <typename R> struct FftArgs {
     long in_ts, in_es;   // strides (in complex elements) between transforms / elements
     long out_ts, out_es;
     // Adjoint row pass of the compile-time kernel: gridding halos to add on
-    // load (nullptr: none), with the gridding tile side, J and tiles per side.
+    // load (nullptr: none), with the gridding tile side, band rows, J and tiles per side.
     const C<R> *halo;
-    int hT, hJ, htps;
+    int hT, hTB, hJ, htps;
     // CG steps folded into the column passes (compile-time kernel).  Forward:
     // with cg_r set, the input p is replaced by r + beta p first and written
     // back, beta = sum(cg_part[cg_new]) / sum(cg_part[cg_old]).  Adjoint: with
@@ -433,8 +433,8 @@ fft_pass_ct(FftArgs<R> a) {
 #pragma unroll
         for (int e = 0; e < E; ++e) v[e] = active ? src[(jt + e * NE) * ies] : mk<R>(0, 0);
         if constexpr (!COLS) {
-            // Gridding halos: a tile's first J - 1 rows and columns receive
-            // what the tiles above, to the left and above-left left in their
+            // Gridding halos: a band's first J - 1 rows and columns receive
+            // what the bands above, to the left and above-left left in their
             // halo cells, added in that order.  The row's left and above-left
             // parts (J - 1 values per tile) are first gathered into this
             // row's LDS line at a stride W = 8 or 16 per tile, which the
@@ -446,14 +446,14 @@ fft_pass_ct(FftArgs<R> a) {
                 // Halo layout (gridding): the right strips by grid row, so
                 // the left parts of row k1 are one contiguous run of
                 // tps (J - 1) cells; then the bottom strips (with the corner)
-                // tile by tile, BC = (J - 1)(T + J - 1) cells each.
+                // band by band, BC = (J - 1)(T + J - 1) cells each.
                 const int BC = J1 * (T + J1);
-                const int k1 = (int)t, dr = k1 >> lt, i = k1 & (T - 1);
-                const int upr = dr == 0 ? tps - 1 : dr - 1;
+                const int k1 = (int)t, lb = __builtin_ctz(a.hTB), dr = k1 >> lb, i = k1 & (a.hTB - 1);
+                const int upr = dr == 0 ? (N >> lb) - 1 : dr - 1;
                 const C<R> *hrow = a.halo + (long)k1 * tps * J1;                            // left parts
                 const C<R> *hup = a.halo + (long)tps * tps * T * J1 + (long)upr * tps * BC +
                                   i * (T + J1);                                             // above, above-left
-                // The above tile's part (rows i < J - 1), loaded with the
+                // The above band's part (rows i < J - 1), loaded with the
                 // line so that the latencies overlap.
                 C<R> up[E];
 #pragma unroll
@@ -726,7 +726,7 @@ bool launch_phi_fft_adjoint(riop_plan *p, void *x, hipStream_t st, const void *g
     // Pass 1: rows k1 of grid, inverse transform over k2, keep the n cropped outputs.
     FftArgs<R> a{};
     a.in = grid ? static_cast<const C<R> *>(grid) : p->grid.as<C<R>>();
-    // A grid just written by gridding still lacks its tiles' halos: the
+    // A grid just written by gridding still lacks its bands' halos: the
     // specialised row pass adds them on load, otherwise they are merged first.
     if (p->halo_pending) {
         const int N = p->fft.N;
@@ -735,6 +735,7 @@ bool launch_phi_fft_adjoint(riop_plan *p, void *x, hipStream_t st, const void *g
         if (ct && p->halo_pending == a.in && 2 * w * p->tiles_per_side <= N) {
             a.halo = p->halo.as<C<R>>();
             a.hT = p->tile;
+            a.hTB = p->band;
             a.hJ = p->J;
             a.htps = p->tiles_per_side;
         } else {

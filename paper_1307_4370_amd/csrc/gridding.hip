@@ -15,16 +15,17 @@
 // Neighbouring threads hold neighbouring cells, which keeps LDS bank conflicts
 // low.
 //
-// Gridding (G^T): one workgroup per sort tile.  Its visibilities are one
-// contiguous plan-order range and their windows reach only the tile and the
+// Gridding (G^T): one workgroup per band, TB rows of a sort tile (TB = T where
+// the tiles alone keep the GPU busy; see choose_band).  Its visibilities are one
+// contiguous plan-order range and their windows reach only the band and the
 // first J - 1 rows / columns of its neighbours below and to the right.  The
-// workgroup accumulates them into that (T + J - 1)-sided region, held in
+// workgroup accumulates them into that region, held in
 // double precision in LDS (runs of visibilities that share a window row and an
 // 8-aligned column block are summed in registers, on the matrix cores where
 // possible, and closed with LDS double atomic adds: floating-point LDS
 // atomics in single precision are slow on this GPU), then stores its own
 // cells to the grid and the rest to its halo cells; a second kernel adds each
-// tile's three incoming halos.  No zeroing of the grid, no global atomics,
+// band's three incoming halos.  No zeroing of the grid, no global atomics,
 // and every visibility is read once.
 //
 // Kernel weights: for tap j the weight phi(rho + J/2 - 1 - j) is a polynomial
@@ -233,9 +234,10 @@ __global__ void gather_layout(const int *__restrict__ perm, const uint32_t *__re
     frac[2 * i + 1] = frac_of[2 * (int64_t)m + 1];
 }
 
-__global__ void tile_start_from_keys(const int *__restrict__ start, int ntiles, int T2, int *__restrict__ ts) {
+// ts[t] = start[t * step], t = 0 .. count.
+__global__ void every_start(const int *__restrict__ start, int count, int step, int *__restrict__ ts) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t <= ntiles) ts[t] = start[(int64_t)t * T2];
+    if (t <= count) ts[t] = start[(int64_t)t * step];
 }
 
 // ---------------------------------------------------------------------------
@@ -281,6 +283,7 @@ template <typename R> struct GridArgs {
     int order_user;
 };
 
+constexpr int kBandRows = 8;          // rows of the narrowest gridding band
 constexpr int kUnit = 1024;           // visibilities per work unit
 constexpr int kDegridThreads = 256;
 constexpr int kPerThread = kUnit / kDegridThreads;
@@ -388,7 +391,7 @@ __global__ void __launch_bounds__(kDegridThreads) degrid_kernel(GridArgs<R> a) {
 }
 
 // ---------------------------------------------------------------------------
-// Gridding: one workgroup per sort tile.
+// Gridding: one workgroup per band of a sort tile.
 
 // Windows up to 8 wide are accumulated with matrix instructions
 // (v_mfma_f32_16x16x4_f32, v_mfma_f64_16x16x4_f64: the same operand layouts;
@@ -424,10 +427,11 @@ template <typename R> __host__ __device__ constexpr int grid_stage_bytes(int J) 
     return ((int)sizeof(C<R>) * (grid_mfma<R>(J) ? 8 : J) + (int)sizeof(R) * 8 * ((J + 7) / 8 + 1)) * slice_row<R>(J);
 }
 
-// Region of a T x T tile: the cells its visibilities' windows reach, rows
-// 0 .. T + J - 2 and columns 0 .. T + 8 NB - 1 (the run blocks are 8 NB + 8
-// wide and start at a multiple of 8 below T), held as two double planes.
-__host__ __device__ constexpr int region_rows(int T, int J) { return T + J - 1; }
+// Region of a band (TB rows of a T x T tile): the cells its visibilities'
+// windows reach, rows 0 .. TB + J - 2 and columns 0 .. T + 8 NB - 1 (the run
+// blocks are 8 NB + 8 wide and start at a multiple of 8 below T), held as two
+// double planes.
+__host__ __device__ constexpr int region_rows(int TB, int J) { return TB + J - 1; }
 __host__ __device__ constexpr int region_stride(int T, int J) { return T + 8 * ((J + 7) / 8); }
 
 // Wavefronts per workgroup: of 6, 4 and 2, the count that keeps the most
@@ -440,37 +444,36 @@ template <typename R> __host__ __device__ constexpr int grid_waves(int J) {
     return (w6 >= w4 && w6 >= w2 && w6 > 0) ? 6 : (w4 >= w2 && w4 > 0) ? 4 : 2;
 }
 
-template <typename R> static size_t grid_lds(int T, int J, int waves) {
-    return sizeof(double) * 2 * (size_t)region_rows(T, J) * region_stride(T, J) +
+template <typename R> static size_t grid_lds(int TB, int T, int J, int waves) {
+    return sizeof(double) * 2 * (size_t)region_rows(TB, J) * region_stride(T, J) +
            (size_t)grid_stage_bytes<R>(J) * waves + sizeof(R) * (size_t)J * (KDeg<R>::D / 2 + 1);
 }
 
-// Halo of a tile: the region cells outside it, which belong to the tiles to
-// the right (right strip, T x (J-1)), below and below-right (bottom strip,
+// Halo of a band: the region cells outside it, which belong to the bands to
+// the right (right strip, TB x (J-1)), below and below-right (bottom strip,
 // (J-1) x (T+J-1)).
-__host__ __device__ constexpr int halo_cells(int T, int J) { return T * (J - 1) + (J - 1) * (T + J - 1); }
-// Halo buffer layout.  Right strips first, by grid row: row i of tile (dr,
-// dc) at ((dr T + i) tps + dc) (J - 1), so that the left parts one grid row
+// Halo buffer layout.  Right strips first, by grid row: row `row` of tile
+// column dc at (row tps + dc) (J - 1), so that the left parts one grid row
 // receives are one contiguous run of tps (J - 1) cells.  Then the bottom
-// strips (with the corner), tile by tile: (J - 1) rows of T + J - 1 cells at
-// ntiles T (J - 1) + t (J - 1)(T + J - 1).
-__host__ __device__ inline int64_t halo_right(int T, int J, int tps, int dr, int i, int dc) {
-    return ((int64_t)(dr * T + i) * tps + dc) * (J - 1);
+// strips (with the corner), band by band (band row br = row / TB): (J - 1) rows
+// of T + J - 1 cells at K tps (J - 1) + (br tps + dc)(J - 1)(T + J - 1).
+__host__ __device__ inline int64_t halo_right(int J, int tps, int row, int dc) {
+    return ((int64_t)row * tps + dc) * (J - 1);
 }
-__host__ __device__ inline int64_t halo_bottom(int T, int J, int tps, int t) {
-    return (int64_t)tps * tps * T * (J - 1) + (int64_t)t * (J - 1) * (T + J - 1);
+__host__ __device__ inline int64_t halo_bottom(int T, int J, int tps, int br, int dc) {
+    return (int64_t)tps * tps * T * (J - 1) + ((int64_t)br * tps + dc) * (J - 1) * (T + J - 1);
 }
 
 template <typename R> struct TileArgs {
-    C<R> *grid;               // own T x T cells of every tile
-    C<R> *halo;               // halo_cells(T, J) per tile
+    C<R> *grid;               // own TB x T cells of every band
+    C<R> *halo;               // right and bottom strips of every band
     const uint32_t *cell;     // plan order: a0 | b0 << 16
     const R *frac;            // plan order: rho_u, rho_v
     const int *perm;          // plan order -> caller order
-    const WorkUnit *order;    // tiles, heaviest first: (tile, first visibility, count)
+    const WorkUnit *order;    // bands, heaviest first: (tile T/TB + band in the tile, first visibility, count)
     const C<R> *vin;          // values to grid
     const R *__restrict__ kc; // kernel coefficients [pair][even/odd][D/2 + 1]
-    int K, T, tps;            // grid side, tile side, tiles per side
+    int K, T, TB, tps;        // grid side, tile side, band rows, tiles per side
     // Fused l2-ball prox (P2 kernels, plan order): the values gridded are
     // d2 = r2 - z2' - s with v = s + z2, r2 = y + (v - y) scale, z2' = v - r2,
     // and z2' replaces z2.
@@ -479,20 +482,20 @@ template <typename R> struct TileArgs {
     const double *p2scale;    // min(1, eps / ||v - y||), one value
 };
 
-// Own cells of tile t to the grid, the rest of its region to its halo cells.
-// T is a power of two (shifts and masks); the bottom strip's row is found by
-// a single-precision reciprocal, exact here: cell index and strip width are
-// small integers, so (c + 1/2) / W stays at least 1 / (2 W) away from the
-// integers.
+// Own cells of the band at (ta, tb) to the grid, the rest of its region to its
+// halo cells.  T and TB are powers of two (shifts and masks); the bottom strip's
+// row is found by a single-precision reciprocal, exact here: cell index and
+// strip width are small integers, so (c + 1/2) / W stays at least 1 / (2 W) away
+// from the integers.
 template <typename R, int J>
-__device__ inline void store_region(const TileArgs<R> &a, const double *tre, const double *tim, int t, int tid,
-                                    int nthreads) {
-    const int T = a.T, K = a.K, RS = region_stride(T, J), lt = __builtin_ctz(T);
-    const int ta = (t / a.tps) * T, tb = (t % a.tps) * T;
-    C<R> *gbase = a.grid + (int64_t)ta * K + tb;  // T rows of K cells: 32-bit offsets below
+__device__ inline void store_region(const TileArgs<R> &a, const double *tre, const double *tim, int ta, int tb,
+                                    int tid, int nthreads) {
+    const int T = a.T, TB = a.TB, K = a.K, RS = region_stride(T, J), lt = __builtin_ctz(T);
+    const int dc = tb >> lt, br = ta >> __builtin_ctz(TB);
+    C<R> *gbase = a.grid + (int64_t)ta * K + tb;  // TB rows of K cells: 32-bit offsets below
     // Two horizontally adjacent cells per step (T and RS are even): 16-byte
     // LDS reads of each plane.
-    for (int c2 = tid; c2 < T * T / 2; c2 += nthreads) {
+    for (int c2 = tid; c2 < TB * T / 2; c2 += nthreads) {
         const int c = 2 * c2, r = c >> lt, col = c & (T - 1);
         const double2 re = *reinterpret_cast<const double2 *>(tre + r * RS + col);
         const double2 im = *reinterpret_cast<const double2 *>(tim + r * RS + col);
@@ -501,23 +504,23 @@ __device__ inline void store_region(const TileArgs<R> &a, const double *tre, con
         g[1] = mk<R>((R)re.y, (R)im.y);
     }
     // Right strip: J - 1 cells of each row, rows tps (J - 1) apart.
-    C<R> *right = a.halo + halo_right(T, J, a.tps, t / a.tps, 0, t % a.tps);
+    C<R> *right = a.halo + halo_right(J, a.tps, ta, dc);
     const int rstride = a.tps * (J - 1);
-    for (int c = tid; c < T * (J - 1); c += nthreads) {
+    for (int c = tid; c < TB * (J - 1); c += nthreads) {
         const int r = c / (J - 1), jj = c - r * (J - 1);
         right[(int64_t)r * rstride + jj] = mk<R>((R)tre[r * RS + T + jj], (R)tim[r * RS + T + jj]);
     }
-    C<R> *bottom = a.halo + halo_bottom(T, J, a.tps, t);
+    C<R> *bottom = a.halo + halo_bottom(T, J, a.tps, br, dc);
     const int W = T + J - 1;
     const float inv = 1.0f / (float)W;
     for (int c = tid; c < (J - 1) * W; c += nthreads) {  // bottom strip with the corner
         const int q = (int)(((float)c + 0.5f) * inv);
-        const int r = T + q, col = c - q * W;
+        const int r = TB + q, col = c - q * W;
         bottom[c] = mk<R>((R)tre[r * RS + col], (R)tim[r * RS + col]);
     }
 }
 
-// A tile's visibilities are one contiguous plan-order range; its wavefronts
+// A band's visibilities are one contiguous plan-order range; its wavefronts
 // take equal contiguous shares of it and work independently, at most 64
 // visibilities (a slice) at a time.
 //
@@ -538,9 +541,9 @@ __device__ inline void store_region(const TileArgs<R> &a, const double *tre, con
 // and column slots j + 8q.  No workgroup barrier inside the loop: a wavefront
 // reads only what it staged itself.
 //
-// The workgroup finally stores its own T x T cells to the grid and the rest
+// The workgroup finally stores its own TB x T cells to the grid and the rest
 // of the region to its halo cells; the adjoint FFT's row pass adds the halos
-// of the three neighbours a tile receives from as it loads the grid (or
+// of the three neighbours a band receives from as it loads the grid (or
 // grid_merge does, where that pass is not the specialised one).
 // WAVES: grid_waves<R>(J), or 2 for tiles whose region leaves too little LDS.
 // P2: the values are formed from the l2-ball prox's inputs (see TileArgs), in
@@ -562,8 +565,8 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
     constexpr bool kUnroll = !(sizeof(R) == 8 && J > 12);
     constexpr int KS = KDeg<R>::D / 2 + 1;
     extern __shared__ unsigned char smem_raw[];
-    const int T = a.T, K = a.K, tps = a.tps;
-    const int RR = region_rows(T, J), RS = region_stride(T, J), PS = RR * RS;
+    const int T = a.T, TB = a.TB, K = a.K, tps = a.tps;
+    const int RR = region_rows(TB, J), RS = region_stride(T, J), PS = RR * RS;
     double *tre = reinterpret_cast<double *>(smem_raw);                   // [RR][RS] real parts
     double *tim = tre + PS;                                               // [RR][RS] imaginary parts
     C<R> *wuv_all = reinterpret_cast<C<R> *>(tim + PS);                   // [waves][JR][SR]: wu_i * value
@@ -574,23 +577,25 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
         for (int i = tid; i < (J / 2) * 2 * KS; i += kThreads) kcl[i] = a.kc[i];
 
     const WorkUnit wk = a.order[blockIdx.x];
-    const int t = wk.tile, v0 = wk.start, total = wk.count;
-    if (total == 0) {  // an empty tile: zeros for its cells and its halo cells, no region
-        const int ta0 = (t / tps) * T, tb0 = (t % tps) * T, lt = __builtin_ctz(T);
-        for (int c = tid; c < T * T; c += kThreads) {
+    const int v0 = wk.start, total = wk.count;
+    const int lnb = __builtin_ctz(T) - __builtin_ctz(TB);  // log2 of the tile's bands
+    const int tile = wk.tile >> lnb, band = wk.tile & ((1 << lnb) - 1);
+    const int ta = (tile / tps) * T + band * TB, tb = (tile % tps) * T;
+    if (total == 0) {  // an empty band: zeros for its cells and its halo cells, no region
+        const int lt = __builtin_ctz(T), dc = tb >> lt, br = ta >> __builtin_ctz(TB);
+        for (int c = tid; c < TB * T; c += kThreads) {
             const int r = c >> lt;
-            a.grid[(int64_t)(ta0 + r) * K + tb0 + (c & (T - 1))] = mk<R>(0, 0);
+            a.grid[(int64_t)(ta + r) * K + tb + (c & (T - 1))] = mk<R>(0, 0);
         }
-        C<R> *right = a.halo + halo_right(T, J, tps, t / tps, 0, t % tps);
-        for (int c = tid; c < T * (J - 1); c += kThreads) {
+        C<R> *right = a.halo + halo_right(J, tps, ta, dc);
+        for (int c = tid; c < TB * (J - 1); c += kThreads) {
             const int r = c / (J - 1);
             right[(int64_t)r * tps * (J - 1) + c - r * (J - 1)] = mk<R>(0, 0);
         }
-        C<R> *bottom = a.halo + halo_bottom(T, J, tps, t);
+        C<R> *bottom = a.halo + halo_bottom(T, J, tps, br, dc);
         for (int c = tid; c < (J - 1) * (T + J - 1); c += kThreads) bottom[c] = mk<R>(0, 0);
         return;
     }
-    const int ta = (t / tps) * T, tb = (t % tps) * T;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, li = lane >> 3, lj = lane & 7;
     // 32-entry slices: lane = entry + 32 axis stages one axis of one entry
@@ -598,7 +603,7 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
     // both axes.
     constexpr bool SPLIT = SL == 32;
     const int e = SPLIT ? (lane & 31) : lane, ax = SPLIT ? (lane >> 5) : 0;
-    // This wavefront's share of the tile's visibilities (tile-relative).
+    // This wavefront's share of the band's visibilities (band-relative).
     const int f_begin = (int)(((int64_t)wave * total) / kWaves);
     const int f_end = (int)(((int64_t)(wave + 1) * total) / kWaves);
 
@@ -887,19 +892,19 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
         else close_run(cur);
     }
     __syncthreads();
-    store_region<R, J>(a, tre, tim, t, tid, kThreads);
+    store_region<R, J>(a, tre, tim, ta, tb, tid, kThreads);
 }
 
-// Adds to each tile's first J-1 rows and columns what the tiles above, to
-// the left and above-left left in their halo cells (periodic in the tile
-// grid), in that fixed order.  One thread per border cell.  The adjoint FFT's
-// specialised row pass performs the same additions, in the same order, on
+// Adds to each band's first J-1 rows and columns what the bands above, to
+// the left and above-left left in their halo cells (periodic in the grid), in
+// that fixed order.  One thread per border cell.  The adjoint FFT's
+// compile-time row pass performs the same additions, in the same order, on
 // load; this kernel serves the other FFT lengths.
 template <typename R>
-__global__ void grid_merge(C<R> *grid, const C<R> *halo, int K, int T, int J, int tps) {
-    const int per = (J - 1) * (2 * T - J + 1);  // border cells per tile
+__global__ void grid_merge(C<R> *grid, const C<R> *halo, int K, int T, int TB, int J, int tps) {
+    const int per = (J - 1) * (T + TB - J + 1), nbr = K / TB;  // border cells per band, band rows
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= (int64_t)tps * tps * per) return;
+    if (g >= (int64_t)nbr * tps * per) return;
     const int d = (int)(g / per), e = (int)(g % per);
     int i, j;
     if (e < (J - 1) * T) {
@@ -910,15 +915,12 @@ __global__ void grid_merge(C<R> *grid, const C<R> *halo, int K, int T, int J, in
         i = J - 1 + e2 / (J - 1);
         j = e2 % (J - 1);
     }
-    const int dr = d / tps, dc = d % tps;
-    const int up = ((dr + tps - 1) % tps) * tps + dc;
-    const int left = dr * tps + (dc + tps - 1) % tps;
-    const int ul = ((dr + tps - 1) % tps) * tps + (dc + tps - 1) % tps;
-    const int64_t cell = (int64_t)(dr * T + i) * K + dc * T + j;
+    const int br = d / tps, dc = d % tps, up = (br + nbr - 1) % nbr, left = (dc + tps - 1) % tps;
+    const int64_t cell = (int64_t)(br * TB + i) * K + dc * T + j;
     C<R> v = grid[cell];
-    if (i < J - 1) v = cadd<R>(v, halo[halo_bottom(T, J, tps, up) + i * (T + J - 1) + j]);
-    if (j < J - 1) v = cadd<R>(v, halo[halo_right(T, J, tps, dr, i, left % tps) + j]);
-    if (i < J - 1 && j < J - 1) v = cadd<R>(v, halo[halo_bottom(T, J, tps, ul) + i * (T + J - 1) + T + j]);
+    if (i < J - 1) v = cadd<R>(v, halo[halo_bottom(T, J, tps, up, dc) + i * (T + J - 1) + j]);
+    if (j < J - 1) v = cadd<R>(v, halo[halo_right(J, tps, br * TB + i, left) + j]);
+    if (i < J - 1 && j < J - 1) v = cadd<R>(v, halo[halo_bottom(T, J, tps, up, left) + i * (T + J - 1) + T + j]);
     grid[cell] = v;
 }
 
@@ -949,6 +951,38 @@ static void scan_exclusive(const int *in, int *out, int64_t n, int *sums, hipStr
     hipLaunchKernelGGL(scan_sums, dim3(1), dim3(kScanBlock), 0, st, sums, nsums);
     hipLaunchKernelGGL(scan_add, dim3(nsums), dim3(kScanBlock), 0, st, out, n, (const int *)sums);
     RIOP_HIP(hipGetLastError());
+}
+
+// Rows of a gridding band: T, T/2, .. kBandRows, at least J - 1 (a window spans
+// two bands at most), from the counts of the narrowest bands.  One workgroup
+// takes a band, so the launch lasts as long as the slower of
+//   - the heaviest band's wavefronts: `lat` us per 64 visibilities, 6 wavefronts;
+//   - the whole GPU's throughput: `thr` us per 64 visibilities on each of its
+//     3072 resident wavefronts, plus `fix` us per band on each of 512 workgroup
+//     slots (region clear and store, halo cells).
+// Measured (us; FP32 then FP64, J = 8, bands of 32 / 16 / 8 rows): 256^2 with
+// M = 65536 and 131072 17.8 / 12.5 / 9.9, 60 / 34 / 22; 512^2, M = 700001 33 / 24 / 31,
+// 86 / 52 / 58; 1024^2, M = 4194304 85 / 98 / 126, 199 / 224 / 266; 1536^2,
+// M = 2350001 103 / 135 / 200.  Every count enters, so one dense tile is enough to
+// narrow the bands where the rest of the GPU would wait for it.
+template <typename R> static int choose_band(const std::vector<int> &fine, int T, int J, int64_t M) {
+    const double wide = J > 8 ? 2.5 : 1.0;  // the vector path of wide windows
+    const double lat = wide * (sizeof(R) == 4 ? 1.8 : 4.4), thr = wide * (sizeof(R) == 4 ? 3.3 : 8.0);
+    const double fix = sizeof(R) == 4 ? 1.7 : 3.0;
+    int best = T;
+    double best_us = 0;
+    for (int TB = T; TB >= kBandRows && TB >= J - 1; TB /= 2) {
+        const size_t step = TB / kBandRows;
+        int heaviest = 0;
+        for (size_t t = 0; t + step < fine.size(); t += step) heaviest = std::max(heaviest, fine[t + step] - fine[t]);
+        const double us = std::max(lat * heaviest / (6 * 64) + 3.0,
+                                   thr * (double)M / (3072 * 64) + fix * (double)(fine.size() / step) / 512);
+        if (TB == T || us < best_us) {
+            best = TB;
+            best_us = us;
+        }
+    }
+    return best;
 }
 
 template <typename R> static void build_layout_t(riop_plan *p, const void *uv, hipStream_t st) {
@@ -1011,13 +1045,19 @@ template <typename R> static void build_layout_t(riop_plan *p, const void *uv, h
                            (const uint32_t *)key_a.as<uint32_t>(), (int64_t)0, nkeys, start);
         RIOP_HIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(tile_start_from_keys, dim3((ntiles + 1 + 255) / 256), dim3(256), 0, st, (const int *)start,
-                       ntiles, T * T, p->tile_start.as<int>());
+    hipLaunchKernelGGL(every_start, dim3((ntiles + 1 + 255) / 256), dim3(256), 0, st, (const int *)start, ntiles,
+                       T * T, p->tile_start.as<int>());
+    // Starts of the narrowest bands (kBandRows rows), for the host.
+    const int fine = T / kBandRows, nfine = ntiles * fine;
+    DevBuf fine_start;
+    fine_start.alloc(sizeof(int) * ((size_t)nfine + 1));
+    hipLaunchKernelGGL(every_start, dim3((nfine + 1 + 255) / 256), dim3(256), 0, st, (const int *)start, nfine,
+                       kBandRows * T, fine_start.as<int>());
     RIOP_HIP(hipGetLastError());
     int hflag = 0;
-    std::vector<int> ts(ntiles + 1);
+    std::vector<int> fs((size_t)nfine + 1);
     RIOP_HIP(hipMemcpyAsync(&hflag, flag.ptr, sizeof(int), hipMemcpyDeviceToHost, st));
-    RIOP_HIP(hipMemcpyAsync(ts.data(), p->tile_start.ptr, sizeof(int) * (ntiles + 1), hipMemcpyDeviceToHost, st));
+    RIOP_HIP(hipMemcpyAsync(fs.data(), fine_start.ptr, sizeof(int) * fs.size(), hipMemcpyDeviceToHost, st));
     RIOP_HIP(hipStreamSynchronize(st));
     RIOP_REQUIRE(hflag == 0, RIOP_EINVAL, "uv coordinates must be finite and inside [-pi, pi]");
 
@@ -1025,7 +1065,7 @@ template <typename R> static void build_layout_t(riop_plan *p, const void *uv, h
     std::vector<WorkUnit> units;
     int maxc = 0;
     for (int t = 0; t < ntiles; ++t) {
-        const int s0 = ts[t], e0 = ts[t + 1];
+        const int s0 = fs[(size_t)t * fine], e0 = fs[(size_t)(t + 1) * fine];
         for (int c = s0; c < e0; c += kUnit) {
             const int cnt = std::min(kUnit, e0 - c);
             units.push_back(WorkUnit{t, c, cnt, 0});
@@ -1039,17 +1079,21 @@ template <typename R> static void build_layout_t(riop_plan *p, const void *uv, h
         RIOP_HIP(hipMemcpyAsync(p->units.ptr, units.data(), sizeof(WorkUnit) * units.size(),
                                 hipMemcpyHostToDevice, st));
 
-    // Gridding: sort tiles, heaviest first, each with its visibility range.
-    std::vector<std::pair<int, int>> work(ntiles);
-    for (int t = 0; t < ntiles; ++t) work[t] = {ts[t + 1] - ts[t], t};
+    // Gridding: bands, heaviest first, each with its visibility range.
+    const int TB = choose_band<R>(fs, T, J, M), step = TB / kBandRows, nbands = nfine / step;
+    p->band = TB;
+    std::vector<std::pair<int, int>> work(nbands);
+    for (int t = 0; t < nbands; ++t) work[t] = {fs[(size_t)(t + 1) * step] - fs[(size_t)t * step], t};
     std::stable_sort(work.begin(), work.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
-    std::vector<WorkUnit> order(ntiles);
-    for (int k = 0; k < ntiles; ++k) {
+    std::vector<WorkUnit> order(nbands);
+    for (int k = 0; k < nbands; ++k) {
         const int t = work[k].second;
-        order[k] = WorkUnit{t, ts[t], ts[t + 1] - ts[t], 0};
+        order[k] = WorkUnit{t, fs[(size_t)t * step], work[k].first, 0};
     }
-    p->tile_order.alloc(sizeof(WorkUnit) * ntiles);
-    RIOP_HIP(hipMemcpyAsync(p->tile_order.ptr, order.data(), sizeof(WorkUnit) * ntiles, hipMemcpyHostToDevice, st));
+    p->nbands = nbands;
+    p->halo.alloc(sizeof(C<R>) * (size_t)(J - 1) * ((size_t)K * tps + (size_t)nbands * (T + J - 1)));
+    p->tile_order.alloc(sizeof(WorkUnit) * nbands);
+    RIOP_HIP(hipMemcpyAsync(p->tile_order.ptr, order.data(), sizeof(WorkUnit) * nbands, hipMemcpyHostToDevice, st));
     RIOP_HIP(hipStreamSynchronize(st));
 }
 
@@ -1121,7 +1165,7 @@ template <typename R> void launch_degrid(riop_plan *p, void *y, int order_user, 
 }
 
 void check_grid_lds(riop_plan *p) {
-    const size_t lds = p->prec == RIOP_F64 ? grid_lds<double>(p->tile, p->J, 2) : grid_lds<float>(p->tile, p->J, 2);
+    const size_t lds = p->prec == RIOP_F64 ? grid_lds<double>(p->tile, p->tile, p->J, 2) : grid_lds<float>(p->tile, p->tile, p->J, 2);
     RIOP_REQUIRE(lds <= p->lds_max, RIOP_ENOTSUP, "gridding tile too large for LDS; use a smaller tile");
 }
 
@@ -1139,6 +1183,7 @@ static void launch_tiles(riop_plan *p, const void *vals, int order_user, void *o
     a.kc = p->kcoef_compact.as<R>();
     a.K = p->K;
     a.T = p->tile;
+    a.TB = p->band;
     a.tps = p->tiles_per_side;
     if (p2) {
         RIOP_REQUIRE(!order_user, RIOP_EINVAL, "the fused prox gridding is plan order only");
@@ -1148,11 +1193,11 @@ static void launch_tiles(riop_plan *p, const void *vals, int order_user, void *o
         a.p2scale = p2->p2scale;
     }
     int waves = grid_waves<R>(p->J);
-    if (grid_lds<R>(p->tile, p->J, waves) > p->lds_max) waves = 2;
-    const size_t lds = grid_lds<R>(p->tile, p->J, waves);
+    if (grid_lds<R>(p->band, p->tile, p->J, waves) > p->lds_max) waves = 2;
+    const size_t lds = grid_lds<R>(p->band, p->tile, p->J, waves);
     RIOP_REQUIRE(lds <= p->lds_max, RIOP_ENOTSUP, "gridding tile too large for LDS");
     TimedScope ts(p, p2 ? KK_GRID_PROX2 : KK_GRID, st);
-    const dim3 g(p->ntiles);
+    const dim3 g(p->nbands);
     switch (p->J) {
 #define GK(JJ)                                                                                            \
     case JJ: {                                                                                            \
@@ -1178,12 +1223,12 @@ static void launch_tiles(riop_plan *p, const void *vals, int order_user, void *o
 }
 
 template <typename R> void launch_grid_merge(riop_plan *p, void *grid, hipStream_t st) {
-    const int64_t cells = (int64_t)p->ntiles * (p->J - 1) * (2 * p->tile - p->J + 1);
+    const int64_t cells = (int64_t)p->nbands * (p->J - 1) * (p->tile + p->band - p->J + 1);
     if (cells > 0) {
         TimedScope ts(p, KK_GRID, st);
         const int threads = 256;
         hipLaunchKernelGGL(grid_merge<R>, dim3((unsigned)((cells + threads - 1) / threads)), dim3(threads), 0, st,
-                           static_cast<C<R> *>(grid), (const C<R> *)p->halo.as<C<R>>(), p->K, p->tile, p->J,
+                           static_cast<C<R> *>(grid), (const C<R> *)p->halo.as<C<R>>(), p->K, p->tile, p->band, p->J,
                            p->tiles_per_side);
         RIOP_HIP(hipGetLastError());
     }
