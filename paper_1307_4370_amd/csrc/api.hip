@@ -544,7 +544,6 @@ riop_status riop_gram_build(riop_plan *p, void *stream) {
     return guarded([&] {
         check_plan(p);
         p->gram.release();
-        p->gram_offs.release();
         p->gram_nplanes = 0;
         gram_build_plan(p, S(stream));
         mark_done(p, S(stream));
@@ -556,7 +555,6 @@ riop_status riop_gram_release(riop_plan *p) {
         check_plan(p);
         if (p->done) RIOP_HIP(hipEventSynchronize(p->done));
         p->gram.release();
-        p->gram_offs.release();
         p->gram_nplanes = 0;
     });
 }
@@ -598,7 +596,7 @@ riop_status riop_plan_info(const riop_plan *p, riop_info *info) {
         int64_t extra = 0;
         for (const DevBuf *b : {&p->sd.xhat, &p->sd.rhs, &p->sd.r, &p->sd.p, &p->sd.qp, &p->sd.tmpN, &p->sd.x1,
                                 &p->sd.z3loc, &p->sd.z1loc, &p->sd.w1, &p->sd.ysort, &p->sd.z2loc, &p->sd.s2,
-                                &p->sd.partials, &p->sd.scalars, &p->sd.history, &p->gram, &p->gram_offs})
+                                &p->sd.partials, &p->sd.scalars, &p->sd.history, &p->gram})
             extra += (int64_t)b->bytes;
         info->device_bytes = p->device_bytes + extra;
     });

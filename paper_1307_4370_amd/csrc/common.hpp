@@ -229,8 +229,8 @@ struct riop_plan {
     size_t ll_stride = 0;   // complex entries per basis in `ll`
 
     // Precomputed Gram operator G^T G (optional): one K x K plane of the
-    // plan's real type per offset of the half set, and the offsets (int2).
-    riop::DevBuf gram, gram_offs;
+    // plan's real type per offset of the half set.
+    riop::DevBuf gram;
     int gram_nplanes = 0;
 
     riop::SdmmWork sd;
