@@ -712,8 +712,7 @@ riop_status riop_psi_adj(riop_plan *p, const void *x, void *alpha, void *stream)
         check_plan(p);
         RIOP_REQUIRE(x && alpha, RIOP_EINVAL, "NULL data pointer");
         RIOP_REQUIRE(x != alpha, RIOP_EINVAL, "x and alpha must not alias");
-        check_finite_input(p, x, 2 * (int64_t)p->n * p->n, S(stream));
-        RIOP_DISPATCH(p, launch_psi_adj, p, x, alpha, S(stream));
+        RIOP_DISPATCH(p, launch_psi_adj, p, x, alpha, S(stream), p->nonfinite.as<int>());  // checks x as it loads it
         mark_done(p, S(stream));
     });
 }
@@ -723,8 +722,7 @@ riop_status riop_psi(riop_plan *p, const void *alpha, void *x, void *stream) {
         check_plan(p);
         RIOP_REQUIRE(x && alpha, RIOP_EINVAL, "NULL data pointer");
         RIOP_REQUIRE(x != alpha, RIOP_EINVAL, "x and alpha must not alias");
-        check_finite_input(p, alpha, 2 * (int64_t)p->q * p->n * p->n, S(stream));
-        RIOP_DISPATCH(p, launch_psi, p, alpha, x, S(stream));
+        RIOP_DISPATCH(p, launch_psi, p, alpha, x, S(stream), p->nonfinite.as<int>());  // checks alpha as it loads it
         mark_done(p, S(stream));
     });
 }

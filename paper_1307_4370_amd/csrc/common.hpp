@@ -305,8 +305,11 @@ void launch_grid(riop_plan *p, const void *y, int order_user, hipStream_t st);
 template <typename R>
 void launch_grid_prox2(riop_plan *p, const void *s, void *z2, const void *y, const double *scale, hipStream_t st);
 template <typename R> void launch_fill_zero(void *buf, size_t ncomplex, hipStream_t st);
-template <typename R> void launch_psi_adj(riop_plan *p, const void *x, void *alpha, hipStream_t st);
-template <typename R> void launch_psi(riop_plan *p, const void *alpha, void *x, hipStream_t st);
+// flag (nullable): set to 1 where the input holds a NaN or Inf.
+template <typename R>
+void launch_psi_adj(riop_plan *p, const void *x, void *alpha, hipStream_t st, int *flag = nullptr);
+template <typename R>
+void launch_psi(riop_plan *p, const void *alpha, void *x, hipStream_t st, int *flag = nullptr);
 
 // SDMM l1 step fused into the last analysis pass (Algorithm 1, steps 7-9, i = 1).
 template <typename R> struct Prox1 {

@@ -35,47 +35,39 @@ template <typename R> struct AnaArgs {
     int basis[8];       // Daubechies order of each launched basis
     int plane[8];       // plane index of each launched basis
     int n, s, TO, last;
+    int nbases;         // Daubechies bases launched
+    int dirac_plane;    // level 1: plane of the Dirac basis, done by blockIdx.y = nbases (-1: none)
     R scale;            // 1/sqrt(q) applied to final coefficients
+    int *flag;          // level 1: set to 1 where the input holds a NaN or Inf (nullptr: not checked)
     int prox;
     Prox1<R> px;
 };
 
-template <typename R>
-__device__ inline void emit_coef(const AnaArgs<R> &a, long j, C<R> c, double &f1) {
-    c = cscale<R>(c, a.scale);
-    if (!a.prox) {
-        a.alpha[j] = c;
-        return;
+// Check of loaded inputs: 0 z added for every value; the sum is zero unless one
+// was a NaN or an infinity.
+template <typename R> struct FiniteCheck {
+    R acc = R(0);
+    __device__ void add(C<R> z) { acc = z.y * R(0) + (z.x * R(0) + acc); }
+    __device__ void report(int *flag) const {
+        if (!(acc == R(0))) atomicOr(flag, 1);
     }
-    const R w = a.px.weights ? a.px.weights[j] : R(1);
-    const R lam = (R)(*a.px.gamma) * w;
-    const C<R> z = a.px.z1[j];
-    const C<R> v = cadd<R>(c, z);
-    const R mag = sqrt(v.x * v.x + v.y * v.y);
-    const R sc = mag > lam ? R(1) - lam / mag : R(0);
-    const C<R> r = cscale<R>(v, sc);
-    const C<R> zn = csub<R>(v, r);
-    a.px.z1[j] = zn;
-    a.px.w1[j] = csub<R>(r, zn);
-    f1 += (double)w * sqrt((double)c.x * c.x + (double)c.y * c.y);
-}
+};
 
 // Block sum of f1 into this block's own partial slot (no atomics; the
 // consumer adds the slots in a fixed order).
-template <typename R> __device__ inline void block_add_f1(double f1, double *part) {
-    __shared__ double red[256];
-    red[threadIdx.x] = f1;
+__device__ inline void block_add_f1(double f1, double *part) {
+    __shared__ double red[4];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) f1 += __shfl_xor(f1, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = f1;
     __syncthreads();
-    for (int off = blockDim.x / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[(long)blockIdx.y * gridDim.x + blockIdx.x] = red[0];
+    if (threadIdx.x == 0) part[(long)blockIdx.y * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// Prox epilogue with its operands already loaded (see emit_coef).
+// A final coefficient c (unscaled): stored, or the prox epilogue with its
+// operands z = z1[j] and w (the weight) already loaded.
 template <typename R>
-__device__ inline void emit_coef_pre(const AnaArgs<R> &a, long j, C<R> c, C<R> z, R w, double &f1) {
+__device__ inline void emit_coef(const AnaArgs<R> &a, long j, C<R> c, C<R> z, R w, double &f1) {
     c = cscale<R>(c, a.scale);
     if (!a.prox) {
         a.alpha[j] = c;
@@ -93,169 +85,202 @@ __device__ inline void emit_coef_pre(const AnaArgs<R> &a, long j, C<R> c, C<R> z
 }
 
 // One level of the analysis for one basis (blockIdx.y) and one TO x TO tile
-// of each sub-band (blockIdx.x); 256 threads, seen as 4 rows of 64.
-template <typename R, int TO>
-__global__ void __launch_bounds__(256) dwt_analysis(AnaArgs<R> a) {
-    extern __shared__ unsigned char smem_raw[];
-    const int bi = blockIdx.y;
-    const int b = a.basis[bi];
-    const int Lf = 2 * b;
-    // Filter taps, zero past Lf: single precision keeps them in (scalar)
-    // registers; double precision would need 64 scalar registers for them and
-    // reads an LDS copy instead.
-    __shared__ R taps[2][kMaxTaps];
-    R h[kMaxTaps], g[kMaxTaps];
-    if constexpr (sizeof(R) == 4) {
-#pragma unroll
-        for (int m = 0; m < kMaxTaps; ++m) {
-            h[m] = m < Lf ? a.filt[(b * 2 + 0) * kMaxTaps + m] : R(0);
-            g[m] = m < Lf ? a.filt[(b * 2 + 1) * kMaxTaps + m] : R(0);
-        }
-    } else {
-        if (threadIdx.x < 2 * kMaxTaps) {
-            const int e = threadIdx.x / kMaxTaps, m = threadIdx.x % kMaxTaps;
-            taps[e][m] = m < Lf ? a.filt[(b * 2 + e) * kMaxTaps + m] : R(0);
-        }
-    }
-#define TAP_H(m) (sizeof(R) == 4 ? h[m] : taps[0][m])
-#define TAP_G(m) (sizeof(R) == 4 ? g[m] : taps[1][m])
-    const int s = a.s, half = s >> 1;
+// of each sub-band (blockIdx.x), 256 threads; at level 1 blockIdx.y = nbases
+// copies the Dirac plane.
+// Bound by LDS traffic and latency at level 1 (the output is written once, the
+// 8 bases read one input through the caches).  The filter length is a template
+// parameter of the tile, so that every tap loop unrolls and its LDS reads are
+// issued together; a thread filters 4 neighbouring outputs of a row from one
+// window of 2 * 4 + Lf - 2 inputs (16-byte reads, free of bank conflicts at the
+// even row stride) and 2 of a column from Lf + 2.  Only the low-pass taps are
+// loaded: g[m] = (-1)^m h[Lf - 1 - m].
+// 1024^2, 4 levels, 9 bases, FP32: level 1 42 -> 28 us, all levels and the
+// Dirac plane 77 -> 48 us (a run-time tap count put a branch before every
+// read, one output and one read per tap).
+template <int TO> constexpr int ana_stride() { return TO == 16 ? 20 : TO; }  // row-filtered planes: spreads 4 rows over the banks
+template <int TO> constexpr int ana_region() { return 2 * TO + kMaxTaps - 2; }
+
+// Element i >= 0 of a periodic line of s elements; i < 2 s unless `tiny` (a
+// wave-uniform flag: the division stays off the path of all but tiny levels).
+__device__ inline int wrap(int i, int s, bool tiny) {
+    if (tiny) return i % s;
+    return i - (i >= s ? s : 0);
+}
+
+template <typename R, int TO, int NB>
+__device__ inline void ana_tile(const AnaArgs<R> &a, int bi, C<R> *smem) {
+    constexpr int Lf = 2 * NB, IR = 2 * TO + Lf - 2, IRM = ana_region<TO>(), RS = ana_stride<TO>();
+    constexpr int VL = TO < 4 ? TO : 4;  // outputs per thread along a row
+    constexpr int VK = TO < 2 ? TO : 2;  // and along a column
+    const int s = a.s, half = s >> 1, n = a.n;
     const int tiles = half / TO;
     const int k0 = (blockIdx.x / tiles) * TO, l0 = (blockIdx.x % tiles) * TO;
-    const int IR = 2 * TO + Lf - 2;
-    constexpr int IRM = 2 * TO + kMaxTaps - 2;  // LDS row stride
-    C<R> *reg = reinterpret_cast<C<R> *>(smem_raw);  // [IRM][IRM]
-    C<R> *rlo = reg + IRM * IRM;                     // [IRM][TO]
-    C<R> *rhi = rlo + IRM * TO;
+    C<R> *reg = smem;                            // [IRM][IRM]
+    C<R> *rows = reg + IRM * IRM;                // [low, high][IRM][RS]
     const C<R> *in = a.in + bi * a.in_bstride;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+    const R *ht = a.filt + NB * 2 * kMaxTaps;
+    R h[Lf];
+#pragma unroll
+    for (int m = 0; m < Lf; ++m) h[m] = ht[m];
+    auto g = [&](int m) { return (m & 1) ? -h[Lf - 1 - m] : h[Lf - 1 - m]; };
 
-    // Prox operands of this thread's outputs, loaded before the filtering.
-    const int n = a.n;
-    const long pbase = (long)a.plane[bi] * n * n;
-    constexpr int PER = (TO * TO + 255) / 256;
-    C<R> zq[PER][4];
-    R wq[PER][4];
-    long jq[PER][4];
+    // This thread's column outputs: VK rows of column l of the low or high
+    // plane, low (t = 0) and high (t = 1) filtered.  Their prox operands are
+    // loaded before the filtering.
+    constexpr int kItems = 2 * (TO / VK) * TO;
+    const int p = threadIdx.x / (kItems / 2), kq = threadIdx.x % (kItems / 2);
+    const int k = (kq / TO) * VK, l = kq % TO;
+    const bool mine = threadIdx.x < kItems;
+    const long base = (long)a.plane[bi] * n * n + (long)(k0 + k) * n + p * half + l0 + l;
+    auto place = [&](int v, int t) { return base + (long)(v + t * half) * n; };
+    C<R> zq[VK][2];
+    R wq[VK][2];
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int idx = threadIdx.x + 256 * u;
-        const int k = idx / TO, l = idx % TO;  // TO is a constant power of two
-        const int gk = k0 + k, gl = l0 + l;
-        jq[u][0] = pbase + (long)gk * n + gl;
-        jq[u][1] = pbase + (long)gk * n + half + gl;
-        jq[u][2] = pbase + (long)(half + gk) * n + gl;
-        jq[u][3] = pbase + (long)(half + gk) * n + half + gl;
+    for (int v = 0; v < VK; ++v)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            zq[u][t] = mk<R>(0, 0);
-            wq[u][t] = R(1);
-        }
-        if (a.prox && idx < TO * TO) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                if (t == 0 && !a.last) continue;  // LL goes to the next level
-                zq[u][t] = a.px.z1[jq[u][t]];
-                if (a.px.weights) wq[u][t] = a.px.weights[jq[u][t]];
+        for (int t = 0; t < 2; ++t) {
+            zq[v][t] = mk<R>(0, 0);
+            wq[v][t] = R(1);
+            if (a.prox && mine && (p || t || a.last)) {  // the low-low band goes to the next level
+                zq[v][t] = a.px.z1[place(v, t)];
+                if (a.px.weights) wq[v][t] = a.px.weights[place(v, t)];
             }
         }
-    }
 
-    // Periodic extension (on the smallest levels the region can exceed 2s).
-    // The region is at most 2 TO + 14 <= 64 wide, so thread (ty, tx) stages
-    // column tx of rows ty, ty + 4, ...: all its loads are issued before any
-    // is stored, so their latencies overlap.
-    // (Single precision; double-precision rows would spill registers and
-    // are staged one at a time.)
-    if constexpr (sizeof(R) == 4) {
-        constexpr int RPT = (IRM + 3) / 4;
+    // The region (at most 46 wide): thread (ty, tx) stages column tx of rows
+    // ty, ty + 4, ..., all loads issued before any is stored.
+    {
+        const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+        constexpr int RPT = (IR + 3) / 4;
+        const bool tiny = IR > s;
+        const unsigned gc = wrap(2 * l0 + min(tx, IR - 1), s, tiny);
         C<R> st[RPT];
-        const bool col = tx < IR;
-        const long gc = (2 * l0 + tx) % s;
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-            const int r = ty + 4 * i;
-            if (col && r < IR) st[i] = in[(long)((2 * k0 + r) % s) * s + gc];
+        for (int i = 0; i < RPT; ++i)
+            st[i] = in[(unsigned)wrap(2 * k0 + min(ty + 4 * i, IR - 1), s, tiny) * s + gc];
+        if (a.flag && bi == 0) {
+            FiniteCheck<R> fc;
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) fc.add(st[i]);
+            fc.report(a.flag);
         }
 #pragma unroll
         for (int i = 0; i < RPT; ++i) {
             const int r = ty + 4 * i;
-            if (col && r < IR) reg[r * IRM + tx] = st[i];
-        }
-    } else {
-        for (int r = ty; r < IR; r += 4) {
-            int gr = 2 * k0 + r;
-            while (gr >= s) gr -= s;
-            for (int c = tx; c < IR; c += 64) {
-                int gc = 2 * l0 + c;
-                while (gc >= s) gc -= s;
-                reg[r * IRM + c] = in[(long)gr * s + gc];
-            }
+            if (tx < IR && r < IR) reg[r * IRM + tx] = st[i];
         }
     }
     __syncthreads();
-    // Rows (axis 1): rlo[r][l] = sum_m h[m] in[r][2l + m], rhi with g.
-    for (int idx = threadIdx.x; idx < IR * TO; idx += 256) {
-        const int r = idx / TO, l = idx % TO;
-        R lr = 0, li = 0, hr = 0, hi = 0;
-        const C<R> *row = reg + r * IRM + 2 * l;
+    // Rows (axis 1): low[r][l] = sum_m h[m] in[r][2 l + m], high with g.
+    for (int idx = threadIdx.x; idx < IR * (TO / VL); idx += 256) {
+        const int r = idx / (TO / VL), q = (idx % (TO / VL)) * VL;
+        constexpr int NI = 2 * VL + Lf - 2;
+        C<R> v[NI];
+        const C<R> *row = reg + r * IRM + 2 * q;
+        if constexpr (sizeof(R) == 4) {
 #pragma unroll
-        for (int m = 0; m < kMaxTaps; ++m) {
-            if (m < Lf) {
-                const C<R> v = row[m];
-                lr += TAP_H(m) * v.x;
-                li += TAP_H(m) * v.y;
-                hr += TAP_G(m) * v.x;
-                hi += TAP_G(m) * v.y;
+            for (int m = 0; m < NI; m += 2) {
+                const float4 t = *reinterpret_cast<const float4 *>(row + m);
+                v[m] = mk<R>(t.x, t.y);
+                v[m + 1] = mk<R>(t.z, t.w);
             }
+        } else {
+#pragma unroll
+            for (int m = 0; m < NI; ++m) v[m] = row[m];
         }
-        rlo[r * TO + l] = mk<R>(lr, li);
-        rhi[r * TO + l] = mk<R>(hr, hi);
+#pragma unroll
+        for (int o = 0; o < VL; ++o) {
+            R lr = 0, li = 0, hr = 0, hi = 0;
+#pragma unroll
+            for (int m = 0; m < Lf; ++m) {
+                lr += h[m] * v[2 * o + m].x;
+                li += h[m] * v[2 * o + m].y;
+                hr += g(m) * v[2 * o + m].x;
+                hi += g(m) * v[2 * o + m].y;
+            }
+            rows[r * RS + q + o] = mk<R>(lr, li);
+            rows[(IRM + r) * RS + q + o] = mk<R>(hr, hi);
+        }
     }
     __syncthreads();
     // Columns (axis 0).
     double f1 = 0.0;
+    if (mine) {
+        constexpr int NI = 2 * VK + Lf - 2;
+        C<R> v[NI];
+        const C<R> *col = rows + (p * IRM + 2 * k) * RS + l;
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int idx = threadIdx.x + 256 * u;
-        if (idx >= TO * TO) break;
-        const int k = idx / TO, l = idx % TO;
-        R llr = 0, lli = 0, hlr = 0, hli = 0, lhr = 0, lhi = 0, hhr = 0, hhi = 0;
+        for (int m = 0; m < NI; ++m) v[m] = col[m * RS];
 #pragma unroll
-        for (int m = 0; m < kMaxTaps; ++m) {
-            if (m < Lf) {
-                const C<R> vl = rlo[(2 * k + m) * TO + l];
-                const C<R> vh = rhi[(2 * k + m) * TO + l];
-                llr += TAP_H(m) * vl.x;
-                lli += TAP_H(m) * vl.y;
-                hlr += TAP_G(m) * vl.x;
-                hli += TAP_G(m) * vl.y;
-                lhr += TAP_H(m) * vh.x;
-                lhi += TAP_H(m) * vh.y;
-                hhr += TAP_G(m) * vh.x;
-                hhi += TAP_G(m) * vh.y;
+        for (int o = 0; o < VK; ++o) {
+            R lr = 0, li = 0, hr = 0, hi = 0;
+#pragma unroll
+            for (int m = 0; m < Lf; ++m) {
+                lr += h[m] * v[2 * o + m].x;
+                li += h[m] * v[2 * o + m].y;
+                hr += g(m) * v[2 * o + m].x;
+                hi += g(m) * v[2 * o + m].y;
             }
+            if (p == 0 && !a.last) a.ll_out[bi * a.ll_bstride + (long)(k0 + k + o) * half + l0 + l] = mk<R>(lr, li);
+            else emit_coef<R>(a, place(o, 0), mk<R>(lr, li), zq[o][0], wq[o][0], f1);
+            emit_coef<R>(a, place(o, 1), mk<R>(hr, hi), zq[o][1], wq[o][1], f1);
         }
-        const int gk = k0 + k, gl = l0 + l;
-        if (a.last) emit_coef_pre<R>(a, jq[u][0], mk<R>(llr, lli), zq[u][0], wq[u][0], f1);
-        else a.ll_out[bi * a.ll_bstride + (long)gk * half + gl] = mk<R>(llr, lli);
-        emit_coef_pre<R>(a, jq[u][1], mk<R>(lhr, lhi), zq[u][1], wq[u][1], f1);
-        emit_coef_pre<R>(a, jq[u][2], mk<R>(hlr, hli), zq[u][2], wq[u][2], f1);
-        emit_coef_pre<R>(a, jq[u][3], mk<R>(hhr, hhi), zq[u][3], wq[u][3], f1);
     }
-    if (a.prox) block_add_f1<R>(f1, a.px.f1_part);
-#undef TAP_H
-#undef TAP_G
+    if (a.prox) block_add_f1(f1, a.px.f1_part);
 }
 
-// Dirac plane: alpha_0 = x / sqrt(q) (or its prox epilogue).
-template <typename R> __global__ void dirac_analysis(AnaArgs<R> a, const C<R> *x) {
+// Dirac coefficient j = base + i of pixel value x.
+template <typename R>
+__device__ inline void dirac_coef(const AnaArgs<R> &a, long i, C<R> x, double &f1) {
+    const long j = (long)a.dirac_plane * a.n * a.n + i;
+    const C<R> z = a.prox ? a.px.z1[j] : mk<R>(0, 0);
+    const R w = a.prox && a.px.weights ? a.px.weights[j] : R(1);
+    emit_coef<R>(a, j, x, z, w, f1);
+}
+
+template <typename R, int TO> __global__ void __launch_bounds__(256) dwt_analysis(AnaArgs<R> a) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    C<R> *smem = reinterpret_cast<C<R> *>(smem_raw);
+    const int bi = blockIdx.y;
+    if (bi == a.nbases) {  // level 1: the Dirac plane of this tile, alpha_0 = x / sqrt(q)
+        const int n = a.n, tiles = (n >> 1) / TO;
+        const int i0 = (blockIdx.x / tiles) * 2 * TO, j0 = (blockIdx.x % tiles) * 2 * TO;
+        double f1 = 0.0;
+#pragma unroll
+        for (int u = 0; u < (4 * TO * TO + 255) / 256; ++u) {
+            const int e = threadIdx.x + 256 * u;
+            if (e < 4 * TO * TO) {
+                const long i = (long)(i0 + e / (2 * TO)) * n + j0 + e % (2 * TO);
+                dirac_coef<R>(a, i, a.in[i], f1);
+            }
+        }
+        if (a.prox) block_add_f1(f1, a.px.f1_part);
+        return;
+    }
+    switch (a.basis[bi]) {
+        case 1: ana_tile<R, TO, 1>(a, bi, smem); break;
+        case 2: ana_tile<R, TO, 2>(a, bi, smem); break;
+        case 3: ana_tile<R, TO, 3>(a, bi, smem); break;
+        case 4: ana_tile<R, TO, 4>(a, bi, smem); break;
+        case 5: ana_tile<R, TO, 5>(a, bi, smem); break;
+        case 6: ana_tile<R, TO, 6>(a, bi, smem); break;
+        case 7: ana_tile<R, TO, 7>(a, bi, smem); break;
+        default: ana_tile<R, TO, 8>(a, bi, smem); break;
+    }
+}
+
+// A dictionary of the Dirac basis alone.
+template <typename R> __global__ void __launch_bounds__(256) dirac_analysis(AnaArgs<R> a) {
     const long N = (long)a.n * a.n;
     double f1 = 0.0;
-    const long base = (long)a.plane[0] * N;
-    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (long)gridDim.x * blockDim.x)
-        emit_coef<R>(a, base + i, x[i], f1);
-    if (a.prox) block_add_f1<R>(f1, a.px.f1_part);
+    FiniteCheck<R> fc;
+    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (long)gridDim.x * blockDim.x) {
+        const C<R> x = a.in[i];
+        fc.add(x);
+        dirac_coef<R>(a, i, x, f1);
+    }
+    if (a.flag) fc.report(a.flag);
+    if (a.prox) block_add_f1(f1, a.px.f1_part);
 }
 
 template <typename R> struct SynArgs {
@@ -272,204 +297,262 @@ template <typename R> struct SynArgs {
     int dirac_plane;    // -1 if the Dirac basis is not selected
     int n, s, TO, coarsest;
     R scale;
+    int *flag;          // set to 1 where alpha holds a NaN or Inf (nullptr: not checked)
 };
 
-// The four sub-band regions of one synthesis tile, KR <= TO + 7 square: at
-// most 3 entries per thread for 256 threads, held in registers between their
-// loads and their LDS stores.
-constexpr int kSynEPT = ((kTO + kMaxTaps / 2 - 1) * (kTO + kMaxTaps / 2 - 1) + 255) / 256;
+// Synthesis of one (2 TO)^2 output tile of basis DbN by 256 threads (a group;
+// thread t), from the four KR^2 sub-band regions, KR = TO + N - 1, staged in LDS:
+// columns (axis 0), then rows.  As in the analysis, N is a template parameter of
+// the filter steps, so their loops unroll and issue their LDS reads together.
+// Output rows (and columns) 2 r and 2 r + 1 read the same N inputs with the even
+// and the odd taps; a thread forms two such pairs from N + 1 inputs.
+// Bound by LDS reads and, where there are few tiles, by latency: the last level
+// sums all bases for a tile, so NG groups per block each take every NG-th basis
+// (their sums are added in a fixed order at the end).
+// 512^2, 4 levels, 9 bases, FP64: last level 36 -> 25 us, all 63 -> 48;
+// 1024^2, FP32: last level 44 -> 38 us, all 74 -> 64.
+template <int TO> constexpr int syn_kr() { return TO + kMaxTaps / 2 - 1; }  // the widest region
+template <int TO> constexpr int syn_cells() { return 4 * syn_kr<TO>() * syn_kr<TO>() + 4 * TO * syn_kr<TO>(); }
+template <int TO> constexpr int syn_pairs() { return TO < 2 ? 1 : 2; }
+
+// The regions' loads: thread (t / 32, t % 32) takes column t % 32 of rows t / 32,
+// t / 32 + 8 and t / 32 + 16 (KR <= 23) of each band.
 template <typename R> struct SynRegion {
-    C<R> ll[kSynEPT], lh[kSynEPT], hl[kSynEPT], hh[kSynEPT];
+    C<R> ll[3], lh[3], hl[3], hh[3];
 };
 
-// Issues the loads of basis slot bi's regions for the (2 TO)^2 output tile at (i0, j0).
 template <typename R>
-__device__ inline void syn_load(const SynArgs<R> &a, int bi, int i0, int j0, SynRegion<R> &v) {
-    const int Lf = 2 * a.basis[bi];
-    const int half = a.s >> 1, KR = a.TO + Lf / 2 - 1;
-    const int kst = i0 / 2 - Lf / 2 + 1, lst = j0 / 2 - Lf / 2 + 1;
-    const int n = a.n;
+__device__ inline void syn_load(const SynArgs<R> &a, int bi, int t, int i0, int j0, SynRegion<R> &v) {
+    const int N = a.basis[bi], n = a.n, half = a.s >> 1, KR = a.TO + N - 1;
+    const int c = t & 31, r0 = t >> 5;
+    if (c >= KR) return;
+    const bool tiny = half < kMaxTaps / 2;  // region starts at -7 at least: one period is enough, but for tiny levels
+    auto wrap_neg = [&](int k) { return tiny ? (k % half + half) % half : k + (k < 0 ? half : 0); };
+    const int kst = i0 / 2 - N + 1;
+    const unsigned l = wrap_neg(j0 / 2 - N + 1 + c);
+    // Band origins, uniform; offsets inside a plane are 32-bit.
     const C<R> *plane = a.alpha + (long)a.plane[bi] * n * n;
-    const C<R> *llsrc = a.coarsest ? nullptr : a.ll_in + bi * a.ll_in_bstride;
+    const C<R> *lh = plane + half, *hl = plane + (long)half * n, *hh = hl + half;
+    const C<R> *ll = a.coarsest ? plane : a.ll_in + bi * a.ll_in_bstride;
+    const unsigned ls = a.coarsest ? n : half;
 #pragma unroll
-    for (int q = 0; q < kSynEPT; ++q) {
-        const int idx = threadIdx.x + q * blockDim.x;
-        if (idx < KR * KR) {
-            const int r = idx / KR, c = idx - r * KR;
-            int k = (kst + r) % half, l = (lst + c) % half;
-            if (k < 0) k += half;
-            if (l < 0) l += half;
-            v.ll[q] = a.coarsest ? plane[(long)k * n + l] : llsrc[(long)k * half + l];
-            v.lh[q] = plane[(long)k * n + half + l];
-            v.hl[q] = plane[(long)(half + k) * n + l];
-            v.hh[q] = plane[(long)(half + k) * n + half + l];
+    for (int q = 0; q < 3; ++q) {
+        const int r = r0 + 8 * q;
+        if (r < KR) {
+            const unsigned k = wrap_neg(kst + r), o = k * (unsigned)n + l;
+            v.ll[q] = ll[k * ls + l];
+            v.lh[q] = lh[o];
+            v.hl[q] = hl[o];
+            v.hh[q] = hh[o];
         }
     }
-}
-
-// Column then row synthesis of one (2 TO)^2 output tile of basis slot bi from
-// its loaded regions; adds the result into acc (thread-owned outputs
-// idx = threadIdx.x + k*blockDim).
-template <typename R>
-__device__ inline void syn_tile(const SynArgs<R> &a, int bi, const SynRegion<R> *v, int i0, int j0, C<R> *smem,
-                                C<R> (&acc)[4]) {
-    const int b = a.basis[bi];
-    const int Lf = 2 * b;
-    const R *h = a.filt + (b * 2 + 0) * kMaxTaps;
-    const R *g = a.filt + (b * 2 + 1) * kMaxTaps;
-    const int TO = a.TO, TS = 2 * TO;
-    const int KR = TO + Lf / 2 - 1;
-    C<R> *LL = smem, *LH = LL + KR * KR, *HL = LH + KR * KR, *HH = HL + KR * KR;
-    C<R> *lo1 = HH + KR * KR, *hi1 = lo1 + TS * KR;
-    __syncthreads();  // the previous tile's readers of smem are done
-    if (v) {
+    if (a.flag) {
+        FiniteCheck<R> fc;
 #pragma unroll
-        for (int q = 0; q < kSynEPT; ++q) {
-            const int idx = threadIdx.x + q * blockDim.x;
-            if (idx < KR * KR) {
-                LL[idx] = v->ll[q];
-                LH[idx] = v->lh[q];
-                HL[idx] = v->hl[q];
-                HH[idx] = v->hh[q];
+        for (int q = 0; q < 3; ++q)
+            if (r0 + 8 * q < KR) {
+                if (a.coarsest) fc.add(v.ll[q]);
+                fc.add(v.lh[q]);
+                fc.add(v.hl[q]);
+                fc.add(v.hh[q]);
             }
-        }
-    } else {  // regions read straight into LDS (double precision)
-        const int half = a.s >> 1, n = a.n;
-        const int kst = i0 / 2 - Lf / 2 + 1, lst = j0 / 2 - Lf / 2 + 1;
-        const C<R> *plane = a.alpha + (long)a.plane[bi] * n * n;
-        const C<R> *llsrc = a.coarsest ? nullptr : a.ll_in + bi * a.ll_in_bstride;
-        for (int idx = threadIdx.x; idx < KR * KR; idx += blockDim.x) {
-            const int r = idx / KR, c = idx - r * KR;
-            int k = (kst + r) % half, l = (lst + c) % half;
-            if (k < 0) k += half;
-            if (l < 0) l += half;
-            LL[idx] = a.coarsest ? plane[(long)k * n + l] : llsrc[(long)k * half + l];
-            LH[idx] = plane[(long)k * n + half + l];
-            HL[idx] = plane[(long)(half + k) * n + l];
-            HH[idx] = plane[(long)(half + k) * n + half + l];
-        }
-    }
-    __syncthreads();
-    // Columns (axis 0): lo1[ii][c] from (LL, HL), hi1[ii][c] from (LH, HH).
-    // Output rows 2 r and 2 r + 1 read the same Lf / 2 input rows (even and
-    // odd taps), so one thread forms both from one set of LDS reads.
-    for (int w = threadIdx.x; w < (TS / 2) * KR; w += blockDim.x) {
-        const int rp = w / KR, c = w - rp * KR;
-        R lr0 = 0, li0 = 0, hr0 = 0, hi0 = 0, lr1 = 0, li1 = 0, hr1 = 0, hi1_ = 0;
-        const int base = rp + Lf / 2 - 1;
-        for (int t = 0; t < Lf / 2; ++t) {
-            const int r = base - t;
-            const C<R> vll = LL[r * KR + c], vhl = HL[r * KR + c];
-            const C<R> vlh = LH[r * KR + c], vhh = HH[r * KR + c];
-            const int m0 = 2 * t, m1 = 2 * t + 1;
-            lr0 += h[m0] * vll.x + g[m0] * vhl.x;
-            li0 += h[m0] * vll.y + g[m0] * vhl.y;
-            hr0 += h[m0] * vlh.x + g[m0] * vhh.x;
-            hi0 += h[m0] * vlh.y + g[m0] * vhh.y;
-            lr1 += h[m1] * vll.x + g[m1] * vhl.x;
-            li1 += h[m1] * vll.y + g[m1] * vhl.y;
-            hr1 += h[m1] * vlh.x + g[m1] * vhh.x;
-            hi1_ += h[m1] * vlh.y + g[m1] * vhh.y;
-        }
-        lo1[(2 * rp) * KR + c] = mk<R>(lr0, li0);
-        hi1[(2 * rp) * KR + c] = mk<R>(hr0, hi0);
-        lo1[(2 * rp + 1) * KR + c] = mk<R>(lr1, li1);
-        hi1[(2 * rp + 1) * KR + c] = mk<R>(hr1, hi1_);
-    }
-    __syncthreads();
-    // Rows (axis 1), output columns 2 c and 2 c + 1 of a row per thread and
-    // step from the same Lf / 2 inputs (see syn_out for the ownership).
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int w = threadIdx.x + k * blockDim.x;
-        if (w >= TS * TS / 2) break;
-        const int ii = w / (TS / 2), cp = w - ii * (TS / 2);
-        const int base = cp + Lf / 2 - 1;
-        R xr0 = 0, xi0 = 0, xr1 = 0, xi1 = 0;
-        for (int t = 0; t < Lf / 2; ++t) {
-            const int c = base - t;
-            const C<R> vl = lo1[ii * KR + c], vh = hi1[ii * KR + c];
-            const int m0 = 2 * t, m1 = 2 * t + 1;
-            xr0 += h[m0] * vl.x + g[m0] * vh.x;
-            xi0 += h[m0] * vl.y + g[m0] * vh.y;
-            xr1 += h[m1] * vl.x + g[m1] * vh.x;
-            xi1 += h[m1] * vl.y + g[m1] * vh.y;
-        }
-        acc[2 * k].x += xr0;
-        acc[2 * k].y += xi0;
-        acc[2 * k + 1].x += xr1;
-        acc[2 * k + 1].y += xi1;
+        fc.report(a.flag);
     }
 }
 
-// Output owned by accumulator q of this thread in a (2 TO)^2 synthesis tile:
-// step q / 2 of the row pass, column parity q % 2 (false past the tile).
-__device__ inline bool syn_out(int q, int TS, int &ii, int &jj) {
-    const int w = threadIdx.x + (q >> 1) * blockDim.x;
-    if (w >= TS * TS / 2) return false;
-    ii = w / (TS / 2);
-    jj = 2 * (w - ii * (TS / 2)) + (q & 1);
-    return true;
+// LDS of a group: the regions LL, HL, LH, HH (KR^2 each), then the
+// column-filtered low and high planes (2 TO x KR each).
+template <typename R>
+__device__ inline void syn_stage(const SynArgs<R> &a, int bi, int t, const SynRegion<R> &v, C<R> *smem) {
+    const int KR = a.TO + a.basis[bi] - 1, c = t & 31, r0 = t >> 5, KR2 = KR * KR;
+    if (c >= KR) return;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const int r = r0 + 8 * q;
+        if (r < KR) {
+            smem[r * KR + c] = v.ll[q];
+            smem[KR2 + r * KR + c] = v.hl[q];
+            smem[2 * KR2 + r * KR + c] = v.lh[q];
+            smem[3 * KR2 + r * KR + c] = v.hh[q];
+        }
+    }
 }
+
+// NP output pairs (even: 2 i, odd: 2 i + 1, i = i0 .. i0 + NP - 1) of the 1-D
+// synthesis from low lo[i0 ..] and high hi[i0 ..] inputs `stride` apart, the
+// first of which is entry i0 of a region that starts N - 1 entries early.
+template <typename R, int N, int NP>
+__device__ inline void syn_pairs_1d(const R (&h)[2 * N], const C<R> *lo, const C<R> *hi, int stride,
+                                    C<R> (&out)[2 * NP]) {
+    auto g = [&](int m) { return (m & 1) ? -h[2 * N - 1 - m] : h[2 * N - 1 - m]; };
+    C<R> l[N + NP - 1], u[N + NP - 1];
+#pragma unroll
+    for (int i = 0; i < N + NP - 1; ++i) {
+        l[i] = lo[i * stride];
+        u[i] = hi[i * stride];
+    }
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+#pragma unroll
+        for (int par = 0; par < 2; ++par) {
+            R re = 0, im = 0;
+#pragma unroll
+            for (int t = 0; t < N; ++t) {
+                const int m = 2 * t + par, r = q + N - 1 - t;
+                re += h[m] * l[r].x + g(m) * u[r].x;
+                im += h[m] * l[r].y + g(m) * u[r].y;
+            }
+            out[2 * q + par] = mk<R>(re, im);
+        }
+}
+
+template <typename R, int TO, int N> __device__ inline void syn_cols(const R *filt, int t, C<R> *smem) {
+    constexpr int KR = TO + N - 1, KR2 = KR * KR, NP = syn_pairs<TO>(), per = (TO / NP) * KR;
+    R h[2 * N];
+#pragma unroll
+    for (int m = 0; m < 2 * N; ++m) h[m] = filt[N * 2 * kMaxTaps + m];
+    C<R> *mid = smem + 4 * KR2;
+    for (int w = t; w < 2 * per; w += 256) {  // low plane from (LL, HL), high plane from (LH, HH)
+        const int p = w / per, q = w - p * per, rp = (q / KR) * NP, c = q % KR;
+        const C<R> *lo = smem + 2 * p * KR2 + rp * KR + c;
+        C<R> out[2 * NP];
+        syn_pairs_1d<R, N, NP>(h, lo, lo + KR2, KR, out);
+#pragma unroll
+        for (int i = 0; i < 2 * NP; ++i) mid[(p * 2 * TO + 2 * rp + i) * KR + c] = out[i];
+    }
+}
+
+// Output columns of thread t: row ii, columns jj .. jj + 2 NP - 1 (false: none).
+template <int TO> __device__ inline bool syn_place(int t, int &ii, int &jj) {
+    constexpr int NP = syn_pairs<TO>(), per = TO / NP;
+    ii = t / per;
+    jj = 2 * NP * (t - ii * per);
+    return t < 2 * TO * per;
+}
+
+template <typename R, int TO, int N>
+__device__ inline void syn_rows(const R *filt, int t, const C<R> *smem, C<R> (&acc)[2 * syn_pairs<TO>()]) {
+    constexpr int KR = TO + N - 1, NP = syn_pairs<TO>();
+    R h[2 * N];
+#pragma unroll
+    for (int m = 0; m < 2 * N; ++m) h[m] = filt[N * 2 * kMaxTaps + m];
+    int ii, jj;
+    if (!syn_place<TO>(t, ii, jj)) return;
+    const C<R> *lo = smem + 4 * KR * KR + ii * KR + jj / 2;
+    C<R> out[2 * NP];
+    syn_pairs_1d<R, N, NP>(h, lo, lo + 2 * TO * KR, 1, out);
+#pragma unroll
+    for (int i = 0; i < 2 * NP; ++i) acc[i] = cadd<R>(acc[i], out[i]);
+}
+
+#define SYN_BASES(FN, N, ...)                          \
+    switch (N) {                                       \
+        case 1: FN<R, TO, 1>(__VA_ARGS__); break;      \
+        case 2: FN<R, TO, 2>(__VA_ARGS__); break;      \
+        case 3: FN<R, TO, 3>(__VA_ARGS__); break;      \
+        case 4: FN<R, TO, 4>(__VA_ARGS__); break;      \
+        case 5: FN<R, TO, 5>(__VA_ARGS__); break;      \
+        case 6: FN<R, TO, 6>(__VA_ARGS__); break;      \
+        case 7: FN<R, TO, 7>(__VA_ARGS__); break;      \
+        default: FN<R, TO, 8>(__VA_ARGS__); break;     \
+    }
 
 // Levels > 1: one basis per blockIdx.y, writes the finer LL slot.
-template <typename R> __global__ void __launch_bounds__(256) dwt_synthesis(SynArgs<R> a) {
-    extern __shared__ unsigned char smem_raw[];
+template <typename R, int TO> __global__ void __launch_bounds__(256) dwt_synthesis(SynArgs<R> a) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
     C<R> *smem = reinterpret_cast<C<R> *>(smem_raw);
-    const int bi = blockIdx.y;
-    const int TS = 2 * a.TO, tiles = a.s / TS;
+    constexpr int TS = 2 * TO, NA = 2 * syn_pairs<TO>();
+    const int bi = blockIdx.y, t = threadIdx.x, tiles = a.s / TS;
     const int i0 = (blockIdx.x / tiles) * TS, j0 = (blockIdx.x % tiles) * TS;
-    C<R> acc[4];
-    for (int q = 0; q < 4; ++q) acc[q] = mk<R>(0, 0);
-    if constexpr (sizeof(R) == 4) {
-        SynRegion<R> v;
-        syn_load<R>(a, bi, i0, j0, v);
-        syn_tile<R>(a, bi, &v, i0, j0, smem, acc);
-    } else {
-        syn_tile<R>(a, bi, nullptr, i0, j0, smem, acc);
-    }
-    C<R> *out = a.ll_out + bi * a.ll_out_bstride;
-    for (int q = 0; q < 4; ++q) {
-        int ii, jj;
-        if (syn_out(q, TS, ii, jj)) out[(long)(i0 + ii) * a.s + j0 + jj] = acc[q];
+    SynRegion<R> v;
+    syn_load<R>(a, bi, t, i0, j0, v);
+    syn_stage<R>(a, bi, t, v, smem);
+    __syncthreads();
+    SYN_BASES(syn_cols, a.basis[bi], a.filt, t, smem)
+    __syncthreads();
+    C<R> acc[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) acc[i] = mk<R>(0, 0);
+    SYN_BASES(syn_rows, a.basis[bi], a.filt, t, smem, acc)
+    int ii, jj;
+    if (syn_place<TO>(t, ii, jj)) {
+        C<R> *out = a.ll_out + bi * a.ll_out_bstride + (long)(i0 + ii) * a.s + j0 + jj;
+#pragma unroll
+        for (int i = 0; i < NA; ++i) out[i] = acc[i];
     }
 }
 
-// Level 1: sum of all bases (and the Dirac plane) for one output tile.
-template <typename R> __global__ void __launch_bounds__(256) dwt_synthesis_final(SynArgs<R> a) {
-    extern __shared__ unsigned char smem_raw[];
-    C<R> *smem = reinterpret_cast<C<R> *>(smem_raw);
-    const int TS = 2 * a.TO, tiles = a.s / TS;
+// Level 1: sum of all bases (and the Dirac plane) for one output tile.  Group g
+// takes bases g, 2 NG - 1 - g, 2 NG + g, ... (long and short filters in turn); the
+// next basis's regions load while the current one is filtered.
+template <typename R, int TO, int NG>
+__global__ void __launch_bounds__(256 * NG, sizeof(R) == 4 ? 4 : 2) dwt_synthesis_final(SynArgs<R> a) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    constexpr int TS = 2 * TO, NA = 2 * syn_pairs<TO>();
+    const int g = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), t = threadIdx.x & 255;
+    C<R> *all = reinterpret_cast<C<R> *>(smem_raw), *smem = all + g * syn_cells<TO>();
+    const int n = a.n, tiles = a.s / TS;
     const int i0 = (blockIdx.x / tiles) * TS, j0 = (blockIdx.x % tiles) * TS;
-    C<R> acc[4];
-    for (int q = 0; q < 4; ++q) acc[q] = mk<R>(0, 0);
-    if constexpr (sizeof(R) == 4) {
-        // The next basis's regions load while the current one is filtered
-        // (single precision: double-precision regions would spill).
-        SynRegion<R> v, vn;
-        if (a.nbases > 0) syn_load<R>(a, 0, i0, j0, v);
-        for (int bi = 0; bi < a.nbases; ++bi) {
-            if (bi + 1 < a.nbases) syn_load<R>(a, bi + 1, i0, j0, vn);
-            syn_tile<R>(a, bi, &v, i0, j0, smem, acc);
-            v = vn;
+    auto basis = [&](int step) { return step * NG + ((step & 1) ? NG - 1 - g : g); };
+    int ii, jj;
+    const bool mine = syn_place<TO>(t, ii, jj);
+    const long o = (long)(i0 + ii) * n + j0 + jj;
+    C<R> acc[NA], dirac[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) acc[i] = dirac[i] = mk<R>(0, 0);
+    if (a.dirac_plane >= 0 && g == 0 && mine) {
+        FiniteCheck<R> fc;
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            dirac[i] = a.alpha[(long)a.dirac_plane * n * n + o + i];
+            fc.add(dirac[i]);
         }
-    } else {
-        for (int bi = 0; bi < a.nbases; ++bi) syn_tile<R>(a, bi, nullptr, i0, j0, smem, acc);
+        if (a.flag) fc.report(a.flag);
     }
-    const int n = a.n;
-    for (int q = 0; q < 4; ++q) {
-        int ii, jj;
-        if (!syn_out(q, TS, ii, jj)) continue;
-        const long o = (long)(i0 + ii) * n + j0 + jj;
-        C<R> v = acc[q];
-        if (a.dirac_plane >= 0) v = cadd<R>(v, a.alpha[(long)a.dirac_plane * n * n + o]);
-        a.x[o] = cscale<R>(v, a.scale);
+    SynRegion<R> v;
+    if (basis(0) < a.nbases) syn_load<R>(a, basis(0), t, i0, j0, v);
+    const int steps = (a.nbases + NG - 1) / NG;
+    for (int step = 0; step < steps; ++step) {
+        const int bi = basis(step), bn = basis(step + 1);
+        const bool on = bi < a.nbases;
+        __syncthreads();  // the previous basis's readers are done
+        if (on) syn_stage<R>(a, bi, t, v, smem);
+        if (bn < a.nbases) syn_load<R>(a, bn, t, i0, j0, v);
+        __syncthreads();
+        if (on) SYN_BASES(syn_cols, a.basis[bi], a.filt, t, smem)
+        __syncthreads();
+        if (on) SYN_BASES(syn_rows, a.basis[bi], a.filt, t, smem, acc)
+    }
+    if constexpr (NG > 1) {  // [group - 1][output][thread]
+        __syncthreads();
+        if (g > 0) {
+#pragma unroll
+            for (int i = 0; i < NA; ++i) all[((g - 1) * NA + i) * 256 + t] = acc[i];
+        }
+        __syncthreads();
+        if (g > 0) return;
+        for (int k = 0; k < NG - 1; ++k)
+#pragma unroll
+            for (int i = 0; i < NA; ++i) acc[i] = cadd<R>(acc[i], all[(k * NA + i) * 256 + t]);
+    }
+    if (!mine) return;
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        C<R> z = acc[i];
+        if (a.dirac_plane >= 0) z = cadd<R>(z, dirac[i]);
+        a.x[o + i] = cscale<R>(z, a.scale);
     }
 }
+#undef SYN_BASES
 
-template <typename R> __global__ void dirac_only_synthesis(const C<R> *alpha, int plane, C<R> *x, long N, R scale) {
-    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (long)gridDim.x * blockDim.x)
-        x[i] = cscale<R>(alpha[(long)plane * N + i], scale);
+template <typename R> __global__ void dirac_only_synthesis(SynArgs<R> a, long N) {
+    FiniteCheck<R> fc;
+    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (long)gridDim.x * blockDim.x) {
+        const C<R> z = a.alpha[(long)a.dirac_plane * N + i];
+        fc.add(z);
+        a.x[i] = cscale<R>(z, a.scale);
+    }
+    if (a.flag) fc.report(a.flag);
 }
 
 // ---------------------------------------------------------------------------
@@ -491,31 +574,48 @@ static size_t ll_offset(int n, int level) {
 static int dirac_blocks(int n) { return (int)std::min<long>(((long)n * n + 255) / 256, 4096); }
 
 int psi_adj_blocks(const riop_plan *p) {
-    const int n = p->n;
-    int nb = 0, total = 0;
-    for (int i = 0; i < p->q; ++i) {
-        if (p->bases[i] == 0) total += dirac_blocks(n);
-        else ++nb;
-    }
-    if (nb == 0) return total;
+    const int n = p->n, dirac = p->mask & 1, nb = p->q - dirac;
+    if (nb == 0) return dirac_blocks(n);
+    int total = 0;
     for (int lev = 1; lev <= p->L; ++lev) {
         const int half = (n >> (lev - 1)) >> 1, tiles = half / tile_side(half);
-        total += tiles * tiles * nb;
+        total += tiles * tiles * (nb + (lev == 1 ? dirac : 0));
     }
     return total;
 }
 
-template <typename R> static size_t ana_lds(int TO) {
-    const int IR = 2 * TO + kMaxTaps - 2;
-    return sizeof(C<R>) * (size_t)(IR * IR + 2 * IR * TO);
+template <typename R, int TO> static size_t ana_lds() {
+    return sizeof(C<R>) * (size_t)(ana_region<TO>() * (ana_region<TO>() + 2 * ana_stride<TO>()));
 }
-template <typename R> static size_t syn_lds(int TO) {
-    const int KR = TO + kMaxTaps / 2 - 1;
-    return sizeof(C<R>) * (size_t)(4 * KR * KR + 2 * 2 * TO * KR);
+// Groups per block of the last synthesis level: with fewer tiles than fill the
+// GPU (4 blocks of 256 threads per CU in single, 2 in double precision) the
+// bases of a tile run side by side.
+template <typename R> static int syn_groups(int tiles) {
+    if (sizeof(R) == 8) return tiles >= 512 ? 1 : 2;
+    return tiles >= 1024 ? 1 : tiles >= 512 ? 2 : 4;
+}
+
+template <typename R, int TO>
+static void launch_synthesis(const SynArgs<R> &a, int nb, bool final_level, hipStream_t st) {
+    const int tiles = a.s / (2 * TO), blocks = tiles * tiles;
+    const size_t lds = sizeof(C<R>) * (size_t)syn_cells<TO>();
+    if (!final_level) {
+        hipLaunchKernelGGL((dwt_synthesis<R, TO>), dim3(blocks, nb), dim3(256), lds, st, a);
+        return;
+    }
+    switch (TO < 16 ? 1 : syn_groups<R>(blocks)) {
+        case 1: hipLaunchKernelGGL((dwt_synthesis_final<R, TO, 1>), dim3(blocks), dim3(256), lds, st, a); break;
+        case 2:
+            if constexpr (TO == 16) hipLaunchKernelGGL((dwt_synthesis_final<R, TO, 2>), dim3(blocks), dim3(512), 2 * lds, st, a);
+            break;
+        default:
+            if constexpr (TO == 16 && sizeof(R) == 4)
+                hipLaunchKernelGGL((dwt_synthesis_final<R, TO, 4>), dim3(blocks), dim3(1024), 4 * lds, st, a);
+    }
 }
 
 template <typename R>
-static void psi_adj_impl(riop_plan *p, const void *x, void *alpha, const Prox1<R> *px, hipStream_t st) {
+static void psi_adj_impl(riop_plan *p, const void *x, void *alpha, const Prox1<R> *px, int *flag, hipStream_t st) {
     const int n = p->n, L = p->L;
     AnaArgs<R> a{};
     a.alpha = static_cast<C<R> *>(alpha);
@@ -524,67 +624,63 @@ static void psi_adj_impl(riop_plan *p, const void *x, void *alpha, const Prox1<R
     a.scale = (R)p->scale_q;
     a.prox = px != nullptr;
     if (px) a.px = *px;
-    int nb = 0, dirac_plane = -1;
+    a.in = static_cast<const C<R> *>(x);
+    a.flag = flag;
+    a.dirac_plane = -1;
     for (int i = 0; i < p->q; ++i) {
         if (p->bases[i] == 0) {
-            dirac_plane = i;
+            a.dirac_plane = i;
         } else {
-            a.basis[nb] = p->bases[i];
-            a.plane[nb] = i;
-            ++nb;
+            a.basis[a.nbases] = p->bases[i];
+            a.plane[a.nbases] = i;
+            ++a.nbases;
         }
     }
-    if (dirac_plane >= 0) {
-        AnaArgs<R> d = a;
-        d.plane[0] = dirac_plane;
-        const int blocks = dirac_blocks(n);
+    const int nb = a.nbases;
+    if (nb == 0) {
         TimedScope ts(p, KK_PSI_ADJ, st);
-        hipLaunchKernelGGL(dirac_analysis<R>, dim3(blocks), dim3(256), 0, st, d, static_cast<const C<R> *>(x));
+        hipLaunchKernelGGL(dirac_analysis<R>, dim3(dirac_blocks(n)), dim3(256), 0, st, a);
         RIOP_HIP(hipGetLastError());
-        if (a.prox) a.px.f1_part += blocks;
+        return;
     }
-    if (nb == 0) return;
     C<R> *ll = p->ll.as<C<R>>();
     for (int lev = 1; lev <= L; ++lev) {
         const int s = n >> (lev - 1), half = s >> 1;
         a.s = s;
         a.TO = tile_side(half);
         a.last = lev == L;
-        if (lev == 1) {
-            a.in = static_cast<const C<R> *>(x);
-            a.in_bstride = 0;
-        } else {
+        if (lev > 1) {
             a.in = ll + ll_offset(n, lev - 1);
             a.in_bstride = (long)p->ll_stride;
+            a.flag = nullptr;
         }
         a.ll_out = a.last ? nullptr : ll + ll_offset(n, lev);
         a.ll_bstride = (long)p->ll_stride;
         const int tiles = half / a.TO;
         TimedScope ts(p, KK_PSI_ADJ, st);
-        const dim3 grid(tiles * tiles, nb);
-        AnaArgs<R> al = a;
-        a.px.f1_part += a.prox ? (long)tiles * tiles * nb : 0;
-        switch (al.TO) {
-            case 16: hipLaunchKernelGGL((dwt_analysis<R, 16>), grid, dim3(256), ana_lds<R>(16), st, al); break;
-            case 8: hipLaunchKernelGGL((dwt_analysis<R, 8>), grid, dim3(256), ana_lds<R>(8), st, al); break;
-            case 4: hipLaunchKernelGGL((dwt_analysis<R, 4>), grid, dim3(256), ana_lds<R>(4), st, al); break;
-            case 2: hipLaunchKernelGGL((dwt_analysis<R, 2>), grid, dim3(256), ana_lds<R>(2), st, al); break;
-            default: hipLaunchKernelGGL((dwt_analysis<R, 1>), grid, dim3(256), ana_lds<R>(1), st, al); break;
+        const dim3 grid(tiles * tiles, nb + (lev == 1 && a.dirac_plane >= 0 ? 1 : 0));
+        switch (a.TO) {
+#define ANA(T)                                                                                           \
+    case T: hipLaunchKernelGGL((dwt_analysis<R, T>), grid, dim3(256), (ana_lds<R, T>()), st, a); break;
+            ANA(16) ANA(8) ANA(4) ANA(2)
+#undef ANA
+            default: hipLaunchKernelGGL((dwt_analysis<R, 1>), grid, dim3(256), (ana_lds<R, 1>()), st, a); break;
         }
         RIOP_HIP(hipGetLastError());
+        a.px.f1_part += a.prox ? (long)grid.x * grid.y : 0;
     }
 }
 
-template <typename R> void launch_psi_adj(riop_plan *p, const void *x, void *alpha, hipStream_t st) {
-    psi_adj_impl<R>(p, x, alpha, nullptr, st);
+template <typename R> void launch_psi_adj(riop_plan *p, const void *x, void *alpha, hipStream_t st, int *flag) {
+    psi_adj_impl<R>(p, x, alpha, nullptr, flag, st);
 }
 
 template <typename R>
 void launch_psi_adj_prox(riop_plan *p, const void *x, const Prox1<R> &px, hipStream_t st) {
-    psi_adj_impl<R>(p, x, p->sd.w1.ptr /* unused for prox stores */, &px, st);
+    psi_adj_impl<R>(p, x, p->sd.w1.ptr /* unused for prox stores */, &px, nullptr, st);
 }
 
-template <typename R> void launch_psi(riop_plan *p, const void *alpha, void *x, hipStream_t st) {
+template <typename R> void launch_psi(riop_plan *p, const void *alpha, void *x, hipStream_t st, int *flag) {
     const int n = p->n, L = p->L;
     SynArgs<R> a{};
     a.alpha = static_cast<const C<R> *>(alpha);
@@ -592,6 +688,7 @@ template <typename R> void launch_psi(riop_plan *p, const void *alpha, void *x, 
     a.n = n;
     a.scale = (R)p->scale_q;
     a.x = static_cast<C<R> *>(x);
+    a.flag = flag;
     a.dirac_plane = -1;
     int nb = 0;
     for (int i = 0; i < p->q; ++i) {
@@ -608,8 +705,7 @@ template <typename R> void launch_psi(riop_plan *p, const void *alpha, void *x, 
         const long N = (long)n * n;
         const int blocks = (int)std::min<long>((N + 255) / 256, 4096);
         TimedScope ts(p, KK_PSI, st);
-        hipLaunchKernelGGL(dirac_only_synthesis<R>, dim3(blocks), dim3(256), 0, st, a.alpha, a.dirac_plane,
-                           a.x, N, a.scale);
+        hipLaunchKernelGGL(dirac_only_synthesis<R>, dim3(blocks), dim3(256), 0, st, a, N);
         RIOP_HIP(hipGetLastError());
         return;
     }
@@ -621,24 +717,27 @@ template <typename R> void launch_psi(riop_plan *p, const void *alpha, void *x, 
         a.coarsest = lev == L;
         a.ll_in = a.coarsest ? nullptr : ll + ll_offset(n, lev);
         a.ll_in_bstride = (long)p->ll_stride;
-        const int TS = 2 * a.TO, tiles = s / TS;
         TimedScope ts(p, KK_PSI, st);
         if (lev > 1) {
             a.ll_out = ll + ll_offset(n, lev - 1);
             a.ll_out_bstride = (long)p->ll_stride;
-            hipLaunchKernelGGL(dwt_synthesis<R>, dim3(tiles * tiles, nb), dim3(256), syn_lds<R>(a.TO), st, a);
-        } else {
-            hipLaunchKernelGGL(dwt_synthesis_final<R>, dim3(tiles * tiles), dim3(256), syn_lds<R>(a.TO), st, a);
+        }
+        switch (a.TO) {
+            case 16: launch_synthesis<R, 16>(a, nb, lev == 1, st); break;
+            case 8: launch_synthesis<R, 8>(a, nb, lev == 1, st); break;
+            case 4: launch_synthesis<R, 4>(a, nb, lev == 1, st); break;
+            case 2: launch_synthesis<R, 2>(a, nb, lev == 1, st); break;
+            default: launch_synthesis<R, 1>(a, nb, lev == 1, st); break;
         }
         RIOP_HIP(hipGetLastError());
     }
 }
 
 // Daubechies filters for the device, built on the host (see plan.cpp).
-template void launch_psi_adj<float>(riop_plan *, const void *, void *, hipStream_t);
-template void launch_psi_adj<double>(riop_plan *, const void *, void *, hipStream_t);
-template void launch_psi<float>(riop_plan *, const void *, void *, hipStream_t);
-template void launch_psi<double>(riop_plan *, const void *, void *, hipStream_t);
+template void launch_psi_adj<float>(riop_plan *, const void *, void *, hipStream_t, int *);
+template void launch_psi_adj<double>(riop_plan *, const void *, void *, hipStream_t, int *);
+template void launch_psi<float>(riop_plan *, const void *, void *, hipStream_t, int *);
+template void launch_psi<double>(riop_plan *, const void *, void *, hipStream_t, int *);
 template void launch_psi_adj_prox<float>(riop_plan *, const void *, const Prox1<float> &, hipStream_t);
 template void launch_psi_adj_prox<double>(riop_plan *, const void *, const Prox1<double> &, hipStream_t);
 
