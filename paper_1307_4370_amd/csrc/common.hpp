@@ -32,6 +32,16 @@ template <typename R> __device__ inline C<R> cmul(C<R> a, C<R> b) {
 }
 template <typename R> __device__ inline C<R> cscale(C<R> a, R s) { return mk<R>(a.x * s, a.y * s); }
 
+// Check of loaded inputs: 0 z added for every value; the sum is zero unless one
+// was a NaN or an infinity.
+template <typename R> struct FiniteCheck {
+    R acc = R(0);
+    __device__ void add(C<R> z) { acc = z.y * R(0) + (z.x * R(0) + acc); }
+    __device__ void report(int *flag) const {
+        if (!(acc == R(0))) atomicOr(flag, 1);
+    }
+};
+
 // ---------------------------------------------------------------------------
 // Error handling: every entry point converts failures into a riop_status and a
 // thread-local message.
@@ -267,8 +277,8 @@ constexpr int kRedBlocks = 512;
 // Sec. 4.4): before a forward transform of p, the direction update
 // p <- r + beta p with beta = sum(part[slot_new]) / sum(part[slot_old]) (0 when
 // the old sum is 0); after an adjoint transform into q, q <- q + 2 p with the
-// per-block partials of sum Re(conj(p) q) left in part[slot_pq].  `part` holds
-// kRedBlocks doubles per slot.
+// per-block partials of sum Re(conj(p) q) left in part[slot_pq] (part null: no
+// partials).  `part` holds kRedBlocks doubles per slot.
 template <typename R> struct CgFuse {
     const C<R> *r = nullptr;  // residual (direction update), nullable
     const C<R> *p = nullptr;  // direction (p.q), nullable
@@ -279,9 +289,11 @@ template <typename R> struct CgFuse {
 // kernel with at most kRedBlocks column blocks).
 bool fft_folds_cg(const riop_plan *p);
 // Forward FFT passes; returns whether cg->r's direction update was folded in
-// (false: the caller must apply it first; nothing was done).
+// (false: the caller must apply it first; nothing was done).  flag (nullable): set
+// to 1 where x holds a NaN or Inf.
 template <typename R>
-bool launch_phi_fft_forward(riop_plan *p, const void *x, hipStream_t st, const CgFuse<R> *cg = nullptr);
+bool launch_phi_fft_forward(riop_plan *p, const void *x, hipStream_t st, const CgFuse<R> *cg = nullptr,
+                            int *flag = nullptr);
 // Adjoint FFT passes; `grid` selects the input grid (nullptr: the plan's grid).
 // Returns whether cg->p's q + 2 p and p.q partials were folded in.
 template <typename R>
@@ -300,8 +312,9 @@ template <typename R> void launch_gram_apply(riop_plan *p, const void *in_grid, 
 template <typename R> void launch_grid_merge(riop_plan *p, void *grid, hipStream_t st);
 template <typename R>
 void launch_degrid(riop_plan *p, void *y, int order_user, hipStream_t st);
+// flag (nullable): set to 1 where y holds a NaN or Inf.
 template <typename R>
-void launch_grid(riop_plan *p, const void *y, int order_user, hipStream_t st);
+void launch_grid(riop_plan *p, const void *y, int order_user, hipStream_t st, int *flag = nullptr);
 template <typename R>
 void launch_grid_prox2(riop_plan *p, const void *s, void *z2, const void *y, const double *scale, hipStream_t st);
 template <typename R> void launch_fill_zero(void *buf, size_t ncomplex, hipStream_t st);

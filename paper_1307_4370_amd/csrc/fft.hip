@@ -35,9 +35,10 @@ template <typename R> struct FftArgs {
     // CG steps folded into the column passes (compile-time kernel).  Forward:
     // with cg_r set, the input p is replaced by r + beta p first and written
     // back, beta = sum(cg_part[cg_new]) / sum(cg_part[cg_old]).  Adjoint: with
-    // cg_p set, the output q becomes q + 2 p and each block leaves its part of
-    // sum Re(conj(p) q) in cg_part[cg_pq] (kRedBlocks doubles per slot).
+    // cg_p set, the output q becomes q + 2 p and, unless cg_part is null, each
+    // block leaves its part of sum Re(conj(p) q) in cg_part[cg_pq] (kRedBlocks doubles per slot).
     const C<R> *cg_r, *cg_p;
+    int *flag;           // forward column pass: set to 1 where the input holds a NaN or Inf (nullptr: not checked)
     double *cg_part;
     int cg_old, cg_new, cg_pq;
     int N, nbatch, C, n;
@@ -253,6 +254,7 @@ __global__ void __launch_bounds__(COLS ? fft_col_threads : 256, COLS ? 1 : 2) ff
     const int ls = COLS ? a.C : 1;
 
     C<R> v[E];
+    FiniteCheck<R> fc;
     const R tf = (active && a.dbt && a.factors_at_input) ? a.dbt[t] : R(1);
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -261,6 +263,7 @@ __global__ void __launch_bounds__(COLS ? fft_col_threads : 256, COLS ? 1 : 2) ff
         C<R> z = mk<R>(0, 0);
         if (active && j >= 0) {
             z = a.in[t * a.in_ts + (long)j * a.in_es];
+            if (COLS && SGN < 0 && a.flag) fc.add(z);
             if (a.factors_at_input) {
                 R f = a.scale * tf;
                 if (a.dax) f *= a.dax[j];
@@ -269,6 +272,7 @@ __global__ void __launch_bounds__(COLS ? fft_col_threads : 256, COLS ? 1 : 2) ff
         }
         v[e] = z;
     }
+    if (COLS && SGN < 0 && a.flag) fc.report(a.flag);
 
     int Ns = 1;
     for (int s = 0; s < a.nstages; ++s) {
@@ -378,6 +382,12 @@ fft_pass_ct(FftArgs<R> a) {
             if ((e < E1 || e >= E3) && active) v[e] = src[band(e) * ies];
         }
         if constexpr (COLS) {
+            if (a.flag) {
+                FiniteCheck<R> fc;
+#pragma unroll
+                for (int e = 0; e < E; ++e) fc.add(v[e]);
+                fc.report(a.flag);
+            }
             if (a.cg_r) {
                 // CG direction p = r + beta p, beta = rr_new / rr_old (0 when
                 // rr_old = 0), reduced while the line's loads are in flight.
@@ -509,7 +519,7 @@ fft_pass_ct(FftArgs<R> a) {
                 C<R> z = v[e];
                 if constexpr (COLS) {
                     z = cscale<R>(z, f0 * a.dax[j]);
-                    if (a.cg_p) {  // q + 2 p
+                    if (a.cg_p) {  // q + 2 p (loaded before its place in q is written)
                         const C<R> pv = a.cg_p[t + (long)j * oes];
                         z.x += R(2) * pv.x;
                         z.y += R(2) * pv.y;
@@ -520,7 +530,7 @@ fft_pass_ct(FftArgs<R> a) {
             }
         }
         if constexpr (COLS) {
-            if (a.cg_p) {
+            if (a.cg_p && a.cg_part) {
                 acc = block_sum_all(acc, reinterpret_cast<double *>(smem));
                 double *slot = a.cg_part + (long)a.cg_pq * kRedBlocks;
                 if (threadIdx.x == 0) slot[blockIdx.x] = acc;
@@ -635,11 +645,11 @@ static bool launch_pass(riop_plan *p, FftArgs<R> a, int kind, hipStream_t st) {
     RIOP_REQUIRE(threads <= 1024, RIOP_ENOTSUP, "FFT block too large");
     const int blocks = (a.nbatch + Cb - 1) / Cb;
     const size_t lds = line * Cb;
-    // CG steps ride only on the compile-time column kernel, with at most one
-    // partial per block.
+    // CG steps ride only on the compile-time column kernel, their sums with at
+    // most one partial per block.
     bool fused = false;
     if (a.cg_r || a.cg_p) {
-        fused = COLS && ct && blocks <= kRedBlocks && (threads & (threads - 1)) == 0;
+        fused = COLS && ct && (!a.cg_part || blocks <= kRedBlocks);
         if (!fused) a.cg_r = a.cg_p = nullptr;
     }
     TimedScope ts(p, kind, st);
@@ -675,7 +685,7 @@ bool fft_folds_cg(const riop_plan *p) {
 }
 
 template <typename R>
-bool launch_phi_fft_forward(riop_plan *p, const void *x, hipStream_t st, const CgFuse<R> *cg) {
+bool launch_phi_fft_forward(riop_plan *p, const void *x, hipStream_t st, const CgFuse<R> *cg, int *flag) {
     const int n = p->n, K = p->K;
     const R *d = p->deapod.as<R>();
     // Pass 1: columns q of x, transform over p; pad, correct by d(p) d(q), scale 1/K.
@@ -694,6 +704,7 @@ bool launch_phi_fft_forward(riop_plan *p, const void *x, hipStream_t st, const C
     a.dbt = d;
     a.factors_at_input = 1;
     a.scale = R(1) / R(K);
+    a.flag = flag;
     if (cg && cg->r) {
         a.cg_r = cg->r;
         a.cg_part = cg->part;
@@ -779,8 +790,8 @@ bool launch_phi_fft_adjoint(riop_plan *p, void *x, hipStream_t st, const void *g
     return launch_pass<R, +1, true>(p, b, KK_FFT_ADJ_COL, st);
 }
 
-template bool launch_phi_fft_forward<float>(riop_plan *, const void *, hipStream_t, const CgFuse<float> *);
-template bool launch_phi_fft_forward<double>(riop_plan *, const void *, hipStream_t, const CgFuse<double> *);
+template bool launch_phi_fft_forward<float>(riop_plan *, const void *, hipStream_t, const CgFuse<float> *, int *);
+template bool launch_phi_fft_forward<double>(riop_plan *, const void *, hipStream_t, const CgFuse<double> *, int *);
 template bool launch_phi_fft_adjoint<float>(riop_plan *, void *, hipStream_t, const void *, const CgFuse<float> *);
 template bool launch_phi_fft_adjoint<double>(riop_plan *, void *, hipStream_t, const void *,
                                              const CgFuse<double> *);

@@ -474,6 +474,7 @@ template <typename R> struct TileArgs {
     const C<R> *vin;          // values to grid
     const R *__restrict__ kc; // kernel coefficients [pair][even/odd][D/2 + 1]
     int K, T, TB, tps;        // grid side, tile side, band rows, tiles per side
+    int *flag;                // set to 1 where vin holds a NaN or Inf (nullptr: not checked)
     // Fused l2-ball prox (P2 kernels, plan order): the values gridded are
     // d2 = r2 - z2' - s with v = s + z2, r2 = y + (v - y) scale, z2' = v - r2,
     // and z2' replaces z2.
@@ -710,6 +711,7 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
         }
         dacc = mf4{R(0), R(0), R(0), R(0)};
     };
+    FiniteCheck<R> fc;
     int cur = -1;  // packed window row and column block of the open run (-1: none yet)
 
     for (int base = f_begin; base < f_end; base += SL) {
@@ -727,6 +729,7 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
         // Staging.  Lanes past the end stage zero values, so the
         // accumulation below runs over all 64 entries without bound tests.
         if (!live) val = mk<R>(0, 0);
+        if (!P2 && a.flag) fc.add(val);
         const int la = (int)(cv & 0xffffu) - ta, lb = (int)(cv >> 16) - tb;  // in [0, T)
         const int pos = (live && ax == 0) ? (la << 8) | (lb >> 3) : -1;
         const int db = lb & 7;
@@ -887,6 +890,7 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
         // The next slice's staging overwrites this one.
         __builtin_amdgcn_wave_barrier();
     }
+    if (!P2 && a.flag) fc.report(a.flag);
     if (cur >= 0) {
         if constexpr (MF) close_run_mf(cur);
         else close_run(cur);
@@ -1171,8 +1175,9 @@ void check_grid_lds(riop_plan *p) {
 
 template <typename R>
 static void launch_tiles(riop_plan *p, const void *vals, int order_user, void *out_grid, hipStream_t st,
-                         const TileArgs<R> *p2 = nullptr) {
+                         const TileArgs<R> *p2 = nullptr, int *flag = nullptr) {
     TileArgs<R> a{};
+    a.flag = flag;
     a.grid = static_cast<C<R> *>(out_grid);
     a.halo = p->halo.as<C<R>>();
     a.cell = p->cell.as<uint32_t>();
@@ -1234,8 +1239,8 @@ template <typename R> void launch_grid_merge(riop_plan *p, void *grid, hipStream
     }
 }
 
-template <typename R> void launch_grid(riop_plan *p, const void *y, int order_user, hipStream_t st) {
-    launch_tiles<R>(p, y, order_user, p->grid.ptr, st);
+template <typename R> void launch_grid(riop_plan *p, const void *y, int order_user, hipStream_t st, int *flag) {
+    launch_tiles<R>(p, y, order_user, p->grid.ptr, st, nullptr, flag);
 }
 
 // Gridding of the l2-ball prox's output, formed inside the gridding kernel
@@ -1265,8 +1270,8 @@ template void launch_gram<float>(riop_plan *, const void *, void *, hipStream_t)
 template void launch_gram<double>(riop_plan *, const void *, void *, hipStream_t);
 template void launch_degrid<float>(riop_plan *, void *, int, hipStream_t);
 template void launch_degrid<double>(riop_plan *, void *, int, hipStream_t);
-template void launch_grid<float>(riop_plan *, const void *, int, hipStream_t);
-template void launch_grid<double>(riop_plan *, const void *, int, hipStream_t);
+template void launch_grid<float>(riop_plan *, const void *, int, hipStream_t, int *);
+template void launch_grid<double>(riop_plan *, const void *, int, hipStream_t, int *);
 template void launch_grid_prox2<float>(riop_plan *, const void *, void *, const void *, const double *, hipStream_t);
 template void launch_grid_prox2<double>(riop_plan *, const void *, void *, const void *, const double *, hipStream_t);
 template void launch_grid_merge<float>(riop_plan *, void *, hipStream_t);

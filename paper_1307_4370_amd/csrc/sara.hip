@@ -43,16 +43,6 @@ template <typename R> struct AnaArgs {
     Prox1<R> px;
 };
 
-// Check of loaded inputs: 0 z added for every value; the sum is zero unless one
-// was a NaN or an infinity.
-template <typename R> struct FiniteCheck {
-    R acc = R(0);
-    __device__ void add(C<R> z) { acc = z.y * R(0) + (z.x * R(0) + acc); }
-    __device__ void report(int *flag) const {
-        if (!(acc == R(0))) atomicOr(flag, 1);
-    }
-};
-
 // Block sum of f1 into this block's own partial slot (no atomics; the
 // consumer adds the slots in a fixed order).
 __device__ inline void block_add_f1(double f1, double *part) {

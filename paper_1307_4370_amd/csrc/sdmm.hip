@@ -110,10 +110,12 @@ constexpr int kU = 4;
 template <typename R> __device__ inline double abs2(C<R> z) { return (double)z.x * z.x + (double)z.y * z.y; }
 
 // r = b - (Qx_partial + 2 x); p = r; slot <- sum |r|^2 (ax null: Qx_partial = 0);
-// the CG iteration count restarts.
+// the CG iteration count restarts.  flag (nullable): set to 1 where b holds a NaN
+// or Inf.
 template <typename R>
 __global__ void cg_init(const C<R> *b, const C<R> *x, const C<R> *ax, C<R> *r, C<R> *p, long N, double *partials,
-                        int slot, double *scalars) {
+                        int slot, double *scalars, int *flag) {
+    FiniteCheck<R> fc;
     if (blockIdx.x == 0 && threadIdx.x == 0) scalars[SC_CGIT] = 0.0;
     double acc = 0;
     CHUNK_LOOP(i0, st, N) {
@@ -125,12 +127,14 @@ __global__ void cg_init(const C<R> *b, const C<R> *x, const C<R> *ax, C<R> *r, C
         }
         FOR_U(u) if (i0 + u * st < N) {
             const long i = i0 + u * st;
+            if (flag) fc.add(bv[u]);
             const C<R> ri = mk<R>(bv[u].x - (av[u].x + R(2) * xv[u].x), bv[u].y - (av[u].y + R(2) * xv[u].y));
             r[i] = ri;
             p[i] = ri;
             acc += abs2<R>(ri);
         }
     }
+    if (flag) fc.report(flag);
     const double s = block_sum(acc);
     if (threadIdx.x == 0) partials[slot * kRedBlocks + blockIdx.x] = s;
 }
@@ -234,10 +238,10 @@ __global__ void slot_to_scalar(const double *partials, int slot, double *scalars
     if (threadIdx.x == 0) scalars[which] = s;
 }
 
-// out = a + 2 b
-template <typename R> __global__ void add_2x(const C<R> *a, const C<R> *b, C<R> *out, long N) {
+// out <- out + 2 x
+template <typename R> __global__ void add_2x(const C<R> *x, C<R> *out, long N) {
     GRID_LOOP(i, N) {
-        const C<R> ai = a[i], bi = b[i];
+        const C<R> ai = out[i], bi = x[i];
         out[i] = mk<R>(ai.x + R(2) * bi.x, ai.y + R(2) * bi.y);
     }
 }
@@ -262,8 +266,20 @@ __global__ void set_scalar(double *scalars, int which, double v) {
 }
 
 // Gather / scatter between caller order and plan order.
-template <typename R> __global__ void gather_perm(const C<R> *src, const int *perm, C<R> *dst, long M) {
-    GRID_LOOP(i, M) dst[i] = src[perm[i]];
+// (gather: flag, nullable, set to 1 where src holds a NaN or Inf).
+template <typename R> __global__ void gather_perm(const C<R> *src, const int *perm, C<R> *dst, long M, int *flag) {
+    FiniteCheck<R> fc;
+    CHUNK_LOOP(i0, st, M) {
+        int pv[kU];
+        C<R> v[kU];
+        FOR_U(u) if (i0 + u * st < M) pv[u] = perm[i0 + u * st];
+        FOR_U(u) if (i0 + u * st < M) v[u] = src[pv[u]];
+        FOR_U(u) if (i0 + u * st < M) {
+            fc.add(v[u]);
+            dst[i0 + u * st] = v[u];
+        }
+    }
+    if (flag) fc.report(flag);
 }
 template <typename R> __global__ void scatter_perm(const C<R> *src, const int *perm, C<R> *dst, long M) {
     GRID_LOOP(i, M) dst[perm[i]] = src[i];
@@ -676,11 +692,17 @@ static void ensure_work(riop_plan *p) {
     w.ready = true;
 }
 
-template <typename R> static void gram_sorted(riop_plan *p, const void *x, void *out, hipStream_t s) {
-    // out = Phi^dagger Phi x = Z^T D F^dagger (G^T G) F D Z x, with G^T G fused.
-    launch_phi_fft_forward<R>(p, x, s);
+// out = Phi^dagger Phi x = Z^T D F^dagger (G^T G) F D Z x, with G^T G fused; plus
+// 2 x with plus_2x (returns whether it was added: the column pass can only at some
+// lengths).  flag (nullable): set to 1 where x holds a NaN or Inf.
+template <typename R>
+static bool gram_sorted(riop_plan *p, const void *x, void *out, hipStream_t s, int *flag = nullptr,
+                        bool plus_2x = false) {
+    CgFuse<R> q;
+    if (plus_2x) q.p = static_cast<const C<R> *>(x);
+    launch_phi_fft_forward<R>(p, x, s, nullptr, flag);
     launch_gram<R>(p, p->grid.ptr, p->grid2.ptr, s);
-    launch_phi_fft_adjoint<R>(p, out, s, p->grid2.ptr);
+    return launch_phi_fft_adjoint<R>(p, out, s, p->grid2.ptr, &q);
 }
 
 // out = Phi^dagger y for y in plan order.
@@ -709,18 +731,19 @@ template <typename R> static CgWork<R> plan_cg_work(riop_plan *p) {
 }
 
 // CG on Q from x.  b_less_gram: b already has Phi^dagger Phi x subtracted.
-// Besides the plan's operator buffers it touches only `w`.
+// Besides the plan's operator buffers it touches only `w`.  flag (nullable): set to
+// 1 where b or x holds a NaN or Inf (x is checked unless b_less_gram).
 template <typename R>
 static void cg_run(riop_plan *p, const void *b, void *x, int n_iter, double tol, int *final_slot, hipStream_t s,
-                   const CgWork<R> &w, bool b_less_gram = false) {
+                   const CgWork<R> &w, bool b_less_gram = false, int *flag = nullptr) {
     const long N = (long)p->n * p->n;
     double *part = w.partials;
     double *sc = w.scalars;
     const double tol2 = tol > 0 ? tol * tol : 0.0;
-    if (!b_less_gram) gram_sorted<R>(p, x, w.qp, s);
+    if (!b_less_gram) gram_sorted<R>(p, x, w.qp, s, flag);
     VEC_LAUNCH(p, cg_init<R>, RB(), RT(), 0, s, static_cast<const C<R> *>(b), static_cast<const C<R> *>(x),
                        b_less_gram ? (const C<R> *)nullptr : (const C<R> *)w.qp, w.r, w.p, N, part, (int)SLOT_RR0,
-                       sc);
+                       sc, flag);
     RIOP_HIP(hipGetLastError());
     // Where the FFT's column passes can, they apply the direction update
     // (before transforming p) and form q + 2 p with its p.q partials (after);
@@ -759,11 +782,12 @@ static void cg_run(riop_plan *p, const void *b, void *x, int n_iter, double tol,
 
 // gamma = beta ||L1^dagger Phi^dagger y||_inf with L1 = Psi^dagger (SARA) or I (TV).
 template <typename R> static void gamma_run(riop_plan *p, const void *y_sorted_or_user, int user, double beta,
-                                            hipStream_t s, int which, int prior = PRIOR_SARA) {
+                                            hipStream_t s, int which, int prior = PRIOR_SARA,
+                                            int *flag = nullptr) {
     ensure_work(p);
     SdmmWork &w = p->sd;
     const long N = (long)p->n * p->n, D = (long)p->q * N;
-    launch_grid<R>(p, y_sorted_or_user, user, s);
+    launch_grid<R>(p, y_sorted_or_user, user, s, flag);
     launch_phi_fft_adjoint<R>(p, w.tmpN.ptr, s);
     if (prior == PRIOR_TV) {
         VEC_LAUNCH(p, max_abs<R>, RB(), RT(), 0, s, w.tmpN.as<C<R>>(), N, w.partials.as<double>(), (int)SLOT_MAX);
@@ -809,19 +833,17 @@ static void sdmm_init(riop_plan *p, const void *y, double eps, const riop_sdmm_p
     w.cg_tol = prm->cg_tol;
     C<R> *xh = w.xhat.as<C<R>>();
     // Caller inputs: NaN or Inf sets the plan's non-finite flag.
-    check_finite_input(p, y, 2 * M, s);
     check_finite_input(p, x0, 2 * N, s);
     check_finite_input(p, prm->weights, D, s);
     if (prm->resume) {
         check_finite_input(p, prm->z1, 2 * D, s);
-        check_finite_input(p, prm->z2, 2 * M, s);
         check_finite_input(p, prm->z3, 2 * N, s);
         check_finite_input(p, prm->rhs, 2 * N, s);
     }
 
     if (M > 0)
         VEC_LAUNCH(p, gather_perm<R>, RB(), RT(), 0, s, static_cast<const C<R> *>(y), p->perm.as<int>(),
-                   w.ysort.as<C<R>>(), M);
+                   w.ysort.as<C<R>>(), M, p->nonfinite.as<int>());
     VEC_LAUNCH(p, set_scalar, dim3(1), dim3(1), 0, s, sc, (int)SC_EPS, eps);
     VEC_LAUNCH(p, set_scalar, dim3(1), dim3(1), 0, s, sc, (int)SC_ITER, 0.0);
     if (prm->gamma > 0) {
@@ -838,7 +860,7 @@ static void sdmm_init(riop_plan *p, const void *y, double eps, const riop_sdmm_p
         RIOP_HIP(hipMemcpyAsync(w.rhs.ptr, prm->rhs, cb * N, hipMemcpyDeviceToDevice, s));
         if (M > 0)
             VEC_LAUNCH(p, gather_perm<R>, RB(), RT(), 0, s, static_cast<const C<R> *>(prm->z2),
-                       p->perm.as<int>(), w.z2loc.as<C<R>>(), M);
+                       p->perm.as<int>(), w.z2loc.as<C<R>>(), M, p->nonfinite.as<int>());
         VEC_LAUNCH(p, set_scalar, dim3(1), dim3(1), 0, s, sc, (int)SC_F1PREV, prm->f1_prev);
         // rhs <- b - Phi^dagger Phi xhat
         phi_into_s2<R>(p, xh, s);
@@ -1188,10 +1210,8 @@ static void reweighted_run(riop_plan *p, const void *y, double eps, const riop_s
 template <typename R> static void apply_q_run(riop_plan *p, const void *x, void *out, hipStream_t s) {
     const long N = (long)p->n * p->n;
     ensure_work(p);
-    check_finite_input(p, x, 2 * N, s);
-    gram_sorted<R>(p, x, p->sd.tmpN.ptr, s);
-    VEC_LAUNCH(p, add_2x<R>, RB(), RT(), 0, s, p->sd.tmpN.as<C<R>>(), static_cast<const C<R> *>(x),
-                       static_cast<C<R> *>(out), N);
+    if (!gram_sorted<R>(p, x, out, s, p->nonfinite.as<int>(), true))
+        VEC_LAUNCH(p, add_2x<R>, RB(), RT(), 0, s, static_cast<const C<R> *>(x), static_cast<C<R> *>(out), N);
     RIOP_HIP(hipGetLastError());
 }
 
@@ -1201,10 +1221,8 @@ template <typename R>
 static void cg_with(riop_plan *p, const void *b, void *x, int n_iter, double tol, double *rr_out, int32_t *iters_out,
                     hipStream_t s, const CgWork<R> &w) {
     const long N = (long)p->n * p->n;
-    check_finite_input(p, b, 2 * N, s);
-    check_finite_input(p, x, 2 * N, s);
     int slot = SLOT_RR0;
-    cg_run<R>(p, b, x, n_iter, tol, &slot, s, w);
+    cg_run<R>(p, b, x, n_iter, tol, &slot, s, w, false, p->nonfinite.as<int>());
     if (rr_out || iters_out) {
         VEC_LAUNCH(p, slot_to_scalar, dim3(1), RT(), 0, s, (const double *)w.partials, slot, w.scalars,
                    (int)SC_RRFINAL);
@@ -1287,8 +1305,7 @@ static void cg_noalloc_entry(riop_plan *p, const void *b, void *x, int n_iter, d
 
 template <typename R> static void gamma_entry(riop_plan *p, const void *y, double beta, double *g, hipStream_t s) {
     ensure_work(p);
-    check_finite_input(p, y, 2 * p->M, s);
-    gamma_run<R>(p, y, 1, beta, s, (int)SC_GAMMA_Q);
+    gamma_run<R>(p, y, 1, beta, s, (int)SC_GAMMA_Q, PRIOR_SARA, p->nonfinite.as<int>());
     RIOP_HIP(hipMemcpyAsync(g, p->sd.scalars.as<double>() + SC_GAMMA_Q, sizeof(double), hipMemcpyDeviceToHost, s));
     report_nonfinite(p, s);
     mark_done(p, s);
