@@ -140,13 +140,14 @@ def algorithmic_bytes(kind: str, n: int, M: int, cbytes: int, J: int = 8):
       degrid:      read the grid 4N + (u, v) M, write y M            -> 4N + 2M
       grid:        read (u, v) M + values M, write the grid 4N       -> 4N + 2M
       grid_zero:   write the grid 4N
+      gram_fused:  read the grid 4N and (u, v) M, write the grid 4N  -> 8N + M
       gram:        read the J + (J-1)(2J-1) real planes of G^T G (half a
                    complex each per cell), read the grid 4N, write 4N
     """
     N = n * n
     planes = J + (J - 1) * (2 * J - 1)
     table = {"gram": 4 * N * 2 + 4 * N * planes / 2, "fft_fwd_col": 3 * N, "fft_fwd_row": 6 * N, "fft_adj_row": 6 * N, "fft_adj_col": 3 * N,
-             "degrid": 4 * N + 2 * M, "grid": 4 * N + 2 * M, "grid_zero": 4 * N}
+             "degrid": 4 * N + 2 * M, "grid": 4 * N + 2 * M, "grid_zero": 4 * N, "gram_fused": 8 * N + M}
     return table[kind] * cbytes if kind in table else None
 
 

@@ -150,7 +150,8 @@ TimedScope::~TimedScope() {
 
 static const char *kKindNames[KK_COUNT] = {"fft_fwd_col", "fft_fwd_row", "fft_adj_row", "fft_adj_col",
                                            "degrid",      "grid",        "grid_zero",   "psi_adj",
-                                           "psi",         "vector",      "grid_prox2",  "gram"};
+                                           "psi",         "vector",      "grid_prox2",  "gram",
+                                           "gram_fused"};
 
 // ---------------------------------------------------------------------------
 // Kaiser-Bessel kernel on the host.

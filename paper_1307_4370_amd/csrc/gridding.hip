@@ -521,6 +521,23 @@ __device__ inline void store_region(const TileArgs<R> &a, const double *tre, con
     }
 }
 
+// An empty band: zeros for its cells and its halo cells.
+template <typename R, int J>
+__device__ inline void store_empty(const TileArgs<R> &a, int ta, int tb, int tid, int nthreads) {
+    const int T = a.T, TB = a.TB, tps = a.tps, lt = __builtin_ctz(T), dc = tb >> lt, br = ta >> __builtin_ctz(TB);
+    for (int c = tid; c < TB * T; c += nthreads) {
+        const int r = c >> lt;
+        a.grid[(int64_t)(ta + r) * a.K + tb + (c & (T - 1))] = mk<R>(0, 0);
+    }
+    C<R> *right = a.halo + halo_right(J, tps, ta, dc);
+    for (int c = tid; c < TB * (J - 1); c += nthreads) {
+        const int r = c / (J - 1);
+        right[(int64_t)r * tps * (J - 1) + c - r * (J - 1)] = mk<R>(0, 0);
+    }
+    C<R> *bottom = a.halo + halo_bottom(T, J, tps, br, dc);
+    for (int c = tid; c < (J - 1) * (T + J - 1); c += nthreads) bottom[c] = mk<R>(0, 0);
+}
+
 // A band's visibilities are one contiguous plan-order range; its wavefronts
 // take equal contiguous shares of it and work independently, at most 64
 // visibilities (a slice) at a time.
@@ -582,19 +599,8 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
     const int lnb = __builtin_ctz(T) - __builtin_ctz(TB);  // log2 of the tile's bands
     const int tile = wk.tile >> lnb, band = wk.tile & ((1 << lnb) - 1);
     const int ta = (tile / tps) * T + band * TB, tb = (tile % tps) * T;
-    if (total == 0) {  // an empty band: zeros for its cells and its halo cells, no region
-        const int lt = __builtin_ctz(T), dc = tb >> lt, br = ta >> __builtin_ctz(TB);
-        for (int c = tid; c < TB * T; c += kThreads) {
-            const int r = c >> lt;
-            a.grid[(int64_t)(ta + r) * K + tb + (c & (T - 1))] = mk<R>(0, 0);
-        }
-        C<R> *right = a.halo + halo_right(J, tps, ta, dc);
-        for (int c = tid; c < TB * (J - 1); c += kThreads) {
-            const int r = c / (J - 1);
-            right[(int64_t)r * tps * (J - 1) + c - r * (J - 1)] = mk<R>(0, 0);
-        }
-        C<R> *bottom = a.halo + halo_bottom(T, J, tps, br, dc);
-        for (int c = tid; c < (J - 1) * (T + J - 1); c += kThreads) bottom[c] = mk<R>(0, 0);
+    if (total == 0) {
+        store_empty<R, J>(a, ta, tb, tid, kThreads);
         return;
     }
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -899,6 +905,214 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
     store_region<R, J>(a, tre, tim, ta, tb, tid, kThreads);
 }
 
+// ---------------------------------------------------------------------------
+// G^T G in one launch (single precision, windows up to 8 wide): each visibility
+// of a band is degridded from the input grid's region, staged in LDS beside the
+// output region, and gridded at once.  The M values are never stored, cells and
+// offsets are read and weights formed once instead of twice.
+//
+// Slices of 32 visibilities, lane = entry + 32 half.  Each lane forms the J
+// weights of one axis (lower half u, upper half v); lane swaps between the
+// halves then leave in every lane the row weights of its own J/2 window rows and
+// all column weights.  A lane degrids its rows and a swap adds the two sums; it
+// stages its rows' weights times the value and its half of the column block.
+// The 4.6 KB of staging per wavefront (8.7 KB with 64-entry slices) and the
+// single-precision input region leave room for two workgroups of eight
+// wavefronts per CU (81.8 of 160 KB each at 32 x 32); four, five and six
+// wavefronts measured 148, 148 and 141 us, 16-row bands 141 us.
+// Bound by LDS (window reads, 512 B per visibility, and the run closes: 83 of
+// 124 us busy) and the vector unit (62 us busy) together.
+// J = 8, degridding + gridding -> here: 1024^2, M = 4194304, 54 + 86 -> 124 us;
+// 512^2, M = 700001, 15 + 24 -> 33 us; 1536^2, M = 2350001, 52 + 101 -> 141 us;
+// 256^2, M = 131072, 7.5 + 11.6 -> 14.8 us.
+constexpr int kGramWaves = 8;
+// Row length of the input region: a multiple of 32 cells, so that a row's cells
+// continue in the banks where the row before ends, as plan order does.
+__host__ __device__ constexpr int gram_stride(int T, int J) { return (T + J - 1 + 31) / 32 * 32; }
+template <int J> static size_t gram_tile_lds(int TB, int T) {
+    return (size_t)region_rows(TB, J) * (region_stride(T, J) * 2 * sizeof(double) + gram_stride(T, J) * sizeof(float2)) + (size_t)kGramWaves * 36 * (8 * sizeof(float2) + 16 * sizeof(float));
+}
+
+// {a.lower, b.lower} and {a.upper, b.upper} (halves of 32 lanes).
+__device__ inline void swap_halves(float &a, float &b) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+__device__ inline float sum_halves(float a) {
+    float b = a;
+    swap_halves(a, b);
+    return a + b;
+}
+
+template <int J> __global__ void __launch_bounds__(64 * kGramWaves, 4) gram_tile(TileArgs<float> a, const float2 *gin) {
+    constexpr int kThreads = 64 * kGramWaves, H = J / 2, SL = 32, SR = 36;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int T = a.T, TB = a.TB, K = a.K, tps = a.tps;
+    const int RR = region_rows(TB, J), RS = region_stride(T, J), PS = RR * RS;
+    double *tre = reinterpret_cast<double *>(smem_raw), *tim = tre + PS;  // output region [RR][RS]
+    const int GS = gram_stride(T, J), GP = RR * GS;
+    float2 *reg = reinterpret_cast<float2 *>(tim + PS);                   // input region [RR][GS]
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    float2 *wuv = reg + GP + wave * 8 * SR;                                           // [8][SR]: row weight times value
+    float *wv = reinterpret_cast<float *>(reg + GP + kGramWaves * 8 * SR) + wave * 16 * SR;  // [16][SR]: column weights
+    const WorkUnit wk = a.order[blockIdx.x];
+    const int v0 = wk.start, total = wk.count;
+    const int lnb = __builtin_ctz(T) - __builtin_ctz(TB), tile = wk.tile >> lnb, band = wk.tile & ((1 << lnb) - 1);
+    const int ta = (tile / tps) * T + band * TB, tb = (tile % tps) * T;
+    if (total == 0) {
+        store_empty<float, J>(a, ta, tb, tid, kThreads);
+        return;
+    }
+    const int e = lane & 31, half = lane >> 5;
+    const int f_begin = (int)(((int64_t)wave * total) / kGramWaves);
+    const int f_end = (int)(((int64_t)(wave + 1) * total) / kGramWaves);
+    uint32_t cv = 0;
+    float rho = 0;
+    auto load = [&](int f) {
+        if (f < f_end) {
+            cv = a.cell[v0 + f];
+            rho = a.frac[2 * (int64_t)(v0 + f) + half];
+        }
+    };
+    load(f_begin + e);
+    // Input region, rows by wavefront; the first kRows rows of a wavefront (all
+    // of them up to 32 x 32 tiles) are in flight while the output region is cleared.
+    constexpr int kRows = 5, kStep = kRows * kGramWaves;
+    const int W = T + J - 1;
+    float2 g[kRows];
+    auto fetch = [&](int i0, int j) {
+        int gj = tb + j;
+        if (gj >= K) gj -= K;
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            int gi = ta + min(i0 + r * kGramWaves, RR - 1);
+            if (gi >= K) gi -= K;
+            g[r] = gin[(int64_t)gi * K + gj];
+        }
+    };
+    auto put = [&](int i0, int j) {
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+            if (i0 + r * kGramWaves < RR) reg[(i0 + r * kGramWaves) * GS + j] = g[r];
+    };
+    fetch(wave, min(lane, W - 1));
+    {
+        double2 *t2 = reinterpret_cast<double2 *>(tre);
+        for (int c = tid; c < PS; c += kThreads) t2[c] = make_double2(0.0, 0.0);
+    }
+    if (lane < W) put(wave, lane);
+    for (int j = lane; j < W; j += 64)
+        for (int i0 = wave + (j == lane ? kStep : 0); i0 < RR; i0 += kStep) {
+            fetch(i0, j);
+            put(i0, j);
+        }
+    // Row-weight rows J .. 7 are never staged and stay zero.
+    for (int i = J * SR + lane; i < 8 * SR; i += 64) wuv[i] = make_float2(0.f, 0.f);
+    __syncthreads();
+
+    typedef float mf4 __attribute__((ext_vector_type(4)));
+    mf4 dacc = {0.f, 0.f, 0.f, 0.f};
+    const int mk_ = lane >> 4, mi = lane & 15;
+    const int abase = 2 * ((mi >> 1) * SR + mk_) + (mi & 1), bbase = mi * SR + mk_, coff = 2 * mk_ * RS + mi;
+    const float *wuf = reinterpret_cast<const float *>(wuv);
+    auto close = [&](int pos) {
+        const int c = (pos >> 8) * RS + ((pos & 255) << 3) + coff;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (2 * mk_ + h < J) {
+                __hip_atomic_fetch_add(tre + c + h * RS, (double)dacc[2 * h], __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                __hip_atomic_fetch_add(tim + c + h * RS, (double)dacc[2 * h + 1], __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        }
+        dacc = mf4{0.f, 0.f, 0.f, 0.f};
+    };
+    int cur = -1;
+    auto group = [&](int g, uint64_t starts, int pos) {
+        const float av = wuf[abase + 8 * g], bv = wv[bbase + 4 * g];
+        const unsigned s4 = (unsigned)(starts >> (4 * g)) & 0xFu;
+        if (__builtin_expect(s4 == 0, 1)) {
+            dacc = mfma_16x16x4(av, bv, dacc);
+        } else {
+            unsigned m = s4;
+            int lo = 0;
+            while (m) {
+                const int b = __builtin_ctz(m);
+                m &= m - 1;
+                if (b > lo) dacc = mfma_16x16x4(av, (mk_ >= lo && mk_ < b) ? bv : 0.f, dacc);
+                if (cur >= 0) close(cur);
+                cur = __builtin_amdgcn_readlane(pos, 4 * g + b);
+                lo = b;
+            }
+            dacc = mfma_16x16x4(av, mk_ >= lo ? bv : 0.f, dacc);
+        }
+    };
+    for (int base = f_begin; base < f_end; base += SL) {
+        const int nlive = min(SL, f_end - base);
+        const bool live = e < nlive;
+        // Lanes past the end take the window at the region's origin, value 0.
+        const int la = live ? (int)(cv & 0xffffu) - ta : 0, lb = live ? (int)(cv >> 16) - tb : 0;
+        const int pos = (live && half == 0) ? (la << 8) | (lb >> 3) : -1, db = lb & 7;
+        float w[J], wr[H], wc[J];  // own axis; own window rows; columns
+        kb_weights_ptr<float, J>(rho, a.kc, w);
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+            wr[j] = w[j];
+            float c0 = w[j + H], c1;
+            swap_halves(wr[j], c0);  // wr: u weights j (lower), j + H (upper); c0: the v weights
+            c1 = c0;
+            swap_halves(c0, c1);
+            wc[j] = c0;
+            wc[j + H] = c1;
+        }
+        float xr = 0, xi = 0;
+        const float2 *win = reg + (la + half * H) * GS + lb;
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            float rr = 0, ri = 0;
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const float2 g = win[i * GS + j];
+                rr += wc[j] * g.x;
+                ri += wc[j] * g.y;
+            }
+            xr += wr[i] * rr;
+            xi += wr[i] * ri;
+        }
+        xr = live ? sum_halves(xr) : 0.f;
+        xi = live ? sum_halves(xi) : 0.f;
+#pragma unroll
+        for (int i = 0; i < H; ++i) wuv[(half * H + i) * SR + e] = make_float2(wr[i] * xr, wr[i] * xi);
+        // Column weights at rows db .. db + J - 1 of the 16-row block, zeros in
+        // the others: each half clears 8 rows, then writes its half of the weights
+        // (one wavefront's LDS writes land in order).
+#pragma unroll
+        for (int r = 0; r < 8; ++r) wv[(half * 8 + r) * SR + e] = 0.f;
+        float *wcol = wv + (db + half * H) * SR + e;
+#pragma unroll
+        for (int j = 0; j < H; ++j) wcol[j * SR] = half ? wc[j + H] : wc[j];
+        const int prev = __builtin_amdgcn_update_dpp(cur, pos, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
+        const uint64_t starts = __ballot(live && half == 0 && pos != prev);
+        __builtin_amdgcn_wave_barrier();
+        load(base + SL + e);  // in flight during the accumulation
+        if (nlive == SL) {
+#pragma unroll
+            for (int g = 0; g < SL / 4; ++g) group(g, starts, pos);
+        } else {
+            const int ng = (nlive + 3) >> 2;
+#pragma unroll 1
+            for (int g = 0; g < ng; ++g) group(g, starts, pos);
+        }
+        __builtin_amdgcn_wave_barrier();  // the next slice's staging overwrites this one
+    }
+    if (cur >= 0) close(cur);
+    __syncthreads();
+    store_region<float, J>(a, tre, tim, ta, tb, tid, kThreads);
+}
+
 // Adds to each band's first J-1 rows and columns what the bands above, to
 // the left and above-left left in their halo cells (periodic in the grid), in
 // that fixed order.  One thread per border cell.  The adjoint FFT's
@@ -1173,23 +1387,28 @@ void check_grid_lds(riop_plan *p) {
     RIOP_REQUIRE(lds <= p->lds_max, RIOP_ENOTSUP, "gridding tile too large for LDS; use a smaller tile");
 }
 
-template <typename R>
-static void launch_tiles(riop_plan *p, const void *vals, int order_user, void *out_grid, hipStream_t st,
-                         const TileArgs<R> *p2 = nullptr, int *flag = nullptr) {
+template <typename R> static TileArgs<R> tile_args(riop_plan *p, void *out_grid) {
     TileArgs<R> a{};
-    a.flag = flag;
     a.grid = static_cast<C<R> *>(out_grid);
     a.halo = p->halo.as<C<R>>();
     a.cell = p->cell.as<uint32_t>();
     a.frac = p->frac.as<R>();
     a.perm = p->perm.as<int>();
     a.order = p->tile_order.as<WorkUnit>();
-    a.vin = static_cast<const C<R> *>(vals);
     a.kc = p->kcoef_compact.as<R>();
     a.K = p->K;
     a.T = p->tile;
     a.TB = p->band;
     a.tps = p->tiles_per_side;
+    return a;
+}
+
+template <typename R>
+static void launch_tiles(riop_plan *p, const void *vals, int order_user, void *out_grid, hipStream_t st,
+                         const TileArgs<R> *p2 = nullptr, int *flag = nullptr) {
+    TileArgs<R> a = tile_args<R>(p, out_grid);
+    a.flag = flag;
+    a.vin = static_cast<const C<R> *>(vals);
     if (p2) {
         RIOP_REQUIRE(!order_user, RIOP_EINVAL, "the fused prox gridding is plan order only");
         a.p2s = p2->p2s;
@@ -1255,12 +1474,31 @@ void launch_grid_prox2(riop_plan *p, const void *s, void *z2, const void *y, con
     launch_tiles<R>(p, nullptr, 0, p->grid.ptr, st, &q);
 }
 
+// The one-launch G^T G, where it applies (false: nothing was done).
+static bool launch_gram_tile(riop_plan *p, const void *in_grid, void *out_grid, hipStream_t st) {
+    if (p->J != 8 && p->J != 6) return false;
+    const size_t lds = p->J == 8 ? gram_tile_lds<8>(p->band, p->tile) : gram_tile_lds<6>(p->band, p->tile);
+    if (lds > p->lds_max) return false;
+    const TileArgs<float> a = tile_args<float>(p, out_grid);
+    TimedScope ts(p, KK_GRAM_FUSED, st);
+    const dim3 g(p->nbands), t(64 * kGramWaves);
+    const float2 *in = static_cast<const float2 *>(in_grid);
+    if (p->J == 8) hipLaunchKernelGGL((gram_tile<8>), g, t, lds, st, a, in);
+    else hipLaunchKernelGGL((gram_tile<6>), g, t, lds, st, a, in);
+    RIOP_HIP(hipGetLastError());
+    p->halo_pending = out_grid;
+    return true;
+}
+
 // out_grid = G^T G in_grid: the precomputed planes when the plan holds them,
-// else degridding into plan-order scratch, then gridding.
+// else the fused kernel, else degridding into plan-order scratch, then gridding.
 template <typename R> void launch_gram(riop_plan *p, const void *in_grid, void *out_grid, hipStream_t st) {
     if (p->gram.ptr) {
         launch_gram_apply<R>(p, in_grid, out_grid, st);
         return;
+    }
+    if constexpr (sizeof(R) == 4) {
+        if (launch_gram_tile(p, in_grid, out_grid, st)) return;
     }
     launch_degrid_from<R>(p, in_grid, p->vis.ptr, 0, st);
     launch_tiles<R>(p, p->vis.ptr, 0, out_grid, st);

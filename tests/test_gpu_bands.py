@@ -58,3 +58,23 @@ def test_bands(prec, n, M, J, kind):
     got, _, _, _ = plan.sdmm(to_dev(w, prec), eps, 2, n_cg=3)
     x, _, _, _ = osdmm.sdmm(w, eps, op, sara, 2, n_cg=3)
     assert rel(host(got), x) <= 10 * TOL[prec]
+
+
+@pytest.mark.parametrize("n,M,J,tile", [(32, 1, 8, 8), (64, 33, 6, 16), (64, 5000, 8, 16), (64, 5000, 8, 64),
+                                        (96, 20000, 6, 64), (128, 60000, 8, 32), (48, 255, 8, 32)])
+def test_fused_gram(n, M, J, tile):
+    """Single-precision Q through the fused kernel at every tile side (64: the two
+    launches it replaces), one visibility, slices with 1 and 31 live entries, a
+    dense corner that wraps the grid's edges."""
+    device()
+    announce(f"fused G^T G n={n} M={M} J={J} tile={tile}")
+    from paper_1307_4370_amd import Plan
+    g = W.rng(321, 1, n * 31 + tile)
+    uv = g.uniform(-math.pi, math.pi, size=(M, 2))
+    uv[M // 2:] = math.pi - 0.02 - 0.1 * g.random((M - M // 2, 2))
+    uv = uv.astype(np.float32).astype(np.float64)
+    x = W.random_complex((n, n), g).astype(np.complex64).astype(np.complex128)
+    op = nufft.Operator(n, uv, J)
+    plan = Plan(n, to_dev(uv, "f32"), J=J, levels=1, prec="f32", tile=tile)
+    got = host(plan.apply_q(to_dev(x, "f32"))) - 2 * x
+    assert rel(got, op.phi_adj(op.phi(x))) <= TOL["f32"]
