@@ -407,17 +407,36 @@ __device__ inline mfma_d4 mfma_16x16x4(double a, double b, mfma_d4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
+// {a.lower, b.lower} and {a.upper, b.upper} (halves of 32 lanes).
+__device__ inline void swap_halves(float &a, float &b) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const u2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+__device__ inline void swap_halves(double &a, double &b) {
+    float al = __int_as_float(__double2loint(a)), ah = __int_as_float(__double2hiint(a));
+    float bl = __int_as_float(__double2loint(b)), bh = __int_as_float(__double2hiint(b));
+    swap_halves(al, bl);
+    swap_halves(ah, bh);
+    a = __hiloint2double(__float_as_int(ah), __float_as_int(al));
+    b = __hiloint2double(__float_as_int(bh), __float_as_int(bl));
+}
+__device__ inline float sum_halves(float a) {
+    float b = a;
+    swap_halves(a, b);
+    return a + b;
+}
+
 // Row length of a wavefront's tap-major staging arrays.  Vector path: odd,
 // so the eight-address broadcast reads fall in distinct banks.  Matrix path:
 // 4 mod 32, so the operand reads (16 rows x 4 entries per instruction) hit 64
 // distinct banks.  Either way the staging stores (consecutive lanes) are
 // conflict-free.
-// Entries per staged slice: 32 on the double-precision matrix path (one lane
-// per entry and axis, which halves the staging area so that two workgroups
-// fit per CU), 64 otherwise (one lane per entry).
-template <typename R> __host__ __device__ constexpr int slice_len(int J) {
-    return grid_mfma<R>(J) && sizeof(R) == 8 ? 32 : 64;
-}
+// Entries per staged slice: 32 on the matrix path (one lane per entry and axis,
+// which halves the staging area so that more wavefronts fit per CU), 64
+// otherwise (one lane per entry).
+template <typename R> __host__ __device__ constexpr int slice_len(int J) { return grid_mfma<R>(J) ? 32 : 64; }
 template <typename R> __host__ __device__ constexpr int slice_row(int J) {
     return grid_mfma<R>(J) ? (slice_len<R>(J) == 32 ? 36 : 68) : 65;
 }
@@ -563,7 +582,15 @@ __device__ inline void store_empty(const TileArgs<R> &a, int ta, int tb, int tid
 // of the region to its halo cells; the adjoint FFT's row pass adds the halos
 // of the three neighbours a band receives from as it loads the grid (or
 // grid_merge does, where that pass is not the specialised one).
-// WAVES: grid_waves<R>(J), or 2 for tiles whose region leaves too little LDS.
+// WAVES: grid_waves<R>(J), 8 where the bands are narrow (single precision, matrix
+// path), or 2 for tiles whose region leaves too little LDS.
+// Bound by the slice loop's staging and operand reads in LDS, and by the latency
+// of the light bands (clear, first slice, store).  Balanced staging (each half
+// of the wavefront half of the rows and columns, where all lanes staged one
+// whole 64-entry slice, or each half one axis in double precision) against that
+// form, J = 8: FP64, 1024^2, M = 4194304, caller order 220 -> 192 us, 256^2,
+// M = 131072 22 -> 20 us; FP32, plan order 90 -> 81 us, 1536^2, M = 2350001,
+// caller order 116 -> 93 us.
 // P2: the values are formed from the l2-ball prox's inputs (see TileArgs), in
 // double precision, at staging (the second pass of the prox of f2, Sec. 4.4).
 template <typename R, int J, bool USER, int WAVES, bool P2>
@@ -605,9 +632,10 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
     }
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, li = lane >> 3, lj = lane & 7;
-    // 32-entry slices: lane = entry + 32 axis stages one axis of one entry
-    // (axis 0: u, with the value; axis 1: v).  64-entry slices: lane = entry,
-    // both axes.
+    // 32-entry slices: lane = entry + 32 axis forms the weights of one axis of
+    // one entry and, after a swap between the halves, stages half of the entry's
+    // window rows and half of its columns.  64-entry slices: lane = entry, both
+    // axes.
     constexpr bool SPLIT = SL == 32;
     const int e = SPLIT ? (lane & 31) : lane, ax = SPLIT ? (lane >> 5) : 0;
     // This wavefront's share of the band's visibilities (band-relative).
@@ -619,6 +647,8 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
     R fu = 0, fv = 0;
     C<R> val = mk<R>(0, 0);
     C<R> ps = mk<R>(0, 0), pz = mk<R>(0, 0), py = mk<R>(0, 0);  // P2 inputs
+    // Caller order: the value's place is loaded one slice before the value.
+    int place = USER && f_begin + e < f_end ? a.perm[v0 + f_begin + e] : 0;
     auto load = [&](int f) {
         if (f < f_end) {
             const int v = v0 + f;
@@ -629,15 +659,16 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
                 fu = a.frac[2 * (int64_t)v];
                 fv = a.frac[2 * (int64_t)v + 1];
             }
-            if (ax == 0) {
-                if constexpr (P2) {
+            if constexpr (P2) {
+                if (ax == 0) {
                     ps = a.p2s[v];
                     pz = a.p2z[v];
                     py = a.p2y[v];
-                } else {
-                    val = a.vin[USER ? (int64_t)a.perm[v] : (int64_t)v];
                 }
+            } else {
+                val = a.vin[USER ? place : v];
             }
+            if (USER && f + SL < f_end) place = a.perm[v + SL];
         }
     };
     const double p2sc = P2 ? *a.p2scale : 1.0;
@@ -731,6 +762,11 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
                 a.p2z[v0 + base + e] = mk<R>((R)znr, (R)zni);
                 val = mk<R>((R)(rr - znr - ps.x), (R)(ri - zni - ps.y));
             }
+            if constexpr (SPLIT) {  // the lower half's value to both halves
+                C<R> upper = val;
+                swap_halves(val.x, upper.x);
+                swap_halves(val.y, upper.y);
+            }
         }
         // Staging.  Lanes past the end stage zero values, so the
         // accumulation below runs over all 64 entries without bound tests.
@@ -740,22 +776,24 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
         const int pos = (live && ax == 0) ? (la << 8) | (lb >> 3) : -1;
         const int db = lb & 7;
         if constexpr (SPLIT) {
-            R w_[J];
-            if constexpr (kScalarCoef) kb_weights_ptr<R, J>(fu, a.kc, w_);
-            else kb_weights_ptr<R, J>(fu, kcl, w_);
-            if (ax == 0) {
+            constexpr int H = J / 2;
+            R w[J], c[H];
+            if constexpr (kScalarCoef) kb_weights_ptr<R, J>(fu, a.kc, w);
+            else kb_weights_ptr<R, J>(fu, kcl, w);
 #pragma unroll
-                for (int i = 0; i < J; ++i) wuv[i * SR + e] = mk<R>(w_[i] * val.x, w_[i] * val.y);
-            } else {
-                // Column weights at rows db .. db + J - 1, zeros in the other
-                // rows: all rows cleared at fixed offsets, then the weights
-                // written over them (one wavefront's LDS writes land in order).
-#pragma unroll
-                for (int r = 0; r < NC; ++r) wv[r * SR + e] = R(0);
-                R *wcol = wv + db * SR + e;
-#pragma unroll
-                for (int j = 0; j < J; ++j) wcol[j * SR] = w_[j];
+            for (int j = 0; j < H; ++j) {
+                c[j] = w[j + H];
+                swap_halves(w[j], c[j]);  // u weights and v weights j (lower half), j + H (upper half)
+                wuv[(ax * H + j) * SR + e] = mk<R>(w[j] * val.x, w[j] * val.y);
             }
+            // Column weights at rows db .. db + J - 1, zeros in the other rows:
+            // each half clears 8 rows at fixed offsets, then its weights are
+            // written over them (one wavefront's LDS writes land in order).
+#pragma unroll
+            for (int r = 0; r < 8; ++r) wv[(ax * 8 + r) * SR + e] = R(0);
+            R *wcol = wv + (db + ax * H) * SR + e;
+#pragma unroll
+            for (int j = 0; j < H; ++j) wcol[j * SR] = c[j];
         } else {
             R wu_[J], wv_[J];
             if constexpr (kScalarCoef) {
@@ -931,19 +969,6 @@ constexpr int kGramWaves = 8;
 __host__ __device__ constexpr int gram_stride(int T, int J) { return (T + J - 1 + 31) / 32 * 32; }
 template <int J> static size_t gram_tile_lds(int TB, int T) {
     return (size_t)region_rows(TB, J) * (region_stride(T, J) * 2 * sizeof(double) + gram_stride(T, J) * sizeof(float2)) + (size_t)kGramWaves * 36 * (8 * sizeof(float2) + 16 * sizeof(float));
-}
-
-// {a.lower, b.lower} and {a.upper, b.upper} (halves of 32 lanes).
-__device__ inline void swap_halves(float &a, float &b) {
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    const u2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    a = __uint_as_float(r[0]);
-    b = __uint_as_float(r[1]);
-}
-__device__ inline float sum_halves(float a) {
-    float b = a;
-    swap_halves(a, b);
-    return a + b;
 }
 
 template <int J> __global__ void __launch_bounds__(64 * kGramWaves, 4) gram_tile(TileArgs<float> a, const float2 *gin) {
@@ -1416,29 +1441,36 @@ static void launch_tiles(riop_plan *p, const void *vals, int order_user, void *o
         a.p2y = p2->p2y;
         a.p2scale = p2->p2scale;
     }
-    int waves = grid_waves<R>(p->J);
+    // Narrow bands are latency-bound: eight wavefronts shorten each band's chain
+    // (256^2, M = 131072, FP32 12.7 -> 10.9 us).  Whole tiles keep six, three
+    // workgroups per CU (1024^2 81 us against 83, 1536^2 93 against 102).
+    const bool eight = sizeof(R) == 4 && grid_mfma<R>(p->J) && p->band < p->tile;
+    int waves = eight ? 8 : grid_waves<R>(p->J);
     if (grid_lds<R>(p->band, p->tile, p->J, waves) > p->lds_max) waves = 2;
     const size_t lds = grid_lds<R>(p->band, p->tile, p->J, waves);
     RIOP_REQUIRE(lds <= p->lds_max, RIOP_ENOTSUP, "gridding tile too large for LDS");
     TimedScope ts(p, p2 ? KK_GRID_PROX2 : KK_GRID, st);
     const dim3 g(p->nbands);
     switch (p->J) {
-#define GK(JJ)                                                                                            \
-    case JJ: {                                                                                            \
-        constexpr int WD = grid_waves<R>(JJ);                                                             \
-        if (waves == WD) {                                                                                \
-            if (p2) hipLaunchKernelGGL((grid_tile<R, JJ, false, WD, true>), g, dim3(64 * WD), lds, st, a);  \
-            else if (order_user) hipLaunchKernelGGL((grid_tile<R, JJ, true, WD, false>), g, dim3(64 * WD), lds, st, a); \
-            else hipLaunchKernelGGL((grid_tile<R, JJ, false, WD, false>), g, dim3(64 * WD), lds, st, a);    \
-        } else {                                                                                          \
-            if (p2) hipLaunchKernelGGL((grid_tile<R, JJ, false, 2, true>), g, dim3(128), lds, st, a);        \
-            else if (order_user) hipLaunchKernelGGL((grid_tile<R, JJ, true, 2, false>), g, dim3(128), lds, st, a); \
-            else hipLaunchKernelGGL((grid_tile<R, JJ, false, 2, false>), g, dim3(128), lds, st, a);          \
-        }                                                                                                 \
-        break;                                                                                            \
+#define GK_LAUNCH(JJ, W)                                                                                \
+    do {                                                                                                \
+        const dim3 t(64 * (W));                                                                         \
+        if (p2) hipLaunchKernelGGL((grid_tile<R, JJ, false, W, true>), g, t, lds, st, a);               \
+        else if (order_user) hipLaunchKernelGGL((grid_tile<R, JJ, true, W, false>), g, t, lds, st, a);  \
+        else hipLaunchKernelGGL((grid_tile<R, JJ, false, W, false>), g, t, lds, st, a);                 \
+    } while (0)
+#define GK(JJ)                                                            \
+    case JJ: {                                                            \
+        constexpr int WD = grid_waves<R>(JJ);                             \
+        constexpr int W8 = sizeof(R) == 4 && grid_mfma<R>(JJ) ? 8 : WD;   \
+        if (waves == W8) GK_LAUNCH(JJ, W8);                               \
+        else if (waves == WD) GK_LAUNCH(JJ, WD);                          \
+        else GK_LAUNCH(JJ, 2);                                            \
+        break;                                                            \
     }
         RIOP_J_CASES(GK)
 #undef GK
+#undef GK_LAUNCH
         default: throw Error{RIOP_ENOTSUP, "unsupported kernel width"};
     }
     RIOP_HIP(hipGetLastError());
