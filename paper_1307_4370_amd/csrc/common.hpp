@@ -166,10 +166,11 @@ struct SdmmWork {
     DevBuf blk, beps, bscale, bnu, bpart, bflag;
     // Prior of the l1 step: 0 = analysis l1 over the SARA dictionary (L1 =
     // Psi^dagger), 1 = weighted TV (L1 = I, prox by fast gradient projection
-    // on the dual with tv_inner iterations; buffers N complex each).
+    // on the dual with tv_inner iterations; tvb N complex, the point the prox
+    // is taken at, tvd two sets of the four dual images, read and written in turn).
     int prior = 0;
     int tv_inner = 0;
-    DevBuf tvb, tvu, tvp, tvq, tvr, tvs;
+    DevBuf tvb, tvd[2];
     DevBuf rw_w;            // reweighted l1: the current weights (q*N reals)
     DevBuf xprev;           // reweighted l1: the previous pass's solution (N complex)
     DevBuf history;         // doubles, kHistStride per iteration

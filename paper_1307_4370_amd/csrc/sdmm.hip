@@ -499,87 +499,121 @@ __global__ void gather_blocks(const int *block_of, const int *perm, long M, int 
 
 enum Prior { PRIOR_SARA = 0, PRIOR_TV = 1 };
 
-template <typename R> __device__ inline C<R> grad_adj_at(const C<R> *p, const C<R> *q, int i, int j, int n) {
-    const long k = (long)i * n + j;
-    C<R> v = mk<R>(0, 0);
-    if (i >= 1) v = cadd<R>(v, p[k - n]);
-    if (i < n - 1) v = csub<R>(v, p[k]);
-    if (j >= 1) v = cadd<R>(v, q[k - 1]);
-    if (j < n - 1) v = csub<R>(v, q[k]);
-    return v;
-}
+// The dual iterations, `it` of them per launch on a tile with a border of `it`
+// pixels that is computed along and not stored: an iteration reads its
+// neighbours to the left and above (gradT) and to the right and below (grad), so
+// each one costs a pixel of border on every side.  One thread per pixel; b, the
+// duals p, q and their extrapolations r, s stay in registers, and r, s and u pass
+// through LDS.  Bound by launches and latency on small images, by the border's
+// work on large ones (7 iterations store 18 x 18 of 32 x 32 pixels).  20
+// iterations, FP32, against one launch for u and one for the dual step of each
+// (13 images read or written per iteration): 256^2 125 -> 29 us, 512^2
+// 195 -> 62 us, 1024^2 612 -> 145 us.
+//   u = b - lam gradT(r, s);
+//   (p, q) <- projection onto |(p, q)_ij| <= w_ij of (r, s) + grad(u) / (8 lam);
+//   (r, s) <- (p, q) + c ((p, q) - (p, q)_previous).
+// The first launch forms b = xhat + z1 (the point the prox is taken at) and
+// starts the dual at zero; the last one (Algorithm 1 steps 7-9, L1 = I) sets
+// r1 = b - lam gradT(p, q), z1 <- b - r1, x1 = r1 - z1.  No launch is both: the
+// first reads z1 in its border, the last overwrites it.
+constexpr int kTvTile = 32;   // threads of a tile side (1024 per block)
+constexpr int kTvIters = 7;   // iterations per launch at most
+// Iterations per launch: 4 / 5 / 7 / 10 took 35 / 32 / 29 / 38 us at 256^2,
+// 58 / 62 / 61 / 102 at 512^2 and 145 / 145 / 169 / 346 at 1024^2 (FP32), 82 / 81 /
+// 88 / 157 at 512^2 in double precision.
+static int tv_iters(int n) { return n <= 384 ? 7 : 5; }
 
-// b = xhat + z1 (the point the prox is taken at); the dual starts at zero.
-template <typename R>
-__global__ void tv_begin(const C<R> *xh, const C<R> *z1, C<R> *b, C<R> *p, C<R> *q, C<R> *r, C<R> *s, long N) {
-    GRID_LOOP(i, N) {
-        b[i] = cadd<R>(xh[i], z1[i]);
-        const C<R> z = mk<R>(0, 0);
-        p[i] = z;
-        q[i] = z;
-        r[i] = z;
-        s[i] = z;
+template <typename R> struct TvArgs {
+    const C<R> *xh, *z1_in;  // first launch
+    C<R> *b;
+    const C<R> *in;          // p, q, r, s (N each), read unless first
+    C<R> *out;               // written unless last
+    C<R> *z1, *x1;           // last launch
+    const R *w;              // weights, nullable (1)
+    const double *lam;
+    int n, it, first, last;
+    double c[kTvIters];
+};
+
+template <typename R> __global__ void __launch_bounds__(kTvTile * kTvTile) tv_tile(TvArgs<R> a) {
+    constexpr int S = kTvTile;
+    __shared__ C<R> sr[S][S + 1], ss[S][S + 1], su[S][S + 1];
+    const int n = a.n, lo = a.it + a.last, own = S - lo - a.it, tiles = (n + own - 1) / own;
+    const int ty = threadIdx.x / S, tx = threadIdx.x % S;
+    const int i = (int)(blockIdx.x / tiles) * own - lo + ty, j = (int)(blockIdx.x % tiles) * own - lo + tx;
+    const bool inside = i >= 0 && i < n && j >= 0 && j < n;
+    const bool mine = inside && ty >= lo && ty < lo + own && tx >= lo && tx < lo + own;
+    const long N = (long)n * n, k = inside ? (long)i * n + j : 0;
+    const double lamd = *a.lam;
+    const R lam = (R)lamd, step = lamd > 0 ? (R)(1.0 / (8.0 * lamd)) : R(0);
+    const C<R> zero = mk<R>(0, 0);
+    C<R> b = zero, p = zero, q = zero, r = zero, s = zero;
+    R w = R(1);
+    if (inside) {
+        if (a.first) {
+            b = cadd<R>(a.xh[k], a.z1_in[k]);
+        } else {
+            b = a.b[k];
+            p = a.in[k];
+            q = a.in[N + k];
+            r = a.in[2 * N + k];
+            s = a.in[3 * N + k];
+        }
+        if (a.w) w = a.w[k];
     }
-}
-
-// u = b - lam gradT(r, s)
-template <typename R> __global__ void tv_u(const C<R> *b, const C<R> *r, const C<R> *s, C<R> *u, int n,
-                                           const double *lamp) {
-    const R lam = (R)*lamp;
-    GRID_LOOP(k, (long)n * n) {
-        const int i = (int)(k / n), j = (int)(k - (long)i * n);
-        const C<R> g = grad_adj_at<R>(r, s, i, j, n);
-        u[k] = mk<R>(b[k].x - lam * g.x, b[k].y - lam * g.y);
-    }
-}
-
-// (p, q) <- projection onto |(p, q)_ij| <= w_ij of (r, s) + grad(u) / (8 lam);
-// (r, s) <- (p, q) + c ((p, q) - (p, q)_previous).
-template <typename R>
-__global__ void tv_dual(const C<R> *u, const R *w, C<R> *p, C<R> *q, C<R> *r, C<R> *s, int n, const double *lamp,
-                        double c) {
-    const double lam = *lamp;
-    const R step = lam > 0 ? (R)(1.0 / (8.0 * lam)) : R(0);
-    const R cc = (R)c;
-    GRID_LOOP(k, (long)n * n) {
-        const int i = (int)(k / n), j = (int)(k - (long)i * n);
-        const C<R> uk = u[k];
-        const C<R> gx = i < n - 1 ? csub<R>(u[k + n], uk) : mk<R>(0, 0);
-        const C<R> gy = j < n - 1 ? csub<R>(u[k + 1], uk) : mk<R>(0, 0);
-        C<R> pn = mk<R>(r[k].x + step * gx.x, r[k].y + step * gx.y);
-        C<R> qn = mk<R>(s[k].x + step * gy.x, s[k].y + step * gy.y);
-        const R wk = w ? w[k] : R(1);
-        if (wk > R(0)) {
+    // gradT of the images in sr, ss (minus the divergence).
+    auto grad_adj = [&] {
+        C<R> v = zero;
+        if (i >= 1) v = cadd<R>(v, sr[max(ty - 1, 0)][tx]);
+        if (i < n - 1) v = csub<R>(v, sr[ty][tx]);
+        if (j >= 1) v = cadd<R>(v, ss[ty][max(tx - 1, 0)]);
+        if (j < n - 1) v = csub<R>(v, ss[ty][tx]);
+        return v;
+    };
+    for (int t = 0; t < a.it; ++t) {
+        sr[ty][tx] = r;
+        ss[ty][tx] = s;
+        __syncthreads();
+        const C<R> g = grad_adj(), u = mk<R>(b.x - lam * g.x, b.y - lam * g.y);
+        su[ty][tx] = u;
+        __syncthreads();
+        const C<R> gx = i < n - 1 ? csub<R>(su[min(ty + 1, S - 1)][tx], u) : zero;
+        const C<R> gy = j < n - 1 ? csub<R>(su[ty][min(tx + 1, S - 1)], u) : zero;
+        C<R> pn = mk<R>(r.x + step * gx.x, r.y + step * gx.y);
+        C<R> qn = mk<R>(s.x + step * gy.x, s.y + step * gy.y);
+        if (w > R(0)) {
             const R mag = sqrt(pn.x * pn.x + pn.y * pn.y + qn.x * qn.x + qn.y * qn.y);
-            if (mag > wk) {
-                const R f = wk / mag;
+            if (mag > w) {
+                const R f = w / mag;
                 pn = cscale<R>(pn, f);
                 qn = cscale<R>(qn, f);
             }
         } else {
-            pn = mk<R>(0, 0);
-            qn = mk<R>(0, 0);
+            pn = zero;
+            qn = zero;
         }
-        const C<R> po = p[k], qo = q[k];
-        r[k] = mk<R>(pn.x + cc * (pn.x - po.x), pn.y + cc * (pn.y - po.y));
-        s[k] = mk<R>(qn.x + cc * (qn.x - qo.x), qn.y + cc * (qn.y - qo.y));
-        p[k] = pn;
-        q[k] = qn;
+        const R cc = (R)a.c[t];
+        r = mk<R>(pn.x + cc * (pn.x - p.x), pn.y + cc * (pn.y - p.y));
+        s = mk<R>(qn.x + cc * (qn.x - q.x), qn.y + cc * (qn.y - q.y));
+        p = pn;
+        q = qn;
     }
-}
-
-// r1 = b - lam gradT(p, q); z1 <- b - r1; x1 = r1 - z1 (Algorithm 1 steps 7-9, L1 = I).
-template <typename R>
-__global__ void tv_finish(const C<R> *b, const C<R> *p, const C<R> *q, C<R> *z1, C<R> *x1, int n, const double *lamp) {
-    const R lam = (R)*lamp;
-    GRID_LOOP(k, (long)n * n) {
-        const int i = (int)(k / n), j = (int)(k - (long)i * n);
-        const C<R> g = grad_adj_at<R>(p, q, i, j, n);
-        const C<R> bk = b[k];
-        const C<R> r1 = mk<R>(bk.x - lam * g.x, bk.y - lam * g.y);
-        const C<R> zn = csub<R>(bk, r1);
-        z1[k] = zn;
-        x1[k] = csub<R>(r1, zn);
+    if (a.last) {
+        __syncthreads();
+        sr[ty][tx] = p;
+        ss[ty][tx] = q;
+        __syncthreads();
+        if (mine) {
+            const C<R> g = grad_adj(), r1 = mk<R>(b.x - lam * g.x, b.y - lam * g.y), zn = csub<R>(b, r1);
+            a.z1[k] = zn;
+            a.x1[k] = csub<R>(r1, zn);
+        }
+    } else if (mine) {
+        if (a.first) a.b[k] = b;
+        a.out[k] = p;
+        a.out[N + k] = q;
+        a.out[2 * N + k] = r;
+        a.out[3 * N + k] = s;
     }
 }
 
@@ -810,7 +844,8 @@ static void sdmm_init(riop_plan *p, const void *y, double eps, const riop_sdmm_p
     // Length of the l1 term's variables: q N coefficients (SARA) or N pixels (TV).
     const long D = prior == PRIOR_TV ? N : (long)p->q * N;
     if (prior == PRIOR_TV) {
-        for (DevBuf *b : {&w.tvb, &w.tvu, &w.tvp, &w.tvq, &w.tvr, &w.tvs}) b->reserve(cbytes(p) * (size_t)N);
+        w.tvb.reserve(cbytes(p) * (size_t)N);
+        for (DevBuf &b : w.tvd) b.reserve(4 * cbytes(p) * (size_t)N);
     }
     if (w.prior != prior || w.tv_inner != tv_inner) ++w.epoch;
     w.prior = prior;
@@ -915,25 +950,34 @@ template <typename R> static void sdmm_step(riop_plan *p, int iters, hipStream_t
         if (w.prior == PRIOR_TV) {
             // Steps 7-9, i = 1 with L1 = I: r1 = prox of gamma ||W grad .||_1 at
             // xhat + z1 by fast gradient projection on the dual; x1 = r1 - z1.
-            const long N = (long)p->n * p->n;
             const int n = p->n;
             const R *tw = static_cast<const R *>(w.weights);
-            VEC_LAUNCH(p, tv_begin<R>, RB(), RT(), 0, s, (const C<R> *)xh, (const C<R> *)w.z1loc.as<C<R>>(),
-                       w.tvb.as<C<R>>(), w.tvp.as<C<R>>(), w.tvq.as<C<R>>(), w.tvr.as<C<R>>(), w.tvs.as<C<R>>(), N);
+            TvArgs<R> tv{};
+            tv.xh = xh;
+            tv.z1_in = tv.z1 = w.z1loc.as<C<R>>();
+            tv.x1 = w.x1.as<C<R>>();
+            tv.b = w.tvb.as<C<R>>();
+            tv.w = tw;
+            tv.lam = sc + SC_GAMMA;
+            tv.n = n;
+            // The iterations spread evenly over the launches, at least two.
+            const int per = tv_iters(n), launches = std::max(2, (w.tv_inner + per - 1) / per);
             double tk = 1.0;
-            for (int k = 0; k < w.tv_inner; ++k) {
-                const double tn = (1.0 + std::sqrt(1.0 + 4.0 * tk * tk)) / 2.0;
-                VEC_LAUNCH(p, tv_u<R>, RB(), RT(), 0, s, (const C<R> *)w.tvb.as<C<R>>(),
-                           (const C<R> *)w.tvr.as<C<R>>(), (const C<R> *)w.tvs.as<C<R>>(), w.tvu.as<C<R>>(), n,
-                           (const double *)(sc + SC_GAMMA));
-                VEC_LAUNCH(p, tv_dual<R>, RB(), RT(), 0, s, (const C<R> *)w.tvu.as<C<R>>(), tw, w.tvp.as<C<R>>(),
-                           w.tvq.as<C<R>>(), w.tvr.as<C<R>>(), w.tvs.as<C<R>>(), n, (const double *)(sc + SC_GAMMA),
-                           (tk - 1.0) / tn);
-                tk = tn;
+            for (int l = 0, done = 0; l < launches; ++l) {
+                tv.it = (w.tv_inner - done + launches - l - 1) / (launches - l);
+                done += tv.it;
+                tv.first = l == 0;
+                tv.last = l == launches - 1;
+                tv.in = w.tvd[l & 1].as<C<R>>();
+                tv.out = w.tvd[1 - (l & 1)].as<C<R>>();
+                for (int k = 0; k < tv.it; ++k) {
+                    const double tn = (1.0 + std::sqrt(1.0 + 4.0 * tk * tk)) / 2.0;
+                    tv.c[k] = (tk - 1.0) / tn;
+                    tk = tn;
+                }
+                const int own = kTvTile - 2 * tv.it - tv.last, tiles = (n + own - 1) / own;
+                VEC_LAUNCH(p, tv_tile<R>, dim3((unsigned)(tiles * tiles)), dim3(kTvTile * kTvTile), 0, s, tv);
             }
-            VEC_LAUNCH(p, tv_finish<R>, RB(), RT(), 0, s, (const C<R> *)w.tvb.as<C<R>>(),
-                       (const C<R> *)w.tvp.as<C<R>>(), (const C<R> *)w.tvq.as<C<R>>(), w.z1loc.as<C<R>>(),
-                       w.x1.as<C<R>>(), n, (const double *)(sc + SC_GAMMA));
             VEC_LAUNCH(p, tv_norm_partials<R>, RB(), RT(), 0, s, (const C<R> *)xh, tw, n, part);
         } else {
             // Steps 7-9, i = 1: soft threshold fused into Psi^dagger; x1 = Psi (r1 - z1).
