@@ -956,13 +956,15 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
 // stages its rows' weights times the value and its half of the column block.
 // The 4.6 KB of staging per wavefront (8.7 KB with 64-entry slices) and the
 // single-precision input region leave room for two workgroups of eight
-// wavefronts per CU (81.8 of 160 KB each at 32 x 32); four, five and six
-// wavefronts measured 148, 148 and 141 us, 16-row bands 141 us.
-// Bound by LDS (window reads, 512 B per visibility, and the run closes: 83 of
-// 124 us busy) and the vector unit (62 us busy) together.
-// J = 8, degridding + gridding -> here: 1024^2, M = 4194304, 54 + 86 -> 124 us;
-// 512^2, M = 700001, 15 + 24 -> 33 us; 1536^2, M = 2350001, 52 + 101 -> 141 us;
-// 256^2, M = 131072, 7.5 + 11.6 -> 14.8 us.
+// wavefronts per CU (81.8 of 160 KB each at 32 x 32): 119 us at 1024^2,
+// M = 4194304, against 132 with six and 167 with ten (one workgroup per CU).
+// Bound by LDS (window reads, 512 B per visibility, and the run closes) and the
+// vector unit together.
+// J = 8, degridding + gridding -> here: 1024^2, M = 4194304, 54 + 86 -> 117 us;
+// 512^2, M = 700001, 15 + 24 -> 31 us; 1536^2, M = 2350001, 52 + 101 -> 130 us;
+// 256^2, M = 131072, 7.5 + 11.6 -> 14 us.  In double precision (twice the staging and
+// region, 129 registers) the same kernel takes 29, 70, 351 us at 256^2, 512^2,
+// 1024^2 against 31, 72, 294 us in two launches; those stay two.
 constexpr int kGramWaves = 8;
 // Row length of the input region: a multiple of 32 cells, so that a row's cells
 // continue in the banks where the row before ends, as plan order does.
@@ -1107,8 +1109,11 @@ template <int J> __global__ void __launch_bounds__(64 * kGramWaves, 4) gram_tile
             xr += wr[i] * rr;
             xi += wr[i] * ri;
         }
-        xr = live ? sum_halves(xr) : 0.f;
-        xi = live ? sum_halves(xi) : 0.f;
+        // Unconditional: under `live` the compiler sinks each sum into a branch of
+        // its own, with 4-byte window reads for each part (123 against 117 us).
+        xr = sum_halves(xr);
+        xi = sum_halves(xi);
+        if (!live) xr = xi = 0.f;
 #pragma unroll
         for (int i = 0; i < H; ++i) wuv[(half * H + i) * SR + e] = make_float2(wr[i] * xr, wr[i] * xi);
         // Column weights at rows db .. db + J - 1 of the 16-row block, zeros in
