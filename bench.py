@@ -53,23 +53,26 @@ def source_hash(path=GRID_SOURCE):
     return hashlib.sha256(open(path, "rb").read()).hexdigest()[:16]
 
 
-def recorded_traffic():
-    """HBM bytes per FP32 gridding launch from the committed counter summary, or None
-    when the summary is missing or was taken on a different gridding source."""
+TRAFFIC_LINES = {"grid": "HBM bytes per gridding launch", "gram_fused": "HBM bytes per fused G^T G launch"}
+
+
+def recorded_traffic(kind):
+    """HBM bytes per FP32 launch of `kind` from the committed counter summary, or None
+    when it holds none or was taken on a different gridding source."""
     import re
     try:
         text = open(TRAFFIC_FILE).read()
     except OSError:
         return None
     h = re.search(r"gridding source sha256/16: `([0-9a-f]+)`", text)
-    b = re.search(r"HBM bytes per gridding launch: `([0-9.e+]+)`", text)
+    b = re.search(re.escape(TRAFFIC_LINES[kind]) + r": `([0-9.e+]+)`", text) if kind in TRAFFIC_LINES else None
     if not h or not b or h.group(1) != source_hash():
         return None
     return float(b.group(1))
 
 
 def traffic_summary(fetch_dir, write_dir, probe_mib):
-    """Write the HBM-traffic summary of the FP32 gridding launch from two rocprofv3
+    """Write the HBM-traffic summary of the FP32 gridding launches from two rocprofv3
     --pmc runs (FETCH_SIZE, then WRITE_SIZE), each calibrated on a plain device copy
     of probe_mib MiB (the largest __amd_rocclr_copyBuffer dispatch of the run)."""
     import csv, glob, collections
@@ -95,13 +98,16 @@ def traffic_summary(fetch_dir, write_dir, probe_mib):
         cal = probe / max(copies) if copies else 1.0
         tile = [v for n, v in rows if "grid_tile<float, 8, false" in n and ", true>(" not in n]
         merge = [v for n, v in rows if "grid_merge<float>" in n]
+        fused = [v for n, v in rows if "gram_tile<8" in n]
         t = sum(tile) / len(tile) if tile else 0.0
+        f = sum(fused) / len(fused) if fused else 0.0
         m = sum(merge) / len(merge) if merge else 0.0
-        out[counter] = dict(cal=cal, tile=t * cal, merge=m * cal, n_tile=len(tile), n_merge=len(merge),
+        out[counter] = dict(cal=cal, tile=t * cal, merge=m * cal, fused=f * cal, n_tile=len(tile), n_merge=len(merge),
+                            n_fused=len(fused),
                             probe_raw=max(copies) if copies else 0.0)
     total = sum(out[c]["tile"] + out[c]["merge"] for c in out)
-    lines = ["# HBM traffic of the FP32 gridding launch, 1024^2, M = 4194304, J = 8 (grid_tile; grid_merge only where the "
-             "adjoint FFT does not add the halos itself)\n",
+    lines = ["# HBM traffic of the FP32 gridding launches, 1024^2, M = 4194304, J = 8 (grid_tile; grid_merge only where the "
+             "adjoint FFT does not add the halos itself; gram_tile, the fused G^T G)\n",
              "Commands (repository root on the MI355X host, one counter pass each; $OUT is any writable folder):\n", "```",
              "cd /tmp && export TMPDIR=/tmp",
              f"timeout -s KILL 150 rocprofv3 --pmc FETCH_SIZE --output-format csv -d $OUT/pmc_fetch -o t -- "
@@ -112,14 +118,16 @@ def traffic_summary(fetch_dir, write_dir, probe_mib):
              f"--copy-probe {probe_mib}", "```\n",
              f"Calibration: a plain {probe_mib} MiB device copy; its counter reading is scaled to exactly "
              f"{probe_mib} MiB read and written.\n",
-             "| counter | copy-probe reading (bytes) | factor | grid_tile per launch (bytes) | grid_merge per launch (bytes) | launches |",
-             "|---|---:|---:|---:|---:|---:|"]
+             "| counter | copy-probe reading (bytes) | factor | grid_tile per launch (bytes) | grid_merge per launch (bytes) | gram_tile per launch (bytes) | launches |",
+             "|---|---:|---:|---:|---:|---:|---:|"]
     for c in out:
         o = out[c]
         lines.append(f"| {c} | {o['probe_raw']:.4g} | {o['cal']:.4f} | {o['tile']:.4g} | {o['merge']:.4g} | "
-                     f"{o['n_tile']}/{o['n_merge']} |")
-    lines += ["", f"HBM bytes per gridding launch: `{total:.6g}`", "",
+                     f"{o['fused']:.4g} | {o['n_tile']}/{o['n_merge']}/{o['n_fused']} |")
+    lines += ["", f"{TRAFFIC_LINES['grid']}: `{total:.6g}`", "",
               f"Algorithmic bytes per launch (32N + 16M, FP32): {algorithmic_bytes('grid', 1024, 4194304, 8):.6g}", "",
+              f"{TRAFFIC_LINES['gram_fused']}: `{sum(out[c]['fused'] for c in out):.6g}`", "",
+              f"Algorithmic bytes per launch (64N + 8M, FP32): {algorithmic_bytes('gram_fused', 1024, 4194304, 8):.6g}", "",
               f"gridding source sha256/16: `{source_hash()}`", ""]
     open(TRAFFIC_FILE, "w").write("\n".join(lines))
     print("\n".join(lines))
@@ -585,7 +593,7 @@ def main():
     tot_ms, launches = kernels[dom]
     avg_s = tot_ms * 1e-3 / max(1, launches)
     ach = algorithmic_bytes(dom, n, M, cb) / avg_s / 1e9
-    traffic = recorded_traffic() if dom == "grid" else None
+    traffic = recorded_traffic(dom)
     roofline = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel": dom,
                 "avg_launch_us": round(avg_s * 1e6, 2)}
