@@ -214,7 +214,7 @@ struct riop_plan {
     riop::DevBuf halo;        // per band: region cells outside it (gridding)
     void *halo_pending = nullptr;  // grid last written by gridding, its bands' halos not yet added
     int nunits = 0;
-    int max_unit = 0;
+    int degrid_parts = 0;     // degridding: blocks per work unit, each for part of it (0: one for the whole)
 
     // Kaiser-Bessel kernel: per tap pair even/odd polynomial coefficients.
     double kb_beta = 0;

@@ -33,6 +33,7 @@
 // the even and odd parts E(s^2), O(s^2): w_j = E + s O, w_{J-1-j} = E - s O.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "common.hpp"
 
@@ -318,15 +319,20 @@ __device__ inline void degrid_one(const GridArgs<R> &a, const R *kc, const C<R> 
 // Each thread handles a fixed number PT of visibilities, each in its own guarded
 // block: a rolled loop gets rotated so that all J*J window loads of the next
 // visibility stay live across the back edge, which halves occupancy.
-// PT = kPerThread: one block per work unit.  PT = 1: kPerThread blocks per unit
-// (blockIdx.y), each staging the region again (see degrid_split).
+// PT = kPerThread: one block per work unit.  PT = 1: a block per kDegridThreads
+// of a unit's visibilities (blockIdx.y), each staging the region again (see
+// degrid_parts).
 //
 // Bound by the vector unit on large plans (2 J^2 FMAs and 2 J weights per
-// visibility), by latency on small ones, so every load that can be is issued
-// before the first wait: the visibilities' cells and offsets, then
-// kStageRows region rows per wavefront at once (one row at a time before).
-// J = 8, FP32: M = 4194304 at 1024^2 51.3 -> 50.0 us (caller order, cold
-// caches 135 -> 104 us), M = 131072 at 256^2 11.8 -> 7.0 us; FP64 there 16.9 -> 9.9 us.
+// visibility), by latency on small ones, so the loads that can be are issued
+// before the first wait: the visibilities' cells and offsets (PT = 1, or FP32 in
+// caller order), then up to kStageRows region rows per wavefront at once.
+// With PT = kPerThread the preload pays only where the scattered stores dominate
+// (J = 8, M = 4194304 at 1024^2, cold caches, FP32: caller order 133 -> 119 us, plan
+// order 57 -> 61), and its registers do not in FP64.
+// J = 8, one row of loads and no preload before -> now, cold: 1024^2,
+// M = 4194304 FP32 plan order 68 -> 57 us, caller order 143 -> 119, FP64 129 -> 102
+// and 218 -> 160 (there PT = 1); 256^2, M = 131072 warm 11.8 -> 7.0, FP64 16.9 -> 9.5.
 template <typename R, int J, bool USER, int PT>
 __global__ void __launch_bounds__(kDegridThreads) degrid_kernel(GridArgs<R> a) {
     extern __shared__ unsigned char smem_raw[];
@@ -335,41 +341,60 @@ __global__ void __launch_bounds__(kDegridThreads) degrid_kernel(GridArgs<R> a) {
     const int W = a.T + J - 1;
     const int ta = (wu.tile / a.tps) * a.T, tb = (wu.tile % a.tps) * a.T;
     const int K = a.K;
-    // The thread's visibilities (cell, offsets, destination) are loaded first:
-    // their latency then overlaps the region's.
     const int begin = wu.start + blockIdx.y * PT * kDegridThreads, end = wu.start + wu.count;
     if (begin >= end) return;
+    // With PRE the thread's visibilities (cell, offsets, destination) are loaded
+    // first: their latency then overlaps the region's.
+    constexpr bool PRE = PT == 1 || (USER && sizeof(R) == 4);
     uint32_t cv[PT];
     C<R> rho[PT];
     int dst[PT];
+    auto load = [&](int k, int v) {
+        cv[k] = a.cell[v];
+        rho[k] = reinterpret_cast<const C<R> *>(a.frac)[v];
+        dst[k] = USER ? a.perm[v] : v;
+    };
+    if constexpr (PRE) {
 #pragma unroll
-    for (int k = 0; k < PT; ++k) {
-        const int v = begin + threadIdx.x + k * kDegridThreads;
-        if (v < end) {
-            cv[k] = a.cell[v];
-            rho[k] = reinterpret_cast<const C<R> *>(a.frac)[v];
-            dst[k] = USER ? a.perm[v] : v;
+        for (int k = 0; k < PT; ++k) {
+            const int v = begin + threadIdx.x + k * kDegridThreads;
+            if (v < end) load(k, v);
         }
     }
     // Region rows by wavefront (a wave-uniform row and row address), columns
-    // by lane (no divisions); kStageRows rows' loads in flight per wavefront.
+    // by lane (no divisions), in batches of 2, 5 or 10 rows per wavefront whose
+    // loads are all in flight: the smallest batch that holds the rows left, so
+    // that few loads fetch a clamped row (always the largest: 3 % slower at
+    // T = 32, 10 % at T = 8).  Branches around single loads would make each wait
+    // for the one before (cold, caller order: 116 -> 139 us), and the choice of a
+    // batch makes the preloads of kPerThread visibilities wait (116 -> 122): they
+    // keep the largest.
     constexpr int kStageRows = 5 * (sizeof(R) == 4 ? 2 : 1), kWaves = kDegridThreads >> 6;
     for (int j = threadIdx.x & 63; j < W; j += 64) {
         int gj = tb + j;
         if (gj >= K) gj -= K;
-        for (int i0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); i0 < W; i0 += kStageRows * kWaves) {
-            C<R> g[kStageRows];
+        auto rows = [&](int i0, auto count) {
+            constexpr int N = decltype(count)::value;
+            typedef R Pair __attribute__((ext_vector_type(2)));  // an array of C<double> goes to scratch here
+            Pair g[N];
 #pragma unroll
-            for (int r = 0; r < kStageRows; ++r) {
+            for (int r = 0; r < N; ++r) {
                 int gi = ta + min(i0 + r * kWaves, W - 1);
                 if (gi >= K) gi -= K;
-                g[r] = a.grid[(int64_t)gi * K + gj];
+                g[r] = reinterpret_cast<const Pair *>(a.grid)[(int64_t)gi * K + gj];
             }
 #pragma unroll
-            for (int r = 0; r < kStageRows; ++r) {
+            for (int r = 0; r < N; ++r) {
                 const int i = i0 + r * kWaves;
-                if (i < W) reg[i * W + j] = g[r];
+                if (i < W) reinterpret_cast<Pair *>(reg)[i * W + j] = g[r];
             }
+        };
+        for (int i0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); i0 < W; i0 += kStageRows * kWaves) {
+            const int left = (W - i0 + kWaves - 1) / kWaves;
+            if (PRE && PT > 1) rows(i0, std::integral_constant<int, kStageRows>{});
+            else if (left <= 2) rows(i0, std::integral_constant<int, 2>{});
+            else if (left <= 5 || kStageRows == 5) rows(i0, std::integral_constant<int, 5>{});
+            else rows(i0, std::integral_constant<int, kStageRows>{});
         }
     }
     // Single precision: the coefficient table (32 values at J = 8) in
@@ -386,7 +411,10 @@ __global__ void __launch_bounds__(kDegridThreads) degrid_kernel(GridArgs<R> a) {
 #pragma unroll
     for (int k = 0; k < PT; ++k) {
         const int v = begin + threadIdx.x + k * kDegridThreads;
-        if (v < end) degrid_one<R, J>(a, kc, reg, W, ta, tb, cv[k], rho[k], dst[k]);
+        if (v < end) {
+            if constexpr (!PRE) load(k, v);
+            degrid_one<R, J>(a, kc, reg, W, ta, tb, cv[k], rho[k], dst[k]);
+        }
     }
 }
 
@@ -1233,6 +1261,25 @@ template <typename R> static int choose_band(const std::vector<int> &fine, int T
     return best;
 }
 
+// Blocks per work unit of the degridding (PT = 1), or 0 for one block per unit
+// (PT = kPerThread).  `parts`: the blocks that have work if every unit is
+// spread; `largest`: the largest unit.  Spreading shortens each block's chain
+// and costs a staging of the region per further block, W^2 cells against M J^2
+// taps in all, and block slots for parts that are empty or nearly so.  Units of
+// at most kDegridThreads need one block in either form.  So it is done where the
+// restaged cells are few and the units too few to fill the GPU (or, in double
+// precision, whose blocks hold more registers, the parts well filled).
+// Spread / whole, cold us: 256^2, M = 131072 FP32 8.4 / 13.2 (300 units); 1024^2,
+// M = 4194304 (6900 units) FP32 68 / 57, FP64 102 / 117; tiles of 64,
+// M = 1048576 FP32 49 / 36, FP64 120 / 78 (restaged 0.23 of the taps).
+template <typename R>
+static int degrid_parts(int64_t nunits, int64_t parts, int largest, int T, int J, int64_t M) {
+    const int most = (largest + kDegridThreads - 1) / kDegridThreads;
+    const double W = T + J - 1, restaged = (double)(parts - nunits) * W * W, taps = (double)M * J * J;
+    const bool filled = sizeof(R) == 8 && (double)M > 0.75 * kDegridThreads * (double)parts;
+    return most <= 1 || (restaged < 0.12 * taps && (nunits < 2048 || filled)) ? most : 0;
+}
+
 template <typename R> static void build_layout_t(riop_plan *p, const void *uv, hipStream_t st) {
     const int64_t M = p->M;
     const int K = p->K, T = p->tile, tps = p->tiles_per_side, ntiles = p->ntiles, J = p->J;
@@ -1312,16 +1359,18 @@ template <typename R> static void build_layout_t(riop_plan *p, const void *uv, h
     // Degridding work units: chunks of at most kUnit visibilities of one tile.
     std::vector<WorkUnit> units;
     int maxc = 0;
+    int64_t parts = 0;
     for (int t = 0; t < ntiles; ++t) {
         const int s0 = fs[(size_t)t * fine], e0 = fs[(size_t)(t + 1) * fine];
         for (int c = s0; c < e0; c += kUnit) {
             const int cnt = std::min(kUnit, e0 - c);
             units.push_back(WorkUnit{t, c, cnt, 0});
             maxc = std::max(maxc, cnt);
+            parts += (cnt + kDegridThreads - 1) / kDegridThreads;
         }
     }
     p->nunits = (int)units.size();
-    p->max_unit = maxc;
+    p->degrid_parts = degrid_parts<R>(p->nunits, parts, maxc, T, J, M);
     p->units.alloc(sizeof(WorkUnit) * std::max<size_t>(1, units.size()));
     if (!units.empty())
         RIOP_HIP(hipMemcpyAsync(p->units.ptr, units.data(), sizeof(WorkUnit) * units.size(),
@@ -1368,14 +1417,6 @@ template <typename R> static GridArgs<R> grid_args(riop_plan *p) {
 
 #define RIOP_J_CASES(MACRO) MACRO(2) MACRO(4) MACRO(6) MACRO(8) MACRO(10) MACRO(12) MACRO(14) MACRO(16)
 
-// Whether a unit's visibilities are spread over kPerThread blocks.  Restaging
-// the region costs less than idle compute units do while there are few units:
-// J = 8, FP32, 1500 units 17.7 -> 14.8 us, 6900 units 53.5 -> 58.2 us, 9000
-// units 52.0 -> 53.1 us.  In double precision always: the registers of
-// kPerThread visibilities leave 3 wavefronts per SIMD instead of 8 (6900 units
-// 140 against 115 us).
-template <typename R> static bool degrid_split(int nunits) { return sizeof(R) == 8 || nunits < 4096; }
-
 template <typename R>
 static void launch_degrid_from(riop_plan *p, const void *grid, void *y, int order_user, hipStream_t st) {
     if (p->nunits == 0) return;
@@ -1385,22 +1426,20 @@ static void launch_degrid_from(riop_plan *p, const void *grid, void *y, int orde
     a.order_user = order_user;
     const int W = p->tile + p->J - 1;
     const size_t lds = sizeof(C<R>) * W * W;
-    const bool split = degrid_split<R>(p->nunits);
-    const dim3 g(p->nunits, split ? kPerThread : 1), t(kDegridThreads);
+    const bool split = p->degrid_parts > 0;
+    const dim3 g(p->nunits, split ? p->degrid_parts : 1), t(kDegridThreads);
     TimedScope ts(p, KK_DEGRID, st);
     switch (p->J) {
-#define DG(JJ)                                                                                         \
-    case JJ: {                                                                                         \
-        constexpr int PT = sizeof(R) == 4 ? kPerThread : 1;                                            \
-        if (split) {                                                                                   \
-            if (order_user) hipLaunchKernelGGL((degrid_kernel<R, JJ, true, 1>), g, t, lds, st, a);     \
-            else hipLaunchKernelGGL((degrid_kernel<R, JJ, false, 1>), g, t, lds, st, a);               \
-        } else {                                                                                       \
-            if (order_user) hipLaunchKernelGGL((degrid_kernel<R, JJ, true, PT>), g, t, lds, st, a);    \
-            else hipLaunchKernelGGL((degrid_kernel<R, JJ, false, PT>), g, t, lds, st, a);              \
-        }                                                                                              \
-        break;                                                                                         \
-    }
+#define DG(JJ)                                                                                              \
+    case JJ:                                                                                                \
+        if (split) {                                                                                        \
+            if (order_user) hipLaunchKernelGGL((degrid_kernel<R, JJ, true, 1>), g, t, lds, st, a);          \
+            else hipLaunchKernelGGL((degrid_kernel<R, JJ, false, 1>), g, t, lds, st, a);                    \
+        } else {                                                                                            \
+            if (order_user) hipLaunchKernelGGL((degrid_kernel<R, JJ, true, kPerThread>), g, t, lds, st, a); \
+            else hipLaunchKernelGGL((degrid_kernel<R, JJ, false, kPerThread>), g, t, lds, st, a);           \
+        }                                                                                                   \
+        break;
         RIOP_J_CASES(DG)
 #undef DG
         default: throw Error{RIOP_ENOTSUP, "unsupported kernel width"};
