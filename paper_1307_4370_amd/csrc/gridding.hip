@@ -435,6 +435,16 @@ __device__ inline mfma_d4 mfma_16x16x4(double a, double b, mfma_d4 c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
+// Orders this wavefront's LDS accesses before and after it, across its lanes: the
+// hardware keeps one wavefront's LDS accesses in order, so the fences emit no
+// instruction, but without them the compiler may move a store to a word that
+// another lane also writes or reads.
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // {a.lower, b.lower} and {a.upper, b.upper} (halves of 32 lanes).
 __device__ inline void swap_halves(float &a, float &b) {
     typedef unsigned u2 __attribute__((ext_vector_type(2)));
@@ -815,10 +825,11 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
                 wuv[(ax * H + j) * SR + e] = mk<R>(w[j] * val.x, w[j] * val.y);
             }
             // Column weights at rows db .. db + J - 1, zeros in the other rows:
-            // each half clears 8 rows at fixed offsets, then its weights are
-            // written over them (one wavefront's LDS writes land in order).
+            // each half clears 8 rows at fixed offsets, then both write their
+            // weights over them, also into rows that the other half cleared.
 #pragma unroll
             for (int r = 0; r < 8; ++r) wv[(ax * 8 + r) * SR + e] = R(0);
+            wave_sync();
             R *wcol = wv + (db + ax * H) * SR + e;
 #pragma unroll
             for (int j = 0; j < H; ++j) wcol[j * SR] = c[j];
@@ -846,7 +857,7 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
         // the previous entry's (lane 0 compares with the open run).
         const int prev = __builtin_amdgcn_update_dpp(cur, pos, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
         const uint64_t starts = __ballot(live && ax == 0 && pos != prev);
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         // The next slice's visibility: global loads in flight during the accumulation.
         load(base + SL + e);
 
@@ -960,7 +971,7 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
             }
         }
         // The next slice's staging overwrites this one.
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
     }
     if (!P2 && a.flag) fc.report(a.flag);
     if (cur >= 0) {
@@ -1145,16 +1156,17 @@ template <int J> __global__ void __launch_bounds__(64 * kGramWaves, 4) gram_tile
 #pragma unroll
         for (int i = 0; i < H; ++i) wuv[(half * H + i) * SR + e] = make_float2(wr[i] * xr, wr[i] * xi);
         // Column weights at rows db .. db + J - 1 of the 16-row block, zeros in
-        // the others: each half clears 8 rows, then writes its half of the weights
-        // (one wavefront's LDS writes land in order).
+        // the others: each half clears 8 rows, then writes its half of the weights,
+        // also into rows that the other half cleared.
 #pragma unroll
         for (int r = 0; r < 8; ++r) wv[(half * 8 + r) * SR + e] = 0.f;
+        wave_sync();
         float *wcol = wv + (db + half * H) * SR + e;
 #pragma unroll
         for (int j = 0; j < H; ++j) wcol[j * SR] = half ? wc[j + H] : wc[j];
         const int prev = __builtin_amdgcn_update_dpp(cur, pos, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
         const uint64_t starts = __ballot(live && half == 0 && pos != prev);
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         load(base + SL + e);  // in flight during the accumulation
         if (nlive == SL) {
 #pragma unroll
@@ -1164,7 +1176,7 @@ template <int J> __global__ void __launch_bounds__(64 * kGramWaves, 4) gram_tile
 #pragma unroll 1
             for (int g = 0; g < ng; ++g) group(g, starts, pos);
         }
-        __builtin_amdgcn_wave_barrier();  // the next slice's staging overwrites this one
+        wave_sync();  // the next slice's staging overwrites this one
     }
     if (cur >= 0) close(cur);
     __syncthreads();
