@@ -240,8 +240,8 @@ struct riop_plan {
     riop::DevBuf ll;        // per-basis low-low scratch (analysis / synthesis)
     size_t ll_stride = 0;   // complex entries per basis in `ll`
 
-    // Precomputed Gram operator G^T G (optional): one K x K plane of the
-    // plan's real type per offset of the half set.
+    // Precomputed Gram operator G^T G (optional): K^2 values of the plan's real
+    // type per offset of the half set, interleaved by row chunks (gram.hip).
     riop::DevBuf gram;
     int gram_nplanes = 0;
 

@@ -97,21 +97,22 @@ __global__ void __launch_bounds__(64 * kGramWaves)
     }
 }
 
-// Stored layout: rows cut into chunks of kGramCols cells, the planes innermost
-// but for the chunk's cells: H[k1][chunk][plane][cell] (cells past K zero).  All
-// planes of a chunk lie within some tens of KB, a chunk's planes a constant 256
-// or 512 B apart; whole planes one after the other, a power of two apart, fell
-// into the same cache sets.
+// Stored layout: rows cut into chunks of CW cells, the planes innermost but for
+// the chunk's cells: H[k1][chunk][plane][cell].  CW is the largest power of two
+// up to kGramCols that divides K, so the planes take K^2 values each and no
+// padding.  All planes of a chunk lie within some tens of KB, a chunk's planes a
+// constant 256 or 512 B apart (less for narrower chunks); whole planes one after
+// the other, a power of two apart, fell into the same cache sets.
 constexpr int kGramRows = 4, kGramCols = 64;
+static int gram_chunk(int K) { return std::min(K & -K, kGramCols); }
 
 template <typename R>
-__global__ void gram_round(const double *__restrict__ Hd, R *__restrict__ H, int K, int chunks, int nplanes) {
-    const long K2 = (long)K * K, n = (long)K * chunks * nplanes * kGramCols;
+__global__ void gram_round(const double *__restrict__ Hd, R *__restrict__ H, int K, int CW, int nplanes) {
+    const long K2 = (long)K * K, row_len = (long)K * nplanes, n = K * row_len;
     for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-        const int j = (int)(i % kGramCols);
-        const long r = i / kGramCols, rc = r / nplanes;
-        const int d = (int)(r % nplanes), k2 = (int)(rc % chunks) * kGramCols + j;
-        H[i] = k2 < K ? (R)Hd[d * K2 + (rc / chunks) * K + k2] : R(0);
+        const long k1 = i / row_len;
+        const int r = (int)(i - k1 * row_len), j = r % CW, d = (r / CW) % nplanes, k2 = r / (CW * nplanes) * CW + j;
+        H[i] = (R)Hd[d * K2 + k1 * K + k2];
     }
 }
 
@@ -149,16 +150,19 @@ template <typename R> __device__ inline Quad<R> load_quad(const R *p) {
 // its L2 then holds the plane rows that its second reads ask for again.
 // K = 512, J = 8, FP32 (118 MB of planes, cold): 78 us with one thread
 // per cell over whole planes -> 41 us (64 us over whole planes with this kernel).
-template <typename R, int J>
+// CW: the chunk width if known at compile time (plane offsets are then
+// immediates), 0 to take `cw`.
+template <typename R, int J, int CW>
 __global__ void __launch_bounds__(256) gram_apply(const R *__restrict__ H, const C<R> *__restrict__ in,
-                                                  C<R> *__restrict__ out, int K, int chunks) {
+                                                  C<R> *__restrict__ out, int K, int cw) {
     constexpr int W = J - 1, XW = kGramCols + 2 * W, XH = kGramRows + 2 * W, P = 2 * J - 1, NP = J + W * P;
     constexpr int kX = XH * XW * (int)sizeof(C<R>), kSum = 3 * 64 * 8 * (int)sizeof(double);
     __shared__ __align__(16) unsigned char smem[kX > kSum ? kX : kSum];
     C<R> *xs = reinterpret_cast<C<R> *>(smem);
     const int nb = gridDim.x, xcd = blockIdx.x & 7, per = nb >> 3, rem = nb & 7;
     const int blk = xcd * per + min(xcd, rem) + (blockIdx.x >> 3);
-    const int r0 = (blk / chunks) * kGramRows, c0 = (blk % chunks) * kGramCols;
+    const int tiles = (K + kGramCols - 1) / kGramCols, width = CW ? CW : cw;
+    const int r0 = (blk / tiles) * kGramRows, c0 = (blk % tiles) * kGramCols;
     for (int e = threadIdx.x; e < XH * XW; e += 256) {
         const int i = e / XW, j = e - i * XW;
         // r0 - W and c0 - W are at least -K (K >= 2 J).
@@ -177,7 +181,7 @@ __global__ void __launch_bounds__(256) gram_apply(const R *__restrict__ H, const
         int c = k2 + 4 * (q - Q);
         c += c < 0 ? K : 0;
         c -= c >= K ? K : 0;
-        quad[q] = (size_t)(c / kGramCols) * (NP * kGramCols) + c % kGramCols;
+        quad[q] = (size_t)(c / width) * (NP * width) + c % width;
     }
     double ar[4] = {}, ai[4] = {};
     auto add = [&](R h, C<R> x, int i) {
@@ -188,14 +192,14 @@ __global__ void __launch_bounds__(256) gram_apply(const R *__restrict__ H, const
     // own cell has no second term).
     auto offsets = [&](auto lo, int da) {
         constexpr int LO = decltype(lo)::value;
-        const R *Hd = H + (da == 0 ? 0 : J + (da - 1) * P) * kGramCols;
-        const size_t row_len = (size_t)chunks * (NP * kGramCols);
+        const R *Hd = H + (da == 0 ? 0 : J + (da - 1) * P) * width;
+        const size_t row_len = (size_t)K * NP;
         const R *Hf = Hd + k1 * row_len + quad[Q];
         const R *Hb = Hd + (k1 - da + (k1 < da ? K : 0)) * row_len;
         const C<R> *xf = xs + (row + W + da) * XW + col + W, *xb = xs + (row + W - da) * XW + col + W;
 #pragma unroll
         for (int db = LO; db <= W; ++db) {
-            const int plane = (db - LO) * kGramCols;
+            const int plane = (db - LO) * width;
             const Quad<R> f = load_quad(Hf + plane);
 #pragma unroll
             for (int i = 0; i < 4; ++i) add(f.v[i], xf[i + db], i);
@@ -257,10 +261,9 @@ template <typename R> static void gram_build_t(riop_plan *p, hipStream_t st) {
                            (const R *)p->kcoef_compact.as<R>(), (long)p->M, K, J, p->n_even,
                            (const int3 *)tri_d.as<int3>(), (int)tri.size(), Hd.as<double>());
     }
-    const int chunks = (K + kGramCols - 1) / kGramCols;
-    p->gram.alloc(sizeof(R) * np_ * (size_t)K * chunks * kGramCols);
+    p->gram.alloc(sizeof(R) * np_ * K2);
     hipLaunchKernelGGL((gram_round<R>), dim3(4096), dim3(256), 0, st, (const double *)Hd.as<double>(), p->gram.as<R>(),
-                       K, chunks, np_);
+                       K, gram_chunk(K), np_);
     RIOP_HIP(hipGetLastError());
     RIOP_HIP(hipStreamSynchronize(st));  // the temporaries go out of scope
     p->gram_nplanes = np_;
@@ -275,18 +278,22 @@ void gram_build_plan(riop_plan *p, hipStream_t st) {
 }
 
 template <typename R> void launch_gram_apply(riop_plan *p, const void *in_grid, void *out_grid, hipStream_t st) {
-    const int K = p->K, chunks = (K + kGramCols - 1) / kGramCols;
-    RIOP_REQUIRE(K % 4 == 0, RIOP_EDEVICE, "grid side must be a multiple of 4");
-    const dim3 g((unsigned)(chunks * (K / kGramRows))), t(256);
+    const int K = p->K, cw = gram_chunk(K);
+    RIOP_REQUIRE(cw >= 4, RIOP_EDEVICE, "grid side must be a multiple of 4");
+    const dim3 g((unsigned)((K + kGramCols - 1) / kGramCols * (K / kGramRows))), t(256);
     TimedScope ts(p, KK_GRAM, st);
     switch (p->J) {
-#define GA(JJ)                                                                                                  \
-    case JJ:                                                                                                    \
-        hipLaunchKernelGGL((gram_apply<R, JJ>), g, t, 0, st, (const R *)p->gram.as<R>(),                        \
-                           static_cast<const C<R> *>(in_grid), static_cast<C<R> *>(out_grid), K, chunks);      \
+#define GA_LAUNCH(JJ, CW)                                                                                    \
+    hipLaunchKernelGGL((gram_apply<R, JJ, CW>), g, t, 0, st, (const R *)p->gram.as<R>(),                     \
+                       static_cast<const C<R> *>(in_grid), static_cast<C<R> *>(out_grid), K, cw)
+#define GA(JJ)                                      \
+    case JJ:                                        \
+        if (cw == kGramCols) GA_LAUNCH(JJ, kGramCols); \
+        else GA_LAUNCH(JJ, 0);                      \
         break;
         GA(2) GA(4) GA(6) GA(8) GA(10) GA(12) GA(14) GA(16)
 #undef GA
+#undef GA_LAUNCH
         default: throw Error{RIOP_ENOTSUP, "unsupported kernel width"};
     }
     RIOP_HIP(hipGetLastError());
