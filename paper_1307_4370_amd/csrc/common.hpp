@@ -167,10 +167,11 @@ struct SdmmWork {
     // Prior of the l1 step: 0 = analysis l1 over the SARA dictionary (L1 =
     // Psi^dagger), 1 = weighted TV (L1 = I, prox by fast gradient projection
     // on the dual with tv_inner iterations; tvb N complex, the point the prox
-    // is taken at, tvd two sets of the four dual images, read and written in turn).
+    // is taken at, tvd 5 N: with CG's r, p and qp, idle during the prox, the two
+    // sets of four dual images, read and written in turn).
     int prior = 0;
     int tv_inner = 0;
-    DevBuf tvb, tvd[2];
+    DevBuf tvb, tvd;
     DevBuf rw_w;            // reweighted l1: the current weights (q*N reals)
     DevBuf xprev;           // reweighted l1: the previous pass's solution (N complex)
     DevBuf history;         // doubles, kHistStride per iteration

@@ -526,8 +526,8 @@ static int tv_iters(int n) { return n <= 384 ? 7 : 5; }
 template <typename R> struct TvArgs {
     const C<R> *xh, *z1_in;  // first launch
     C<R> *b;
-    const C<R> *in;          // p, q, r, s (N each), read unless first
-    C<R> *out;               // written unless last
+    const C<R> *in[4];       // p, q, r, s, read unless first
+    C<R> *out[4];            // written unless last
     C<R> *z1, *x1;           // last launch
     const R *w;              // weights, nullable (1)
     const double *lam;
@@ -543,7 +543,7 @@ template <typename R> __global__ void __launch_bounds__(kTvTile * kTvTile) tv_ti
     const int i = (int)(blockIdx.x / tiles) * own - lo + ty, j = (int)(blockIdx.x % tiles) * own - lo + tx;
     const bool inside = i >= 0 && i < n && j >= 0 && j < n;
     const bool mine = inside && ty >= lo && ty < lo + own && tx >= lo && tx < lo + own;
-    const long N = (long)n * n, k = inside ? (long)i * n + j : 0;
+    const long k = inside ? (long)i * n + j : 0;
     const double lamd = *a.lam;
     const R lam = (R)lamd, step = lamd > 0 ? (R)(1.0 / (8.0 * lamd)) : R(0);
     const C<R> zero = mk<R>(0, 0);
@@ -554,10 +554,10 @@ template <typename R> __global__ void __launch_bounds__(kTvTile * kTvTile) tv_ti
             b = cadd<R>(a.xh[k], a.z1_in[k]);
         } else {
             b = a.b[k];
-            p = a.in[k];
-            q = a.in[N + k];
-            r = a.in[2 * N + k];
-            s = a.in[3 * N + k];
+            p = a.in[0][k];
+            q = a.in[1][k];
+            r = a.in[2][k];
+            s = a.in[3][k];
         }
         if (a.w) w = a.w[k];
     }
@@ -610,10 +610,10 @@ template <typename R> __global__ void __launch_bounds__(kTvTile * kTvTile) tv_ti
         }
     } else if (mine) {
         if (a.first) a.b[k] = b;
-        a.out[k] = p;
-        a.out[N + k] = q;
-        a.out[2 * N + k] = r;
-        a.out[3 * N + k] = s;
+        a.out[0][k] = p;
+        a.out[1][k] = q;
+        a.out[2][k] = r;
+        a.out[3][k] = s;
     }
 }
 
@@ -845,7 +845,7 @@ static void sdmm_init(riop_plan *p, const void *y, double eps, const riop_sdmm_p
     const long D = prior == PRIOR_TV ? N : (long)p->q * N;
     if (prior == PRIOR_TV) {
         w.tvb.reserve(cbytes(p) * (size_t)N);
-        for (DevBuf &b : w.tvd) b.reserve(4 * cbytes(p) * (size_t)N);
+        w.tvd.reserve(5 * cbytes(p) * (size_t)N);
     }
     if (w.prior != prior || w.tv_inner != tv_inner) ++w.epoch;
     w.prior = prior;
@@ -960,6 +960,10 @@ template <typename R> static void sdmm_step(riop_plan *p, int iters, hipStream_t
             tv.w = tw;
             tv.lam = sc + SC_GAMMA;
             tv.n = n;
+            // The two sets of p, q, r, s; CG has ended and its vectors are idle.
+            C<R> *const td = w.tvd.as<C<R>>();
+            C<R> *const sets[2][4] = {{td, td + N, td + 2 * N, td + 3 * N},
+                                      {td + 4 * N, w.r.as<C<R>>(), w.p.as<C<R>>(), w.qp.as<C<R>>()}};
             // The iterations spread evenly over the launches, at least two.
             const int per = tv_iters(n), launches = std::max(2, (w.tv_inner + per - 1) / per);
             double tk = 1.0;
@@ -968,8 +972,10 @@ template <typename R> static void sdmm_step(riop_plan *p, int iters, hipStream_t
                 done += tv.it;
                 tv.first = l == 0;
                 tv.last = l == launches - 1;
-                tv.in = w.tvd[l & 1].as<C<R>>();
-                tv.out = w.tvd[1 - (l & 1)].as<C<R>>();
+                for (int i = 0; i < 4; ++i) {
+                    tv.in[i] = sets[l & 1][i];
+                    tv.out[i] = sets[1 - (l & 1)][i];
+                }
                 for (int k = 0; k < tv.it; ++k) {
                     const double tn = (1.0 + std::sqrt(1.0 + 4.0 * tk * tk)) / 2.0;
                     tv.c[k] = (tk - 1.0) / tn;

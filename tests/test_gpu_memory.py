@@ -29,3 +29,21 @@ def test_stored_gram_takes_its_planes(n, J, prec, rb):
     assert device_bytes() - held == (J + (J - 1) * (2 * J - 1)) * (2 * n) ** 2 * rb
     plan.gram_release()
     assert device_bytes() == held
+
+
+@pytest.mark.parametrize("prec,cb", [("f32", 8), ("f64", 16)])
+@pytest.mark.parametrize("n,inner", [(16, 1), (64, 8), (48, 33)])
+def test_tv_takes_six_images(n, inner, prec, cb):
+    """Beyond the solver's workspace the TV prior holds six complex images, whatever
+    the number of inner iterations."""
+    device()
+    announce(f"TV bytes n={n} inner={inner} {prec}")
+    from paper_1307_4370_amd import device_bytes
+    M = 300
+    plan = _plan(n, M, 6, prec)
+    y = to_dev(W.random_complex(M, W.rng(361, n)), prec)
+    eps = 0.5 * float(torch.linalg.vector_norm(y))
+    plan.sdmm(y, eps, 2, n_cg=2)
+    held = device_bytes()
+    plan.sdmm_tv(y, eps, 2, n_cg=2, n_inner=inner)
+    assert device_bytes() - held == 6 * n * n * cb
