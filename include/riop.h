@@ -55,6 +55,8 @@
  *     (bytes, read at each allocation) caps what the library holds in this
  *     process; an allocation past it fails with RIOP_ENOMEM, as a failed
  *     hipMalloc does (riop_device_bytes reports what is held).
+ *     A plan created while it is set takes the gridding form with the smallest
+ *     buffers, which can be slower on small images.
  */
 #ifndef RIOP_H
 #define RIOP_H

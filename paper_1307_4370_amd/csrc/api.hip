@@ -36,9 +36,13 @@ static std::atomic<size_t> g_held{0};
 
 size_t device_bytes_held() { return g_held.load(); }
 
+size_t device_bytes_limit() {
+    const char *e = std::getenv("RIOP_DEVICE_MEMORY_LIMIT");
+    return e ? (size_t)std::strtoull(e, nullptr, 10) : 0;
+}
+
 void account_alloc(size_t bytes) {
-    size_t limit = 0;
-    if (const char *e = std::getenv("RIOP_DEVICE_MEMORY_LIMIT")) limit = (size_t)std::strtoull(e, nullptr, 10);
+    const size_t limit = device_bytes_limit();
     const size_t now = g_held.fetch_add(bytes) + bytes;
     if (limit && now > limit) {
         g_held.fetch_sub(bytes);

@@ -72,6 +72,7 @@ struct Error {
 // read at every allocation; unset or 0 = no limit).  An allocation that would
 // pass the limit fails with RIOP_ENOMEM exactly as a failed hipMalloc does.
 size_t device_bytes_held();
+size_t device_bytes_limit();         // 0: none
 void account_alloc(size_t bytes);    // throws RIOP_ENOMEM past the limit
 void account_free(size_t bytes);
 

@@ -1367,6 +1367,7 @@ template <typename R> static void build_layout_t(riop_plan *p, const void *uv, h
     RIOP_HIP(hipMemcpyAsync(fs.data(), fine_start.ptr, sizeof(int) * fs.size(), hipMemcpyDeviceToHost, st));
     RIOP_HIP(hipStreamSynchronize(st));
     RIOP_REQUIRE(hflag == 0, RIOP_EINVAL, "uv coordinates must be finite and inside [-pi, pi]");
+    for (DevBuf *b : {&key_a, &key_b, &val_b, &cell_of, &frac_of, &counts, &sums, &fine_start}) b->release();
 
     // Degridding work units: chunks of at most kUnit visibilities of one tile.
     std::vector<WorkUnit> units;
@@ -1388,8 +1389,22 @@ template <typename R> static void build_layout_t(riop_plan *p, const void *uv, h
         RIOP_HIP(hipMemcpyAsync(p->units.ptr, units.data(), sizeof(WorkUnit) * units.size(),
                                 hipMemcpyHostToDevice, st));
 
-    // Gridding: bands, heaviest first, each with its visibility range.
-    const int TB = choose_band<R>(fs, T, J, M), step = TB / kBandRows, nbands = nfine / step;
+    // Gridding: bands, heaviest first, each with its visibility range.  Narrow
+    // bands have larger halos: not where the library's memory is capped (a later
+    // call may need what they take), nor where the device has no room.
+    const auto halo_bytes = [&](int TB) {
+        return sizeof(C<R>) * (size_t)(J - 1) * ((size_t)K * tps + (size_t)ntiles * (T / TB) * (T + J - 1));
+    };
+    int TB = device_bytes_limit() ? T : choose_band<R>(fs, T, J, M);
+    try {
+        p->halo.alloc(halo_bytes(TB));
+    } catch (const Error &e) {
+        if (e.status != RIOP_ENOMEM || TB == T) throw;
+        (void)hipGetLastError();  // the failed hipMalloc's
+        TB = T;
+        p->halo.alloc(halo_bytes(TB));
+    }
+    const int step = TB / kBandRows, nbands = nfine / step;
     p->band = TB;
     std::vector<std::pair<int, int>> work(nbands);
     for (int t = 0; t < nbands; ++t) work[t] = {fs[(size_t)(t + 1) * step] - fs[(size_t)t * step], t};
@@ -1400,7 +1415,6 @@ template <typename R> static void build_layout_t(riop_plan *p, const void *uv, h
         order[k] = WorkUnit{t, fs[(size_t)t * step], work[k].first, 0};
     }
     p->nbands = nbands;
-    p->halo.alloc(sizeof(C<R>) * (size_t)(J - 1) * ((size_t)K * tps + (size_t)nbands * (T + J - 1)));
     p->tile_order.alloc(sizeof(WorkUnit) * nbands);
     RIOP_HIP(hipMemcpyAsync(p->tile_order.ptr, order.data(), sizeof(WorkUnit) * nbands, hipMemcpyHostToDevice, st));
     RIOP_HIP(hipStreamSynchronize(st));

@@ -47,3 +47,33 @@ def test_tv_takes_six_images(n, inner, prec, cb):
     held = device_bytes()
     plan.sdmm_tv(y, eps, 2, n_cg=2, n_inner=inner)
     assert device_bytes() - held == 6 * n * n * cb
+
+
+@pytest.mark.parametrize("prec,cb", [("f32", 8), ("f64", 16)])
+@pytest.mark.parametrize("n,J", [(128, 8), (64, 6), (128, 10)])
+def test_capped_plans_keep_the_smallest_halo(n, J, prec, cb, monkeypatch):
+    """A coverage that narrow gridding bands serve best: under a cap the plan keeps
+    one band per tile, (J - 1)(K tps + ntiles (T + J - 1)) halo cells, and gives the
+    same results."""
+    device()
+    announce(f"capped plan n={n} J={J} {prec}")
+    g = W.rng(362, n, J)
+    M = 30000
+    uv = np.clip(g.standard_normal((M, 2)) * 0.3, -np.pi, np.pi).astype(np.float32).astype(np.float64)
+    y = to_dev(W.random_complex(M, g), prec)
+    from paper_1307_4370_amd import Plan, device_bytes
+    held = device_bytes()
+    free = Plan(n, to_dev(uv, prec), J=J, levels=1, prec=prec)
+    free_bytes = device_bytes() - held
+    monkeypatch.setenv("RIOP_DEVICE_MEMORY_LIMIT", str(1 << 36))
+    held = device_bytes()
+    capped = Plan(n, to_dev(uv, prec), J=J, levels=1, prec=prec)
+    extra = free_bytes - (device_bytes() - held)
+    info = capped.info()
+    T = info["tile"]
+    # Per extra band: its bottom strip, and its place in the list of bands.
+    per_band = cb * (J - 1) * (T + J - 1) + 16
+    assert extra % (per_band * info["ntiles"]) == 0
+    assert extra // (per_band * info["ntiles"]) + 1 in (2, 4, 8)
+    a, b = free.phi_adj(y), capped.phi_adj(y)
+    assert float(torch.linalg.vector_norm(a - b) / torch.linalg.vector_norm(a)) <= (1e-6 if prec == "f32" else 1e-14)
