@@ -37,6 +37,7 @@ template <typename R> struct AnaArgs {
     int n, s, TO, last;
     int nbases;         // Daubechies bases launched
     int dirac_plane;    // level 1: plane of the Dirac basis, done by blockIdx.y = nbases (-1: none)
+    int dirac_blocks;   // its blocks (the rest of that row of blocks is idle)
     R scale;            // 1/sqrt(q) applied to final coefficients
     int *flag;          // level 1: set to 1 where the input holds a NaN or Inf (nullptr: not checked)
     int prox;
@@ -232,17 +233,18 @@ template <typename R, int TO> __global__ void __launch_bounds__(256) dwt_analysi
     extern __shared__ __align__(16) unsigned char smem_raw[];
     C<R> *smem = reinterpret_cast<C<R> *>(smem_raw);
     const int bi = blockIdx.y;
-    if (bi == a.nbases) {  // level 1: the Dirac plane of this tile, alpha_0 = x / sqrt(q)
-        const int n = a.n, tiles = (n >> 1) / TO;
-        const int i0 = (blockIdx.x / tiles) * 2 * TO, j0 = (blockIdx.x % tiles) * 2 * TO;
+    if (bi == a.nbases) {  // level 1: the Dirac plane, alpha_0 = x / sqrt(q)
+        if ((int)blockIdx.x >= a.dirac_blocks) return;
+        const long N = (long)a.n * a.n;
         double f1 = 0.0;
+        const long step = a.dirac_blocks * 256L;
+        for (long i0 = (long)blockIdx.x * 256 + threadIdx.x; i0 < N; i0 += 4 * step) {
+            C<R> x[4];
 #pragma unroll
-        for (int u = 0; u < (4 * TO * TO + 255) / 256; ++u) {
-            const int e = threadIdx.x + 256 * u;
-            if (e < 4 * TO * TO) {
-                const long i = (long)(i0 + e / (2 * TO)) * n + j0 + e % (2 * TO);
-                dirac_coef<R>(a, i, a.in[i], f1);
-            }
+            for (int u = 0; u < 4; ++u) x[u] = i0 + u * step < N ? a.in[i0 + u * step] : mk<R>(0, 0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (i0 + u * step < N) dirac_coef<R>(a, i0 + u * step, x[u], f1);
         }
         if (a.prox) block_add_f1(f1, a.px.f1_part);
         return;
@@ -563,13 +565,20 @@ static size_t ll_offset(int n, int level) {
 
 static int dirac_blocks(int n) { return (int)std::min<long>(((long)n * n + 255) / 256, 4096); }
 
+// Blocks of level 1 that copy the Dirac plane: one per tile, but where the tiles
+// are small no more than have 256 pixels each (every block has a partial of f1).
+static int dirac_row_blocks(int n) {
+    const int tiles = (n >> 1) / tile_side(n >> 1);
+    return std::min(tiles * tiles, dirac_blocks(n));
+}
+
 int psi_adj_blocks(const riop_plan *p) {
     const int n = p->n, dirac = p->mask & 1, nb = p->q - dirac;
     if (nb == 0) return dirac_blocks(n);
-    int total = 0;
+    int total = dirac ? dirac_row_blocks(n) : 0;
     for (int lev = 1; lev <= p->L; ++lev) {
         const int half = (n >> (lev - 1)) >> 1, tiles = half / tile_side(half);
-        total += tiles * tiles * (nb + (lev == 1 ? dirac : 0));
+        total += tiles * tiles * nb;
     }
     return total;
 }
@@ -648,7 +657,8 @@ static void psi_adj_impl(riop_plan *p, const void *x, void *alpha, const Prox1<R
         a.ll_bstride = (long)p->ll_stride;
         const int tiles = half / a.TO;
         TimedScope ts(p, KK_PSI_ADJ, st);
-        const dim3 grid(tiles * tiles, nb + (lev == 1 && a.dirac_plane >= 0 ? 1 : 0));
+        a.dirac_blocks = lev == 1 && a.dirac_plane >= 0 ? dirac_row_blocks(n) : 0;
+        const dim3 grid(tiles * tiles, nb + (a.dirac_blocks > 0 ? 1 : 0));
         switch (a.TO) {
 #define ANA(T)                                                                                           \
     case T: hipLaunchKernelGGL((dwt_analysis<R, T>), grid, dim3(256), (ana_lds<R, T>()), st, a); break;
@@ -657,7 +667,7 @@ static void psi_adj_impl(riop_plan *p, const void *x, void *alpha, const Prox1<R
             default: hipLaunchKernelGGL((dwt_analysis<R, 1>), grid, dim3(256), (ana_lds<R, 1>()), st, a); break;
         }
         RIOP_HIP(hipGetLastError());
-        a.px.f1_part += a.prox ? (long)grid.x * grid.y : 0;
+        a.px.f1_part += a.prox ? (long)tiles * tiles * nb + a.dirac_blocks : 0;
     }
 }
 

@@ -77,3 +77,22 @@ def test_capped_plans_keep_the_smallest_halo(n, J, prec, cb, monkeypatch):
     assert extra // (per_band * info["ntiles"]) + 1 in (2, 4, 8)
     a, b = free.phi_adj(y), capped.phi_adj(y)
     assert float(torch.linalg.vector_norm(a - b) / torch.linalg.vector_norm(a)) <= (1e-6 if prec == "f32" else 1e-14)
+
+
+@pytest.mark.parametrize("n,levels,tiles", [(36, 1, [9]), (72, 2, [9, 9]), (108, 1, [27]), (64, 2, [2, 1])])
+def test_solver_workspace(n, levels, tiles):
+    """The solver's workspace at its first use: 8 images, two sets of nine
+    coefficient planes, three sets of visibilities, the partial sums of the
+    reductions, of which the l1 norm has one per analysis tile and basis and at
+    most one per 256 pixels for the Dirac basis, and the scalars."""
+    device()
+    announce(f"solver workspace n={n} levels={levels}")
+    from paper_1307_4370_amd import device_bytes
+    M, N = 300, n * n
+    plan = _plan(n, M, 6, "f32", levels, tile=8 if n % 16 else 0)
+    held = device_bytes()
+    b = to_dev(W.random_complex((n, n), W.rng(363, n)), "f32")
+    plan.cg(b, n_iter=1)
+    f1 = 8 * sum(t * t for t in tiles) + min(tiles[0] ** 2, -(-N // 256))
+    got = device_bytes() - held - 8 * (8 * N + 2 * 9 * N + 3 * M) - 8 * f1
+    assert got == 8 * (7 * 512 + 10)
