@@ -24,6 +24,9 @@ namespace riop {
 constexpr int kMaxTaps = 16;
 constexpr int kTO = 16;  // output tile side per sub-band (analysis) / half the output tile (synthesis)
 
+// Tiles of TO cover a band of `half`; the last of a row or column may be partial:
+// its region wraps as any other and its outputs past the band are dropped.
+__host__ __device__ constexpr int tiles_of(int half, int TO) { return (int)((unsigned)(half + TO - 1) / TO); }
 
 template <typename R> struct AnaArgs {
     const C<R> *in;     // level input: x (level 1, shared) or per-basis LL slot
@@ -34,7 +37,7 @@ template <typename R> struct AnaArgs {
     const R *filt;      // [9][2][kMaxTaps] low / high pass
     int basis[8];       // Daubechies order of each launched basis
     int plane[8];       // plane index of each launched basis
-    int n, s, TO, last;
+    int n, s, TO, last;  // image side, level side, tile side, whether this is the last level
     int nbases;         // Daubechies bases launched
     int dirac_plane;    // level 1: plane of the Dirac basis, done by blockIdx.y = nbases (-1: none)
     int dirac_blocks;   // its blocks (the rest of that row of blocks is idle)
@@ -104,7 +107,7 @@ __device__ inline void ana_tile(const AnaArgs<R> &a, int bi, C<R> *smem) {
     constexpr int VL = TO < 4 ? TO : 4;  // outputs per thread along a row
     constexpr int VK = TO < 2 ? TO : 2;  // and along a column
     const int s = a.s, half = s >> 1, n = a.n;
-    const int tiles = half / TO;
+    const int tiles = tiles_of(half, TO);
     const int k0 = (blockIdx.x / tiles) * TO, l0 = (blockIdx.x % tiles) * TO;
     C<R> *reg = smem;                            // [IRM][IRM]
     C<R> *rows = reg + IRM * IRM;                // [low, high][IRM][RS]
@@ -121,7 +124,10 @@ __device__ inline void ana_tile(const AnaArgs<R> &a, int bi, C<R> *smem) {
     constexpr int kItems = 2 * (TO / VK) * TO;
     const int p = threadIdx.x / (kItems / 2), kq = threadIdx.x % (kItems / 2);
     const int k = (kq / TO) * VK, l = kq % TO;
-    const bool mine = threadIdx.x < kItems;
+    const bool mine = threadIdx.x < kItems && l0 + l < half && k0 + k < half;
+    // Rows past the first are inside with it unless the band's side is odd.
+    const bool odd = half & 1;
+    auto inside = [&](int v) { return v == 0 || !odd || k0 + k + v < half; };
     const long base = (long)a.plane[bi] * n * n + (long)(k0 + k) * n + p * half + l0 + l;
     auto place = [&](int v, int t) { return base + (long)(v + t * half) * n; };
     C<R> zq[VK][2];
@@ -132,7 +138,7 @@ __device__ inline void ana_tile(const AnaArgs<R> &a, int bi, C<R> *smem) {
         for (int t = 0; t < 2; ++t) {
             zq[v][t] = mk<R>(0, 0);
             wq[v][t] = R(1);
-            if (a.prox && mine && (p || t || a.last)) {  // the low-low band goes to the next level
+            if (a.prox && mine && inside(v) && (p || t || a.last)) {  // the low-low band goes to the next level
                 zq[v][t] = a.px.z1[place(v, t)];
                 if (a.px.weights) wq[v][t] = a.px.weights[place(v, t)];
             }
@@ -143,7 +149,7 @@ __device__ inline void ana_tile(const AnaArgs<R> &a, int bi, C<R> *smem) {
     {
         const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
         constexpr int RPT = (IR + 3) / 4;
-        const bool tiny = IR > s;
+        const bool tiny = 2 * (tiles - 1) * TO + IR > 2 * s;
         const unsigned gc = wrap(2 * l0 + min(tx, IR - 1), s, tiny);
         C<R> st[RPT];
 #pragma unroll
@@ -204,6 +210,7 @@ __device__ inline void ana_tile(const AnaArgs<R> &a, int bi, C<R> *smem) {
         for (int m = 0; m < NI; ++m) v[m] = col[m * RS];
 #pragma unroll
         for (int o = 0; o < VK; ++o) {
+            if (!inside(o)) break;
             R lr = 0, li = 0, hr = 0, hi = 0;
 #pragma unroll
             for (int m = 0; m < Lf; ++m) {
@@ -315,13 +322,19 @@ template <typename R> struct SynRegion {
 
 template <typename R>
 __device__ inline void syn_load(const SynArgs<R> &a, int bi, int t, int i0, int j0, SynRegion<R> &v) {
-    const int N = a.basis[bi], n = a.n, half = a.s >> 1, KR = a.TO + N - 1;
+    const int N = a.basis[bi], n = a.n, half = a.s >> 1, TO = a.TO, KR = TO + N - 1;
     const int c = t & 31, r0 = t >> 5;
     if (c >= KR) return;
-    const bool tiny = half < kMaxTaps / 2;  // region starts at -7 at least: one period is enough, but for tiny levels
-    auto wrap_neg = [&](int k) { return tiny ? (k % half + half) % half : k + (k < 0 ? half : 0); };
+    // The region starts at -7 at least and ends at half + TO - 2 at most: one period
+    // either way is enough, but for tiny levels.
+    const bool tiny = half < kTO, last = max(i0, j0) / 2 + TO > half;
+    auto wrap_band = [&](int k) {
+        if (tiny) return (k % half + half) % half;
+        if (last) k -= k >= half ? half : 0;
+        return k + (k < 0 ? half : 0);
+    };
     const int kst = i0 / 2 - N + 1;
-    const unsigned l = wrap_neg(j0 / 2 - N + 1 + c);
+    const unsigned l = wrap_band(j0 / 2 - N + 1 + c);
     // Band origins, uniform; offsets inside a plane are 32-bit.
     const C<R> *plane = a.alpha + (long)a.plane[bi] * n * n;
     const C<R> *lh = plane + half, *hl = plane + (long)half * n, *hh = hl + half;
@@ -331,7 +344,7 @@ __device__ inline void syn_load(const SynArgs<R> &a, int bi, int t, int i0, int 
     for (int q = 0; q < 3; ++q) {
         const int r = r0 + 8 * q;
         if (r < KR) {
-            const unsigned k = wrap_neg(kst + r), o = k * (unsigned)n + l;
+            const unsigned k = wrap_band(kst + r), o = k * (unsigned)n + l;
             v.ll[q] = ll[k * ls + l];
             v.lh[q] = lh[o];
             v.hl[q] = hl[o];
@@ -414,7 +427,8 @@ template <typename R, int TO, int N> __device__ inline void syn_cols(const R *fi
     }
 }
 
-// Output columns of thread t: row ii, columns jj .. jj + 2 NP - 1 (false: none).
+// Output columns of thread t: row ii, columns jj .. jj + 2 NP - 1 (false: none; those
+// past the level are dropped by the caller).
 template <int TO> __device__ inline bool syn_place(int t, int &ii, int &jj) {
     constexpr int NP = syn_pairs<TO>(), per = TO / NP;
     ii = t / per;
@@ -454,7 +468,7 @@ template <typename R, int TO> __global__ void __launch_bounds__(256) dwt_synthes
     extern __shared__ __align__(16) unsigned char smem_raw[];
     C<R> *smem = reinterpret_cast<C<R> *>(smem_raw);
     constexpr int TS = 2 * TO, NA = 2 * syn_pairs<TO>();
-    const int bi = blockIdx.y, t = threadIdx.x, tiles = a.s / TS;
+    const int bi = blockIdx.y, t = threadIdx.x, tiles = tiles_of(a.s, TS);
     const int i0 = (blockIdx.x / tiles) * TS, j0 = (blockIdx.x % tiles) * TS;
     SynRegion<R> v;
     syn_load<R>(a, bi, t, i0, j0, v);
@@ -467,10 +481,12 @@ template <typename R, int TO> __global__ void __launch_bounds__(256) dwt_synthes
     for (int i = 0; i < NA; ++i) acc[i] = mk<R>(0, 0);
     SYN_BASES(syn_rows, a.basis[bi], a.filt, t, smem, acc)
     int ii, jj;
-    if (syn_place<TO>(t, ii, jj)) {
+    if (syn_place<TO>(t, ii, jj) && i0 + ii < a.s && j0 + jj < a.s) {
         C<R> *out = a.ll_out + bi * a.ll_out_bstride + (long)(i0 + ii) * a.s + j0 + jj;
+        const bool odd = a.s & 2;  // else the NA columns are inside together
 #pragma unroll
-        for (int i = 0; i < NA; ++i) out[i] = acc[i];
+        for (int i = 0; i < NA; ++i)
+            if (i < 2 || !odd || j0 + jj + i < a.s) out[i] = acc[i];
     }
 }
 
@@ -483,12 +499,14 @@ __global__ void __launch_bounds__(256 * NG, sizeof(R) == 4 ? 4 : 2) dwt_synthesi
     constexpr int TS = 2 * TO, NA = 2 * syn_pairs<TO>();
     const int g = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), t = threadIdx.x & 255;
     C<R> *all = reinterpret_cast<C<R> *>(smem_raw), *smem = all + g * syn_cells<TO>();
-    const int n = a.n, tiles = a.s / TS;
+    const int n = a.n, tiles = tiles_of(n, TS);
     const int i0 = (blockIdx.x / tiles) * TS, j0 = (blockIdx.x % tiles) * TS;
     auto basis = [&](int step) { return step * NG + ((step & 1) ? NG - 1 - g : g); };
     int ii, jj;
-    const bool mine = syn_place<TO>(t, ii, jj);
+    const bool mine = syn_place<TO>(t, ii, jj) && i0 + ii < n && j0 + jj < n;
     const long o = (long)(i0 + ii) * n + j0 + jj;
+    const bool odd = n & 2;  // else the NA columns are inside together
+    auto inside = [&](int i) { return i < 2 || !odd || j0 + jj + i < n; };
     C<R> acc[NA], dirac[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) acc[i] = dirac[i] = mk<R>(0, 0);
@@ -496,7 +514,7 @@ __global__ void __launch_bounds__(256 * NG, sizeof(R) == 4 ? 4 : 2) dwt_synthesi
         FiniteCheck<R> fc;
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
-            dirac[i] = a.alpha[(long)a.dirac_plane * n * n + o + i];
+            if (inside(i)) dirac[i] = a.alpha[(long)a.dirac_plane * n * n + o + i];
             fc.add(dirac[i]);
         }
         if (a.flag) fc.report(a.flag);
@@ -532,7 +550,7 @@ __global__ void __launch_bounds__(256 * NG, sizeof(R) == 4 ? 4 : 2) dwt_synthesi
     for (int i = 0; i < NA; ++i) {
         C<R> z = acc[i];
         if (a.dirac_plane >= 0) z = cadd<R>(z, dirac[i]);
-        a.x[o + i] = cscale<R>(z, a.scale);
+        if (inside(i)) a.x[o + i] = cscale<R>(z, a.scale);
     }
 }
 #undef SYN_BASES
@@ -550,8 +568,17 @@ template <typename R> __global__ void dirac_only_synthesis(SynArgs<R> a, long N)
 // ---------------------------------------------------------------------------
 // Host side.
 
-// Tile side: the largest power of two dividing the sub-band side, at most kTO.
-static int tile_side(int half) { return std::min(kTO, half & -half); }
+// Tile side: kTO, or the power of two that covers a smaller band.  Tiles that divide
+// the band instead hold few samples where its side has few factors of 2, and most
+// of a block's threads then have nothing to do: 9 bases, one level, FP32 / FP64,
+// dividing -> covering tiles: 972^2 (band 486, tiles of 2) analysis 719 -> 33 us /
+// 1300 -> 64, synthesis 960 -> 48 / 1900 -> 78; 216^2 (108, tiles of 4) 16 -> 9 / 24 -> 9
+// and 24 -> 15 / 37 -> 21.
+static int tile_side(int half) {
+    int TO = 1;
+    while (TO < kTO && TO < half) TO *= 2;
+    return TO;
+}
 
 static size_t ll_offset(int n, int level) {
     // Slot of the LL produced by level `level` (1-based): sum of sizes of the earlier slots.
@@ -568,7 +595,7 @@ static int dirac_blocks(int n) { return (int)std::min<long>(((long)n * n + 255) 
 // Blocks of level 1 that copy the Dirac plane: one per tile, but where the tiles
 // are small no more than have 256 pixels each (every block has a partial of f1).
 static int dirac_row_blocks(int n) {
-    const int tiles = (n >> 1) / tile_side(n >> 1);
+    const int tiles = tiles_of(n >> 1, tile_side(n >> 1));
     return std::min(tiles * tiles, dirac_blocks(n));
 }
 
@@ -577,7 +604,7 @@ int psi_adj_blocks(const riop_plan *p) {
     if (nb == 0) return dirac_blocks(n);
     int total = dirac ? dirac_row_blocks(n) : 0;
     for (int lev = 1; lev <= p->L; ++lev) {
-        const int half = (n >> (lev - 1)) >> 1, tiles = half / tile_side(half);
+        const int half = (n >> (lev - 1)) >> 1, tiles = tiles_of(half, tile_side(half));
         total += tiles * tiles * nb;
     }
     return total;
@@ -596,7 +623,7 @@ template <typename R> static int syn_groups(int tiles) {
 
 template <typename R, int TO>
 static void launch_synthesis(const SynArgs<R> &a, int nb, bool final_level, hipStream_t st) {
-    const int tiles = a.s / (2 * TO), blocks = tiles * tiles;
+    const int tiles = tiles_of(a.s >> 1, TO), blocks = tiles * tiles;
     const size_t lds = sizeof(C<R>) * (size_t)syn_cells<TO>();
     if (!final_level) {
         hipLaunchKernelGGL((dwt_synthesis<R, TO>), dim3(blocks, nb), dim3(256), lds, st, a);
@@ -655,7 +682,7 @@ static void psi_adj_impl(riop_plan *p, const void *x, void *alpha, const Prox1<R
         }
         a.ll_out = a.last ? nullptr : ll + ll_offset(n, lev);
         a.ll_bstride = (long)p->ll_stride;
-        const int tiles = half / a.TO;
+        const int tiles = tiles_of(half, a.TO);
         TimedScope ts(p, KK_PSI_ADJ, st);
         a.dirac_blocks = lev == 1 && a.dirac_plane >= 0 ? dirac_row_blocks(n) : 0;
         const dim3 grid(tiles * tiles, nb + (a.dirac_blocks > 0 ? 1 : 0));
