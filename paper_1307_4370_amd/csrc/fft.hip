@@ -558,7 +558,10 @@ static int ct_elems(int N) {
 // without a block (16 blocks at N = 512), so the compile-time kernel takes fewer
 // columns per block, down to 4 (32 B pieces in single precision), until there
 // are 256: with CG's steps folded in, N = 512 forward 11.1 -> 9.2 us, adjoint
-// 7.5 -> 5.8 us (two columns 9.5 / 5.6, at N = 128 10.8 against 7.6 us).
+// 7.5 -> 5.8 us (two columns 9.5 / 5.6, at N = 128 10.8 against 7.6 us).  Not below
+// a wavefront, where CG's partial sums take a long loop (16 CG iterations at
+// N = 16, 8 threads against 32: FP32 616 / 505 us, FP64 694 / 564; N = 48, 16
+// against 64: 699 / 554).
 static int col_block_transforms(const FftPlan &f, size_t cbytes, int nbatch) {
     const int ct = ct_elems(f.N);
     const int threads = ct ? 1024 : fft_col_threads, E = ct ? ct : f.E;
@@ -566,7 +569,7 @@ static int col_block_transforms(const FftPlan &f, size_t cbytes, int nbatch) {
     Cb = std::max(1, std::min(Cb, 16));
     if (ct) {
         while (Cb & (Cb - 1)) Cb &= Cb - 1;  // a power of two: the block's sums halve it
-        while (Cb > 4 && (nbatch + Cb - 1) / Cb < 256) Cb /= 2;
+        while (Cb > 4 && Cb * (f.N / E) > 64 && (nbatch + Cb - 1) / Cb < 256) Cb /= 2;
     }
     return Cb;
 }
