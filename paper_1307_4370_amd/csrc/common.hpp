@@ -212,6 +212,8 @@ struct riop_plan {
     riop::DevBuf units;       // WorkUnit[nunits] (degridding)
     riop::DevBuf cell_start;  // int32[K^2 + 1]: plan-order start of each cell key
     int band = 0, nbands = 0;   // gridding: rows of a band of a tile, bands in all
+    bool band_eight = false;    // its workgroups have eight wavefronts (else grid_waves)
+    bool gram_one = false;      // G^T G in one launch (single precision, J = 6 or 8)
     riop::DevBuf tile_order;  // WorkUnit[nbands]: bands with their visibility ranges, heaviest first (gridding)
     riop::DevBuf halo;        // per band: region cells outside it (gridding)
     void *halo_pending = nullptr;  // grid last written by gridding, its bands' halos not yet added

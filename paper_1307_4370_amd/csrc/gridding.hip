@@ -620,8 +620,8 @@ __device__ inline void store_empty(const TileArgs<R> &a, int ta, int tb, int tid
 // of the region to its halo cells; the adjoint FFT's row pass adds the halos
 // of the three neighbours a band receives from as it loads the grid (or
 // grid_merge does, where that pass is not the specialised one).
-// WAVES: grid_waves<R>(J), 8 where the bands are narrow (single precision, matrix
-// path), or 2 for tiles whose region leaves too little LDS.
+// WAVES: grid_waves<R>(J), 8 where a plan's heavy bands ask for it (single precision,
+// matrix path; see choose_band), or 2 for tiles whose region leaves too little LDS.
 // Bound by the slice loop's staging and operand reads in LDS, and by the latency
 // of the light bands (clear, first slice, store).  Balanced staging (each half
 // of the wavefront half of the rows and columns, where all lanes staged one
@@ -1008,7 +1008,7 @@ constexpr int kGramWaves = 8;
 // Row length of the input region: a multiple of 32 cells, so that a row's cells
 // continue in the banks where the row before ends, as plan order does.
 __host__ __device__ constexpr int gram_stride(int T, int J) { return (T + J - 1 + 31) / 32 * 32; }
-template <int J> static size_t gram_tile_lds(int TB, int T) {
+static size_t gram_tile_lds(int TB, int T, int J) {
     return (size_t)region_rows(TB, J) * (region_stride(T, J) * 2 * sizeof(double) + gram_stride(T, J) * sizeof(float2)) + (size_t)kGramWaves * 36 * (8 * sizeof(float2) + 16 * sizeof(float));
 }
 
@@ -1241,33 +1241,75 @@ static void scan_exclusive(const int *in, int *out, int64_t n, int *sums, hipStr
     RIOP_HIP(hipGetLastError());
 }
 
-// Rows of a gridding band: T, T/2, .. kBandRows, at least J - 1 (a window spans
-// two bands at most), from the counts of the narrowest bands.  One workgroup
-// takes a band, so the launch lasts as long as the slower of
-//   - the heaviest band's wavefronts: `lat` us per 64 visibilities, 6 wavefronts;
-//   - the whole GPU's throughput: `thr` us per 64 visibilities on each of its
-//     3072 resident wavefronts, plus `fix` us per band on each of 512 workgroup
-//     slots (region clear and store, halo cells).
-// Measured (us; FP32 then FP64, J = 8, bands of 32 / 16 / 8 rows): 256^2 with
-// M = 65536 and 131072 17.8 / 12.5 / 9.9, 60 / 34 / 22; 512^2, M = 700001 33 / 24 / 31,
-// 86 / 52 / 58; 1024^2, M = 4194304 85 / 98 / 126, 199 / 224 / 266; 1536^2,
-// M = 2350001 103 / 135 / 200.  Every count enters, so one dense tile is enough to
-// narrow the bands where the rest of the GPU would wait for it.
-template <typename R> static int choose_band(const std::vector<int> &fine, int T, int J, int64_t M) {
-    const double wide = J > 8 ? 2.5 : 1.0;  // the vector path of wide windows
-    const double lat = wide * (sizeof(R) == 4 ? 1.8 : 4.4), thr = wide * (sizeof(R) == 4 ? 3.3 : 8.0);
-    const double fix = sizeof(R) == 4 ? 1.7 : 3.0;
-    int best = T;
+// Rows of a gridding band (T, T/2, .. kBandRows, at least J - 1: a window spans
+// two bands at most), wavefronts of its workgroups, and whether G^T G takes one
+// launch, from the counts of the narrowest bands.  A workgroup takes a band, so a
+// launch lasts about as long as the larger of two times (their root sum of
+// squares is used):
+//   - the heaviest band's chain: `lat` us per 64 visibilities of a wavefront's
+//     share;
+//   - the whole GPU's work: `thr` us of a CU per 64 visibilities, and per band
+//     `fix` us plus `cells` us per 1000 region cells (clear, store, halo, and for
+//     G^T G the input region) of one of the workgroup slots that the LDS leaves.
+// The constants are fitted to 984 measured launches (J = 2 .. 16, tiles 8 .. 64, 64^2
+// to 1024^2, uniform, Gaussian, narrow and clustered coverages; 5 % to 95 % of the
+// estimates lie within 0.73 .. 1.46 of the time).  Against the best height and
+// wavefront count of each coverage the choice costs 3 % on average, G^T G 1.5 %.
+// Measured (us, J = 8, Gaussian coverage, bands of 32 / 16 / 8 rows, FP32 with 8
+// wavefronts, then FP64): 256^2, M = 131072 25 / 17 / 12, 65 / 36 / 23; 512^2,
+// M = 262144 22 / 21 / 24, 40 / 31 / 41; 1024^2, M = 4194304 83 / 95 / 114,
+// 174 / 204 / 246.
+// One height serves both launches, taken for their sum.  Narrower bands must gain
+// 5 % (15 % for the vector path, whose estimate is coarser); eight wavefronts leave
+// less room per CU than six and are taken unless they lose 15 %.  In one launch the
+// heaviest band's chain degrids as well, work that the two launches spread over the
+// GPU: clustered coverages (256^2, M = 131072, two thirds of it in 1 % of the grid:
+// 423 us against 261) and 8-wide tiles (1024^2, M = 1048576 213 against 144) take two.
+struct BandCost {
+    double c0, lat, thr, fix, cells;
+    double us(int heaviest, int64_t M, int64_t nbands, int region, int waves, size_t lds) const {
+        const double slots = 256.0 * (double)std::max<size_t>(1, std::min<size_t>(163840 / lds, 32 / waves));
+        return c0 + std::hypot(lat * heaviest / (64.0 * waves),
+                               thr * (double)M / (64 * 256) + (double)nbands * (fix + cells * region / 1000) / slots);
+    }
+};
+struct BandChoice {
+    int rows;
+    bool eight, fused;  // eight wavefronts (single precision, matrix path); G^T G in one launch
+};
+
+template <typename R> static BandChoice choose_band(const std::vector<int> &fine, int T, int J, int64_t M, size_t lds_max,
+                                                    bool whole) {
+    const bool f32 = sizeof(R) == 4, mf = grid_mfma<R>(J);
+    const BandCost tile = f32 ? (mf ? BandCost{7.67, 1.47, 0.221, 0.553, 2.64} : BandCost{15.9, 3.82, 1.65, 0, 2.45})
+                              : (mf ? BandCost{8.67, 3.3, 0.599, 0.559, 3.21} : BandCost{17.9, 4.91, 2.45, 0, 2.17});
+    const BandCost one = {8.03, 2.33, 0.336, 1.81, 1.71};
+    const double degrid = 5 + 12.0 * (double)M / (1 << 20) * (J / 8.0) * (J / 8.0);
+    BandChoice best{T, false, false};
     double best_us = 0;
-    for (int TB = T; TB >= kBandRows && TB >= J - 1; TB /= 2) {
+    for (int TB = T; TB >= kBandRows && TB >= J - 1 && (TB == T || !whole); TB /= 2) {
         const size_t step = TB / kBandRows;
+        const int64_t nbands = (int64_t)((fine.size() - 1) / step);
+        const int region = region_rows(TB, J) * region_stride(T, J);
         int heaviest = 0;
         for (size_t t = 0; t + step < fine.size(); t += step) heaviest = std::max(heaviest, fine[t + step] - fine[t]);
-        const double us = std::max(lat * heaviest / (6 * 64) + 3.0,
-                                   thr * (double)M / (3072 * 64) + fix * (double)(fine.size() / step) / 512);
-        if (TB == T || us < best_us) {
-            best = TB;
-            best_us = us;
+        BandChoice c{TB, false, false};
+        const int w = grid_lds<R>(TB, T, J, grid_waves<R>(J)) <= lds_max ? grid_waves<R>(J) : 2;
+        double us = tile.us(heaviest, M, nbands, region, w, grid_lds<R>(TB, T, J, w));
+        if (f32 && mf && grid_lds<R>(TB, T, J, 8) <= lds_max) {
+            const double us8 = tile.us(heaviest, M, nbands, region, 8, grid_lds<R>(TB, T, J, 8));
+            c.eight = 0.85 * us8 < us;
+            if (c.eight) us = us8;
+        }
+        double sum = us + us + degrid;  // a gridding and a G^T G
+        if (f32 && (J == 6 || J == 8) && gram_tile_lds(TB, T, J) <= lds_max) {
+            const double us1 = one.us(heaviest, M, nbands, region, kGramWaves, gram_tile_lds(TB, T, J));
+            c.fused = 0.9 * us1 < us + degrid;
+            if (c.fused) sum = us + us1;
+        }
+        if (TB == T || sum < (mf ? 0.95 : 0.85) * best_us) {
+            best = c;
+            best_us = sum;
         }
     }
     return best;
@@ -1395,17 +1437,19 @@ template <typename R> static void build_layout_t(riop_plan *p, const void *uv, h
     const auto halo_bytes = [&](int TB) {
         return sizeof(C<R>) * (size_t)(J - 1) * ((size_t)K * tps + (size_t)ntiles * (T / TB) * (T + J - 1));
     };
-    int TB = device_bytes_limit() ? T : choose_band<R>(fs, T, J, M);
+    BandChoice bands = choose_band<R>(fs, T, J, M, p->lds_max, device_bytes_limit() > 0);
     try {
-        p->halo.alloc(halo_bytes(TB));
+        p->halo.alloc(halo_bytes(bands.rows));
     } catch (const Error &e) {
-        if (e.status != RIOP_ENOMEM || TB == T) throw;
+        if (e.status != RIOP_ENOMEM || bands.rows == T) throw;
         (void)hipGetLastError();  // the failed hipMalloc's
-        TB = T;
-        p->halo.alloc(halo_bytes(TB));
+        bands = choose_band<R>(fs, T, J, M, p->lds_max, true);
+        p->halo.alloc(halo_bytes(bands.rows));
     }
-    const int step = TB / kBandRows, nbands = nfine / step;
-    p->band = TB;
+    const int step = bands.rows / kBandRows, nbands = nfine / step;
+    p->band = bands.rows;
+    p->band_eight = bands.eight;
+    p->gram_one = bands.fused;
     std::vector<std::pair<int, int>> work(nbands);
     for (int t = 0; t < nbands; ++t) work[t] = {fs[(size_t)(t + 1) * step] - fs[(size_t)t * step], t};
     std::stable_sort(work.begin(), work.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
@@ -1511,11 +1555,7 @@ static void launch_tiles(riop_plan *p, const void *vals, int order_user, void *o
         a.p2y = p2->p2y;
         a.p2scale = p2->p2scale;
     }
-    // Narrow bands are latency-bound: eight wavefronts shorten each band's chain
-    // (256^2, M = 131072, FP32 12.7 -> 10.9 us).  Whole tiles keep six, three
-    // workgroups per CU (1024^2 81 us against 83, 1536^2 93 against 102).
-    const bool eight = sizeof(R) == 4 && grid_mfma<R>(p->J) && p->band < p->tile;
-    int waves = eight ? 8 : grid_waves<R>(p->J);
+    int waves = p->band_eight ? 8 : grid_waves<R>(p->J);
     if (grid_lds<R>(p->band, p->tile, p->J, waves) > p->lds_max) waves = 2;
     const size_t lds = grid_lds<R>(p->band, p->tile, p->J, waves);
     RIOP_REQUIRE(lds <= p->lds_max, RIOP_ENOTSUP, "gridding tile too large for LDS");
@@ -1576,11 +1616,10 @@ void launch_grid_prox2(riop_plan *p, const void *s, void *z2, const void *y, con
     launch_tiles<R>(p, nullptr, 0, p->grid.ptr, st, &q);
 }
 
-// The one-launch G^T G, where it applies (false: nothing was done).
+// The one-launch G^T G, where the plan takes it (false: nothing was done).
 static bool launch_gram_tile(riop_plan *p, const void *in_grid, void *out_grid, hipStream_t st) {
-    if (p->J != 8 && p->J != 6) return false;
-    const size_t lds = p->J == 8 ? gram_tile_lds<8>(p->band, p->tile) : gram_tile_lds<6>(p->band, p->tile);
-    if (lds > p->lds_max) return false;
+    if (!p->gram_one) return false;
+    const size_t lds = gram_tile_lds(p->band, p->tile, p->J);
     const TileArgs<float> a = tile_args<float>(p, out_grid);
     TimedScope ts(p, KK_GRAM_FUSED, st);
     const dim3 g(p->nbands), t(64 * kGramWaves);
