@@ -26,6 +26,8 @@ constexpr int kTO = 16;  // output tile side per sub-band (analysis) / half the 
 
 // Tiles of TO cover a band of `half`; the last of a row or column may be partial:
 // its region wraps as any other and its outputs past the band are dropped.
+// WHOLE kernels (TO = kTO) serve bands that the tiles divide: the tests for a
+// partial tile cost 3 % of the analysis and 1 % of the synthesis.
 __host__ __device__ constexpr int tiles_of(int half, int TO) { return (int)((unsigned)(half + TO - 1) / TO); }
 
 template <typename R> struct AnaArgs {
@@ -101,7 +103,7 @@ __device__ inline int wrap(int i, int s, bool tiny) {
     return i - (i >= s ? s : 0);
 }
 
-template <typename R, int TO, int NB>
+template <typename R, int TO, bool WHOLE, int NB>
 __device__ inline void ana_tile(const AnaArgs<R> &a, int bi, C<R> *smem) {
     constexpr int Lf = 2 * NB, IR = 2 * TO + Lf - 2, IRM = ana_region<TO>(), RS = ana_stride<TO>();
     constexpr int VL = TO < 4 ? TO : 4;  // outputs per thread along a row
@@ -124,10 +126,10 @@ __device__ inline void ana_tile(const AnaArgs<R> &a, int bi, C<R> *smem) {
     constexpr int kItems = 2 * (TO / VK) * TO;
     const int p = threadIdx.x / (kItems / 2), kq = threadIdx.x % (kItems / 2);
     const int k = (kq / TO) * VK, l = kq % TO;
-    const bool mine = threadIdx.x < kItems && l0 + l < half && k0 + k < half;
+    const bool mine = threadIdx.x < kItems && (WHOLE || (l0 + l < half && k0 + k < half));
     // Rows past the first are inside with it unless the band's side is odd.
     const bool odd = half & 1;
-    auto inside = [&](int v) { return v == 0 || !odd || k0 + k + v < half; };
+    auto inside = [&](int v) { return WHOLE || v == 0 || !odd || k0 + k + v < half; };
     const long base = (long)a.plane[bi] * n * n + (long)(k0 + k) * n + p * half + l0 + l;
     auto place = [&](int v, int t) { return base + (long)(v + t * half) * n; };
     C<R> zq[VK][2];
@@ -149,7 +151,7 @@ __device__ inline void ana_tile(const AnaArgs<R> &a, int bi, C<R> *smem) {
     {
         const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
         constexpr int RPT = (IR + 3) / 4;
-        const bool tiny = 2 * (tiles - 1) * TO + IR > 2 * s;
+        const bool tiny = WHOLE ? IR > s : 2 * (tiles - 1) * TO + IR > 2 * s;
         const unsigned gc = wrap(2 * l0 + min(tx, IR - 1), s, tiny);
         C<R> st[RPT];
 #pragma unroll
@@ -236,14 +238,27 @@ __device__ inline void dirac_coef(const AnaArgs<R> &a, long i, C<R> x, double &f
     emit_coef<R>(a, j, x, z, w, f1);
 }
 
-template <typename R, int TO> __global__ void __launch_bounds__(256) dwt_analysis(AnaArgs<R> a) {
+template <typename R, int TO, bool WHOLE> __global__ void __launch_bounds__(256) dwt_analysis(AnaArgs<R> a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     C<R> *smem = reinterpret_cast<C<R> *>(smem_raw);
     const int bi = blockIdx.y;
     if (bi == a.nbases) {  // level 1: the Dirac plane, alpha_0 = x / sqrt(q)
         if ((int)blockIdx.x >= a.dirac_blocks) return;
-        const long N = (long)a.n * a.n;
+        const int n = a.n, tiles = tiles_of(n >> 1, TO);
+        const long N = (long)n * n;
         double f1 = 0.0;
+        // A block per whole tile copies its tile, whose input the other bases read.
+        if (WHOLE && a.dirac_blocks == (int)gridDim.x) {
+            const int i0 = (blockIdx.x / tiles) * 2 * TO, j0 = (blockIdx.x % tiles) * 2 * TO;
+#pragma unroll
+            for (int u = 0; u < 4 * TO * TO / 256; ++u) {
+                const int e = threadIdx.x + 256 * u;
+                const long i = (long)(i0 + e / (2 * TO)) * n + j0 + e % (2 * TO);
+                dirac_coef<R>(a, i, a.in[i], f1);
+            }
+            if (a.prox) block_add_f1(f1, a.px.f1_part);
+            return;
+        }
         const long step = a.dirac_blocks * 256L;
         for (long i0 = (long)blockIdx.x * 256 + threadIdx.x; i0 < N; i0 += 4 * step) {
             C<R> x[4];
@@ -257,14 +272,14 @@ template <typename R, int TO> __global__ void __launch_bounds__(256) dwt_analysi
         return;
     }
     switch (a.basis[bi]) {
-        case 1: ana_tile<R, TO, 1>(a, bi, smem); break;
-        case 2: ana_tile<R, TO, 2>(a, bi, smem); break;
-        case 3: ana_tile<R, TO, 3>(a, bi, smem); break;
-        case 4: ana_tile<R, TO, 4>(a, bi, smem); break;
-        case 5: ana_tile<R, TO, 5>(a, bi, smem); break;
-        case 6: ana_tile<R, TO, 6>(a, bi, smem); break;
-        case 7: ana_tile<R, TO, 7>(a, bi, smem); break;
-        default: ana_tile<R, TO, 8>(a, bi, smem); break;
+        case 1: ana_tile<R, TO, WHOLE, 1>(a, bi, smem); break;
+        case 2: ana_tile<R, TO, WHOLE, 2>(a, bi, smem); break;
+        case 3: ana_tile<R, TO, WHOLE, 3>(a, bi, smem); break;
+        case 4: ana_tile<R, TO, WHOLE, 4>(a, bi, smem); break;
+        case 5: ana_tile<R, TO, WHOLE, 5>(a, bi, smem); break;
+        case 6: ana_tile<R, TO, WHOLE, 6>(a, bi, smem); break;
+        case 7: ana_tile<R, TO, WHOLE, 7>(a, bi, smem); break;
+        default: ana_tile<R, TO, WHOLE, 8>(a, bi, smem); break;
     }
 }
 
@@ -320,14 +335,14 @@ template <typename R> struct SynRegion {
     C<R> ll[3], lh[3], hl[3], hh[3];
 };
 
-template <typename R>
+template <typename R, bool WHOLE>
 __device__ inline void syn_load(const SynArgs<R> &a, int bi, int t, int i0, int j0, SynRegion<R> &v) {
     const int N = a.basis[bi], n = a.n, half = a.s >> 1, TO = a.TO, KR = TO + N - 1;
     const int c = t & 31, r0 = t >> 5;
     if (c >= KR) return;
     // The region starts at -7 at least and ends at half + TO - 2 at most: one period
     // either way is enough, but for tiny levels.
-    const bool tiny = half < kTO, last = max(i0, j0) / 2 + TO > half;
+    const bool tiny = half < (WHOLE ? kMaxTaps / 2 : kTO), last = !WHOLE && max(i0, j0) / 2 + TO > half;
     auto wrap_band = [&](int k) {
         if (tiny) return (k % half + half) % half;
         if (last) k -= k >= half ? half : 0;
@@ -464,14 +479,14 @@ __device__ inline void syn_rows(const R *filt, int t, const C<R> *smem, C<R> (&a
     }
 
 // Levels > 1: one basis per blockIdx.y, writes the finer LL slot.
-template <typename R, int TO> __global__ void __launch_bounds__(256) dwt_synthesis(SynArgs<R> a) {
+template <typename R, int TO, bool WHOLE> __global__ void __launch_bounds__(256) dwt_synthesis(SynArgs<R> a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     C<R> *smem = reinterpret_cast<C<R> *>(smem_raw);
     constexpr int TS = 2 * TO, NA = 2 * syn_pairs<TO>();
     const int bi = blockIdx.y, t = threadIdx.x, tiles = tiles_of(a.s, TS);
     const int i0 = (blockIdx.x / tiles) * TS, j0 = (blockIdx.x % tiles) * TS;
     SynRegion<R> v;
-    syn_load<R>(a, bi, t, i0, j0, v);
+    syn_load<R, WHOLE>(a, bi, t, i0, j0, v);
     syn_stage<R>(a, bi, t, v, smem);
     __syncthreads();
     SYN_BASES(syn_cols, a.basis[bi], a.filt, t, smem)
@@ -481,9 +496,9 @@ template <typename R, int TO> __global__ void __launch_bounds__(256) dwt_synthes
     for (int i = 0; i < NA; ++i) acc[i] = mk<R>(0, 0);
     SYN_BASES(syn_rows, a.basis[bi], a.filt, t, smem, acc)
     int ii, jj;
-    if (syn_place<TO>(t, ii, jj) && i0 + ii < a.s && j0 + jj < a.s) {
+    if (syn_place<TO>(t, ii, jj) && (WHOLE || (i0 + ii < a.s && j0 + jj < a.s))) {
         C<R> *out = a.ll_out + bi * a.ll_out_bstride + (long)(i0 + ii) * a.s + j0 + jj;
-        const bool odd = a.s & 2;  // else the NA columns are inside together
+        const bool odd = !WHOLE && (a.s & 2);  // else the NA columns are inside together
 #pragma unroll
         for (int i = 0; i < NA; ++i)
             if (i < 2 || !odd || j0 + jj + i < a.s) out[i] = acc[i];
@@ -493,7 +508,7 @@ template <typename R, int TO> __global__ void __launch_bounds__(256) dwt_synthes
 // Level 1: sum of all bases (and the Dirac plane) for one output tile.  Group g
 // takes bases g, 2 NG - 1 - g, 2 NG + g, ... (long and short filters in turn); the
 // next basis's regions load while the current one is filtered.
-template <typename R, int TO, int NG>
+template <typename R, int TO, bool WHOLE, int NG>
 __global__ void __launch_bounds__(256 * NG, sizeof(R) == 4 ? 4 : 2) dwt_synthesis_final(SynArgs<R> a) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     constexpr int TS = 2 * TO, NA = 2 * syn_pairs<TO>();
@@ -503,9 +518,9 @@ __global__ void __launch_bounds__(256 * NG, sizeof(R) == 4 ? 4 : 2) dwt_synthesi
     const int i0 = (blockIdx.x / tiles) * TS, j0 = (blockIdx.x % tiles) * TS;
     auto basis = [&](int step) { return step * NG + ((step & 1) ? NG - 1 - g : g); };
     int ii, jj;
-    const bool mine = syn_place<TO>(t, ii, jj) && i0 + ii < n && j0 + jj < n;
+    const bool mine = syn_place<TO>(t, ii, jj) && (WHOLE || (i0 + ii < n && j0 + jj < n));
     const long o = (long)(i0 + ii) * n + j0 + jj;
-    const bool odd = n & 2;  // else the NA columns are inside together
+    const bool odd = !WHOLE && (n & 2);  // else the NA columns are inside together
     auto inside = [&](int i) { return i < 2 || !odd || j0 + jj + i < n; };
     C<R> acc[NA], dirac[NA];
 #pragma unroll
@@ -520,14 +535,14 @@ __global__ void __launch_bounds__(256 * NG, sizeof(R) == 4 ? 4 : 2) dwt_synthesi
         if (a.flag) fc.report(a.flag);
     }
     SynRegion<R> v;
-    if (basis(0) < a.nbases) syn_load<R>(a, basis(0), t, i0, j0, v);
+    if (basis(0) < a.nbases) syn_load<R, WHOLE>(a, basis(0), t, i0, j0, v);
     const int steps = (a.nbases + NG - 1) / NG;
     for (int step = 0; step < steps; ++step) {
         const int bi = basis(step), bn = basis(step + 1);
         const bool on = bi < a.nbases;
         __syncthreads();  // the previous basis's readers are done
         if (on) syn_stage<R>(a, bi, t, v, smem);
-        if (bn < a.nbases) syn_load<R>(a, bn, t, i0, j0, v);
+        if (bn < a.nbases) syn_load<R, WHOLE>(a, bn, t, i0, j0, v);
         __syncthreads();
         if (on) SYN_BASES(syn_cols, a.basis[bi], a.filt, t, smem)
         __syncthreads();
@@ -621,23 +636,25 @@ template <typename R> static int syn_groups(int tiles) {
     return tiles >= 1024 ? 1 : tiles >= 512 ? 2 : 4;
 }
 
-template <typename R, int TO>
+template <typename R, int TO, bool WHOLE>
 static void launch_synthesis(const SynArgs<R> &a, int nb, bool final_level, hipStream_t st) {
     const int tiles = tiles_of(a.s >> 1, TO), blocks = tiles * tiles;
     const size_t lds = sizeof(C<R>) * (size_t)syn_cells<TO>();
     if (!final_level) {
-        hipLaunchKernelGGL((dwt_synthesis<R, TO>), dim3(blocks, nb), dim3(256), lds, st, a);
+        hipLaunchKernelGGL((dwt_synthesis<R, TO, WHOLE>), dim3(blocks, nb), dim3(256), lds, st, a);
         return;
     }
+#define FINAL(NG) \
+    hipLaunchKernelGGL((dwt_synthesis_final<R, TO, WHOLE, NG>), dim3(blocks), dim3(256 * NG), NG * lds, st, a)
     switch (TO < 16 ? 1 : syn_groups<R>(blocks)) {
-        case 1: hipLaunchKernelGGL((dwt_synthesis_final<R, TO, 1>), dim3(blocks), dim3(256), lds, st, a); break;
+        case 1: FINAL(1); break;
         case 2:
-            if constexpr (TO == 16) hipLaunchKernelGGL((dwt_synthesis_final<R, TO, 2>), dim3(blocks), dim3(512), 2 * lds, st, a);
+            if constexpr (TO == 16) FINAL(2);
             break;
         default:
-            if constexpr (TO == 16 && sizeof(R) == 4)
-                hipLaunchKernelGGL((dwt_synthesis_final<R, TO, 4>), dim3(blocks), dim3(1024), 4 * lds, st, a);
+            if constexpr (TO == 16 && sizeof(R) == 4) FINAL(4);
     }
+#undef FINAL
 }
 
 template <typename R>
@@ -687,11 +704,16 @@ static void psi_adj_impl(riop_plan *p, const void *x, void *alpha, const Prox1<R
         a.dirac_blocks = lev == 1 && a.dirac_plane >= 0 ? dirac_row_blocks(n) : 0;
         const dim3 grid(tiles * tiles, nb + (a.dirac_blocks > 0 ? 1 : 0));
         switch (a.TO) {
-#define ANA(T)                                                                                           \
-    case T: hipLaunchKernelGGL((dwt_analysis<R, T>), grid, dim3(256), (ana_lds<R, T>()), st, a); break;
-            ANA(16) ANA(8) ANA(4) ANA(2)
+#define ANA(T, WHOLE) hipLaunchKernelGGL((dwt_analysis<R, T, WHOLE>), grid, dim3(256), (ana_lds<R, T>()), st, a)
+            case kTO:
+                if (half % kTO == 0) ANA(kTO, true);
+                else ANA(kTO, false);
+                break;
+            case 8: ANA(8, false); break;
+            case 4: ANA(4, false); break;
+            case 2: ANA(2, false); break;
+            default: ANA(1, false); break;
 #undef ANA
-            default: hipLaunchKernelGGL((dwt_analysis<R, 1>), grid, dim3(256), (ana_lds<R, 1>()), st, a); break;
         }
         RIOP_HIP(hipGetLastError());
         a.px.f1_part += a.prox ? (long)tiles * tiles * nb + a.dirac_blocks : 0;
@@ -750,11 +772,14 @@ template <typename R> void launch_psi(riop_plan *p, const void *alpha, void *x, 
             a.ll_out_bstride = (long)p->ll_stride;
         }
         switch (a.TO) {
-            case 16: launch_synthesis<R, 16>(a, nb, lev == 1, st); break;
-            case 8: launch_synthesis<R, 8>(a, nb, lev == 1, st); break;
-            case 4: launch_synthesis<R, 4>(a, nb, lev == 1, st); break;
-            case 2: launch_synthesis<R, 2>(a, nb, lev == 1, st); break;
-            default: launch_synthesis<R, 1>(a, nb, lev == 1, st); break;
+            case kTO:
+                if (half % kTO == 0) launch_synthesis<R, kTO, true>(a, nb, lev == 1, st);
+                else launch_synthesis<R, kTO, false>(a, nb, lev == 1, st);
+                break;
+            case 8: launch_synthesis<R, 8, false>(a, nb, lev == 1, st); break;
+            case 4: launch_synthesis<R, 4, false>(a, nb, lev == 1, st); break;
+            case 2: launch_synthesis<R, 2, false>(a, nb, lev == 1, st); break;
+            default: launch_synthesis<R, 1, false>(a, nb, lev == 1, st); break;
         }
         RIOP_HIP(hipGetLastError());
     }
