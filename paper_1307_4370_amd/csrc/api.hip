@@ -549,7 +549,6 @@ riop_status riop_gram_build(riop_plan *p, void *stream) {
     return guarded([&] {
         check_plan(p);
         p->gram.release();
-        p->gram_nplanes = 0;
         gram_build_plan(p, S(stream));
         mark_done(p, S(stream));
     });
@@ -560,7 +559,6 @@ riop_status riop_gram_release(riop_plan *p) {
         check_plan(p);
         if (p->done) RIOP_HIP(hipEventSynchronize(p->done));
         p->gram.release();
-        p->gram_nplanes = 0;
     });
 }
 

@@ -247,7 +247,6 @@ struct riop_plan {
     // Precomputed Gram operator G^T G (optional): K^2 values of the plan's real
     // type per offset of the half set, interleaved by row chunks (gram.hip).
     riop::DevBuf gram;
-    int gram_nplanes = 0;
 
     riop::SdmmWork sd;
     riop::Timing timing;

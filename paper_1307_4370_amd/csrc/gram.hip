@@ -266,7 +266,6 @@ template <typename R> static void gram_build_t(riop_plan *p, hipStream_t st) {
                        K, gram_chunk(K), np_);
     RIOP_HIP(hipGetLastError());
     RIOP_HIP(hipStreamSynchronize(st));  // the temporaries go out of scope
-    p->gram_nplanes = np_;
 }
 
 void gram_build_plan(riop_plan *p, hipStream_t st) {

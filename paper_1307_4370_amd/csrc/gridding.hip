@@ -10,8 +10,9 @@
 // (key = tile * T^2 + local row * T + local col).
 //
 // Degridding (G): one workgroup per work unit (a tile and a chunk of its
-// visibilities) stages the (T + J - 1)^2 grid region its windows can touch in
-// LDS, then each thread interpolates one visibility at a time from LDS.
+// visibilities) or per part of one stages the (T + J - 1)^2 grid region its
+// windows can touch in LDS, then each thread interpolates one visibility at a
+// time from LDS.
 // Neighbouring threads hold neighbouring cells, which keeps LDS bank conflicts
 // low.
 //
@@ -24,9 +25,9 @@
 // 8-aligned column block are summed in registers, on the matrix cores where
 // possible, and closed with LDS double atomic adds: floating-point LDS
 // atomics in single precision are slow on this GPU), then stores its own
-// cells to the grid and the rest to its halo cells; a second kernel adds each
-// band's three incoming halos.  No zeroing of the grid, no global atomics,
-// and every visibility is read once.
+// cells to the grid and the rest to its halo cells; the adjoint FFT's row pass
+// (or grid_merge) adds each band's three incoming halos.  No zeroing of the grid,
+// no global atomics, and every visibility is read once.
 //
 // Kernel weights: for tap j the weight phi(rho + J/2 - 1 - j) is a polynomial
 // in s = 2 rho - 1 fitted at plan time; phi is even, so taps j and J-1-j share
@@ -476,7 +477,7 @@ __device__ inline float sum_halves(float a) {
 // otherwise (one lane per entry).
 template <typename R> __host__ __device__ constexpr int slice_len(int J) { return grid_mfma<R>(J) ? 32 : 64; }
 template <typename R> __host__ __device__ constexpr int slice_row(int J) {
-    return grid_mfma<R>(J) ? (slice_len<R>(J) == 32 ? 36 : 68) : 65;
+    return grid_mfma<R>(J) ? 36 : 65;
 }
 
 // LDS bytes of one wavefront's staging area.
@@ -596,13 +597,15 @@ __device__ inline void store_empty(const TileArgs<R> &a, int ta, int tb, int tid
 }
 
 // A band's visibilities are one contiguous plan-order range; its wavefronts
-// take equal contiguous shares of it and work independently, at most 64
-// visibilities (a slice) at a time.
+// take equal contiguous shares of it and work independently, a slice (32
+// visibilities on the matrix path, 64 on the vector path) at a time.
 //
-// Staging: lane t of the wavefront takes visibility t of the slice and writes
-// its J row weights times the value, and its J column weights shifted by the
-// window's column offset inside an 8-aligned column block (zeros around them),
-// to the wavefront's own LDS area.
+// Staging: a visibility's J row weights times its value, and its J column
+// weights shifted by the window's column offset inside an 8-aligned column block
+// (zeros around them), go to the wavefront's own LDS area.  Vector path: lane t
+// stages visibility t.  Matrix path: lanes t and t + 32 each form the weights of
+// one axis of visibility t, swap, and stage half of its rows and half of its
+// columns.
 //
 // Accumulation: the wavefront walks the slice one visibility per step.  In
 // plan order, visibilities of one window row and one column block are
@@ -806,8 +809,8 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
                 swap_halves(val.y, upper.y);
             }
         }
-        // Staging.  Lanes past the end stage zero values, so the
-        // accumulation below runs over all 64 entries without bound tests.
+        // Staging.  Lanes past the end stage zero values, so the accumulation
+        // below needs no bound tests inside a group of four entries.
         if (!live) val = mk<R>(0, 0);
         if (!P2 && a.flag) fc.add(val);
         const int la = (int)(cv & 0xffffu) - ta, lb = (int)(cv >> 16) - tb;  // in [0, T)
@@ -1005,6 +1008,7 @@ __global__ void __launch_bounds__(64 * WAVES) grid_tile(TileArgs<R> a) {
 // region, 129 registers) the same kernel takes 29, 70, 351 us at 256^2, 512^2,
 // 1024^2 against 31, 72, 294 us in two launches; those stay two.
 constexpr int kGramWaves = 8;
+constexpr int kInputRows = 5;  // region rows per wavefront: bands of up to 32 rows, 39 with the halo
 // Row length of the input region: a multiple of 32 cells, so that a row's cells
 // continue in the banks where the row before ends, as plan order does.
 __host__ __device__ constexpr int gram_stride(int T, int J) { return (T + J - 1 + 31) / 32 * 32; }
@@ -1043,37 +1047,35 @@ template <int J> __global__ void __launch_bounds__(64 * kGramWaves, 4) gram_tile
         }
     };
     load(f_begin + e);
-    // Input region, rows by wavefront; the first kRows rows of a wavefront (all
-    // of them up to 32 x 32 tiles) are in flight while the output region is cleared.
-    constexpr int kRows = 5, kStep = kRows * kGramWaves;
+    // Input region, rows by wavefront (host side: at most kInputRows of them each);
+    // the first 64 columns are in flight while the output region is cleared.
     const int W = T + J - 1;
-    float2 g[kRows];
-    auto fetch = [&](int i0, int j) {
+    float2 g[kInputRows];
+    auto fetch = [&](int j) {
         int gj = tb + j;
         if (gj >= K) gj -= K;
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) {
-            int gi = ta + min(i0 + r * kGramWaves, RR - 1);
+        for (int r = 0; r < kInputRows; ++r) {
+            int gi = ta + min(wave + r * kGramWaves, RR - 1);
             if (gi >= K) gi -= K;
             g[r] = gin[(int64_t)gi * K + gj];
         }
     };
-    auto put = [&](int i0, int j) {
+    auto put = [&](int j) {
 #pragma unroll
-        for (int r = 0; r < kRows; ++r)
-            if (i0 + r * kGramWaves < RR) reg[(i0 + r * kGramWaves) * GS + j] = g[r];
+        for (int r = 0; r < kInputRows; ++r)
+            if (wave + r * kGramWaves < RR) reg[(wave + r * kGramWaves) * GS + j] = g[r];
     };
-    fetch(wave, min(lane, W - 1));
+    fetch(min(lane, W - 1));
     {
         double2 *t2 = reinterpret_cast<double2 *>(tre);
         for (int c = tid; c < PS; c += kThreads) t2[c] = make_double2(0.0, 0.0);
     }
-    if (lane < W) put(wave, lane);
-    for (int j = lane; j < W; j += 64)
-        for (int i0 = wave + (j == lane ? kStep : 0); i0 < RR; i0 += kStep) {
-            fetch(i0, j);
-            put(i0, j);
-        }
+    if (lane < W) put(lane);
+    for (int j = lane + 64; j < W; j += 64) {
+        fetch(j);
+        put(j);
+    }
     // Row-weight rows J .. 7 are never staged and stay zero.
     for (int i = J * SR + lane; i < 8 * SR; i += 64) wuv[i] = make_float2(0.f, 0.f);
     __syncthreads();
@@ -1302,7 +1304,9 @@ template <typename R> static BandChoice choose_band(const std::vector<int> &fine
             if (c.eight) us = us8;
         }
         double sum = us + us + degrid;  // a gridding and a G^T G
-        if (f32 && (J == 6 || J == 8) && gram_tile_lds(TB, T, J) <= lds_max) {
+        // (64-row bands need more LDS than there is.)
+        if (f32 && (J == 6 || J == 8) && gram_tile_lds(TB, T, J) <= lds_max &&
+            region_rows(TB, J) <= kInputRows * kGramWaves) {
             const double us1 = one.us(heaviest, M, nbands, region, kGramWaves, gram_tile_lds(TB, T, J));
             c.fused = 0.9 * us1 < us + degrid;
             if (c.fused) sum = us + us1;
@@ -1619,6 +1623,7 @@ void launch_grid_prox2(riop_plan *p, const void *s, void *z2, const void *y, con
 // The one-launch G^T G, where the plan takes it (false: nothing was done).
 static bool launch_gram_tile(riop_plan *p, const void *in_grid, void *out_grid, hipStream_t st) {
     if (!p->gram_one) return false;
+    RIOP_REQUIRE(region_rows(p->band, p->J) <= kInputRows * kGramWaves, RIOP_EDEVICE, "band too high for the fused G^T G");
     const size_t lds = gram_tile_lds(p->band, p->tile, p->J);
     const TileArgs<float> a = tile_args<float>(p, out_grid);
     TimedScope ts(p, KK_GRAM_FUSED, st);

@@ -785,7 +785,6 @@ template <typename R> void launch_psi(riop_plan *p, const void *alpha, void *x, 
     }
 }
 
-// Daubechies filters for the device, built on the host (see plan.cpp).
 template void launch_psi_adj<float>(riop_plan *, const void *, void *, hipStream_t, int *);
 template void launch_psi_adj<double>(riop_plan *, const void *, void *, hipStream_t, int *);
 template void launch_psi<float>(riop_plan *, const void *, void *, hipStream_t, int *);
