@@ -7,6 +7,9 @@ grid whose halos the adjoint row pass adds (a power of two), that have their own
 kernel (72 = 2^3 9), and with the l2-ball prox fused in (one SDMM iteration).
 Tolerances: relative L2 of 1e-5 (FP32) and 1e-12 (FP64), as for the operators;
 10 times that for the SDMM iterate (CG, condition number below 10).
+Which height and which form of G^T G a coverage takes follows the library's cost
+rule; test_gpu_band_choice.py asserts both, with coverages that reach every height
+and the two launches.
 """
 import math
 

@@ -7,6 +7,8 @@ sums ride on the column passes (halos are added by the row pass where it can).
 Tolerances: the operators' relative L2 of 1e-5 (FP32) and 1e-12 (FP64); CG
 solves a system of condition number at most (||Phi||^2 + 2) / 2 < 10 here, so
 its iterate is held to 10 times that.
+Of the families' largest lengths K = 2048 and K = 3072 are in test_gpu_fft_large.py,
+K = 6144 in test_gpu_limits.py.
 """
 import numpy as np
 import pytest
