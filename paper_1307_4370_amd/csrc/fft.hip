@@ -135,7 +135,7 @@ template <typename R, int SGN> struct Dft<R, 12, SGN> {
 
 // One Stockham stage of radix RR on the thread's E registers (radix 12
 // only as a first stage, Ns = 1, which has no twiddles).
-template <typename R, int E, int RR, int SGN>
+template <typename R, int E, int RR, int SGN, bool TABLE = false>
 __device__ inline void stage(C<R> (&v)[E], int jt, int NE, int N, int Ns, const C<R> *tw) {
     constexpr int B = E / RR;
 #pragma unroll
@@ -148,12 +148,14 @@ __device__ inline void stage(C<R> (&v)[E], int jt, int NE, int N, int Ns, const 
         if (RR <= 8 && Ns > 1) {
             // One table twiddle per butterfly, w = exp(SGN 2 pi i k / (Ns RR));
             // the others are its powers (products at most three deep), which
-            // spares the memory pipeline RR - 2 gathers per butterfly.
+            // spares the memory pipeline RR - 2 gathers per butterfly.  TABLE:
+            // all from the table.
             C<R> w[RR];
-            w[1] = tw[k * (N / (Ns * RR))];
-            if (SGN > 0) w[1].y = -w[1].y;
-            if constexpr (RR > 2) w[2] = cmul<R>(w[1], w[1]);
-            if constexpr (RR > 3) w[3] = cmul<R>(w[2], w[1]);
+            const int step = k * (N / (Ns * RR));
+            auto twiddle = [&](int i) { return SGN > 0 ? mk<R>(tw[i].x, -tw[i].y) : tw[i]; };
+            w[1] = twiddle(step);
+            if constexpr (RR > 2) w[2] = TABLE ? twiddle(2 * step) : cmul<R>(w[1], w[1]);
+            if constexpr (RR > 3) w[3] = TABLE ? twiddle(3 * step) : cmul<R>(w[2], w[1]);
             if constexpr (RR > 4) {
                 w[4] = cmul<R>(w[2], w[2]);
                 w[5] = cmul<R>(w[4], w[1]);
@@ -315,6 +317,10 @@ __global__ void __launch_bounds__(COLS ? fft_col_threads : 256, COLS ? 1 : 2) ff
 // single precision its four passes took 47 / 132 us against 36 / 124 us.  The
 // generic kernel above took 90 / 312 us there: its stage radix, and with it
 // every index of the 24 elements, is a run-time value.
+// At N = 48 and 96 all twiddles come from the table: with two or three stages the
+// products' rounding is a large part of the error (FP32, J = 6, against 64 bits,
+// the generic kernel / products / table: Phi^dagger at N = 48 1.27e-7 / 1.41e-7 /
+// 1.29e-7, at N = 96 1.37e-7 / 1.41e-7 / 1.33e-7; same times).
 // What bounds the passes: latency (load, exchanges and store of a block run
 // back to back) at small N, at large N the 32 B column pieces and HBM.
 
@@ -325,7 +331,7 @@ template <int N, int E, int Ns> __host__ __device__ constexpr int ct_radix() {
 template <typename R, int E, int SGN, int N, int Ns>
 __device__ inline void ct_stages(C<R> (&v)[E], int jt, C<R> *lds, int ls, const C<R> *tw) {
     constexpr int RR = ct_radix<N, E, Ns>(), NE = N / E;
-    stage<R, E, RR, SGN>(v, jt, NE, N, Ns, tw);
+    stage<R, E, RR, SGN, E == 12 && N <= 96>(v, jt, NE, N, Ns, tw);
     if constexpr (Ns * RR < N) {
         exchange<R, E, N % 32 ? 0 : E == 12 ? 2 : 3>(v, lds, ls, jt, NE, Ns, RR);
         ct_stages<R, E, SGN, N, Ns * RR>(v, jt, lds, ls, tw);
