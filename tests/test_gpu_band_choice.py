@@ -28,12 +28,14 @@ def _uv(n, M, kind):
 
 
 @pytest.mark.parametrize("prec,n,M,J,tile,kind,rows,launches", [
-    ("f32", 128, 20000, 8, 32, "uniform", 32, 1), ("f32", 128, 20000, 6, 32, "uniform", 32, 1),
-    ("f32", 128, 3000, 8, 32, "gauss", 16, 1), ("f32", 128, 20000, 8, 32, "gauss", 8, 1),
+    ("f32", 256, 20000, 8, 32, "uniform", 32, 1), ("f32", 256, 20000, 6, 32, "uniform", 32, 1),
+    ("f32", 256, 20000, 12, 32, "uniform", 32, 2), ("f32", 256, 20000, 8, 32, "gauss", 16, 1),
+    ("f32", 128, 20000, 8, 32, "uniform", 16, 1), ("f32", 128, 20000, 6, 32, "uniform", 8, 1),
+    ("f32", 128, 3000, 8, 32, "gauss", 8, 1), ("f32", 128, 20000, 8, 32, "gauss", 8, 1),
     ("f32", 128, 20000, 8, 32, "cluster", 8, 2), ("f32", 128, 20000, 6, 32, "cluster", 8, 2),
-    ("f32", 64, 600, 8, 64, "uniform", 32, 1), ("f32", 256, 30000, 8, 8, "uniform", 8, 2),
-    ("f32", 128, 9000, 12, 32, "uniform", 32, 2), ("f32", 128, 9000, 12, 32, "gauss", 16, 2),
-    ("f64", 256, 20000, 8, 32, "uniform", 32, 2), ("f64", 128, 20000, 6, 32, "uniform", 16, 2),
+    ("f32", 64, 600, 8, 64, "uniform", 8, 1), ("f32", 256, 30000, 8, 8, "uniform", 8, 2),
+    ("f32", 128, 9000, 12, 32, "uniform", 16, 2), ("f32", 128, 9000, 12, 32, "gauss", 16, 2),
+    ("f64", 256, 20000, 8, 32, "uniform", 32, 2), ("f64", 128, 20000, 6, 32, "uniform", 8, 2),
     ("f64", 128, 20000, 8, 32, "gauss", 8, 2), ("f64", 128, 9000, 12, 32, "gauss", 16, 2),
 ])
 def test_band_choice(prec, n, M, J, tile, kind, rows, launches, monkeypatch):
