@@ -26,8 +26,8 @@ constexpr int kTO = 16;  // output tile side per sub-band (analysis) / half the 
 
 // Tiles of TO cover a band of `half`; the last of a row or column may be partial:
 // its region wraps as any other and its outputs past the band are dropped.
-// WHOLE kernels (TO = kTO) serve bands that the tiles divide: the tests for a
-// partial tile cost 3 % of the analysis and 1 % of the synthesis.
+// WHOLE kernels serve bands that the tiles divide: the tests for a partial tile
+// cost 3 % of the analysis and 1 % of the synthesis.
 __host__ __device__ constexpr int tiles_of(int half, int TO) { return (int)((unsigned)(half + TO - 1) / TO); }
 
 template <typename R> struct AnaArgs {
@@ -251,8 +251,9 @@ template <typename R, int TO, bool WHOLE> __global__ void __launch_bounds__(256)
         if (WHOLE && a.dirac_blocks == (int)gridDim.x) {
             const int i0 = (blockIdx.x / tiles) * 2 * TO, j0 = (blockIdx.x % tiles) * 2 * TO;
 #pragma unroll
-            for (int u = 0; u < 4 * TO * TO / 256; ++u) {
+            for (int u = 0; u < (4 * TO * TO + 255) / 256; ++u) {
                 const int e = threadIdx.x + 256 * u;
+                if (e >= 4 * TO * TO) break;
                 const long i = (long)(i0 + e / (2 * TO)) * n + j0 + e % (2 * TO);
                 dirac_coef<R>(a, i, a.in[i], f1);
             }
@@ -583,16 +584,43 @@ template <typename R> __global__ void dirac_only_synthesis(SynArgs<R> a, long N)
 // ---------------------------------------------------------------------------
 // Host side.
 
-// Tile side: kTO, or the power of two that covers a smaller band.  Tiles that divide
-// the band instead hold few samples where its side has few factors of 2, and most
-// of a block's threads then have nothing to do: 9 bases, one level, FP32 / FP64,
-// dividing -> covering tiles: 972^2 (band 486, tiles of 2) analysis 719 -> 33 us /
-// 1300 -> 64, synthesis 960 -> 48 / 1900 -> 78; 216^2 (108, tiles of 4) 16 -> 9 / 24 -> 9
-// and 24 -> 15 / 37 -> 21.
-static int tile_side(int half) {
+// Tile side: the smallest power of two whose tiles over `rows` bases are at most
+// `blocks`, up to kTO and the one that covers the band.  Small tiles have the
+// shorter chain while their blocks are all in flight, large ones the least overlap
+// and the fewest idle threads; tiles that divide the band (the rule before) have
+// neither where its side has few factors of 2: 9 bases, one level, FP32 / FP64, 972^2
+// (band 486, tiles of 2 -> 16) analysis 719 -> 33 us / 1300 -> 64, synthesis
+// 960 -> 48 / 1900 -> 78; 216^2 (108, tiles of 4 -> 16) 16 -> 9 / 24 -> 9 and 24 -> 15 / 37 -> 21.
+static int tile_side(int half, int rows, int blocks) {
     int TO = 1;
-    while (TO < kTO && TO < half) TO *= 2;
+    while (TO < kTO && TO < half && (long)tiles_of(half, TO) * tiles_of(half, TO) * rows > blocks) TO *= 2;
     return TO;
+}
+
+// Two blocks per CU.  Analysis, 8 bases, tiles of 8 / 16, FP32 and FP64: bands of 36 (200 blocks of
+// 8) 6.3 / 6.9 us and 6.5 / 7.2, of 64 (512) 6.4 / 6.6 and 6.8 / 7.1, of 96 (1152)
+// 7.4 / 7.1 and 9.6 / 8.0; one basis, tiles of 4 / 16: 48 (144) 6.3 / 6.8 and 6.4 / 7.2.
+static int level_tile(int half, int nb) { return tile_side(half, nb, 512); }
+
+// The analysis of many bases keeps the side of its first level where that divides
+// the band: every side is another kernel, whose code (a path per basis) is cold where
+// the levels above run other tiles (512^2, 4 levels, 8 bases, FP64, tiles of 8 and 4 on
+// the last two levels 42.2 -> 46.4 us, 1024^2 of 8 on the last one 98.9 -> 101).  With
+// one basis the smaller tiles are still faster (576^2, 6 levels 45.4 -> 42.5).
+static int analysis_tile(int n, int half, int nb) {
+    const int first = level_tile(n >> 1, nb);
+    return nb > 3 && half % first == 0 ? first : level_tile(half, nb);
+}
+
+// The last synthesis level sums all bases in a block, so blocks are fewer and longer.
+// FP64, 8 bases, tiles of 1 / 2 / 4 / 8 / 16: bands of 12 15.1 / 19.3 / 19.1 / 22.0 / 20.7
+// us, of 32 27.9 / 17.8 / 18.9 / 20.1 / 19.8, of 128 (256 tiles of 8) - / - / 36.5 / 19.5 /
+// 20.3, of 144 (324) - / - / 54.8 / 24.6 / 21.8.  In FP32 tiles of kTO share the bases among
+// four groups, which pays from two bases on: 48 13.8 us, 17.2 with tiles of 4 (one
+// basis 8.0, 6.6).
+template <typename R> static int final_tile(int half, int nb) {
+    const bool groups = sizeof(R) == 4 && nb > 1 && 2 * half > kTO;
+    return groups ? kTO : tile_side(half, 1, 256);
 }
 
 static size_t ll_offset(int n, int level) {
@@ -609,17 +637,17 @@ static int dirac_blocks(int n) { return (int)std::min<long>(((long)n * n + 255) 
 
 // Blocks of level 1 that copy the Dirac plane: one per tile, but where the tiles
 // are small no more than have 256 pixels each (every block has a partial of f1).
-static int dirac_row_blocks(int n) {
-    const int tiles = tiles_of(n >> 1, tile_side(n >> 1));
+static int dirac_row_blocks(int n, int nb) {
+    const int tiles = tiles_of(n >> 1, level_tile(n >> 1, nb));
     return std::min(tiles * tiles, dirac_blocks(n));
 }
 
 int psi_adj_blocks(const riop_plan *p) {
     const int n = p->n, dirac = p->mask & 1, nb = p->q - dirac;
     if (nb == 0) return dirac_blocks(n);
-    int total = dirac ? dirac_row_blocks(n) : 0;
+    int total = dirac ? dirac_row_blocks(n, nb) : 0;
     for (int lev = 1; lev <= p->L; ++lev) {
-        const int half = (n >> (lev - 1)) >> 1, tiles = tiles_of(half, tile_side(half));
+        const int half = (n >> (lev - 1)) >> 1, tiles = tiles_of(half, analysis_tile(n, half, nb));
         total += tiles * tiles * nb;
     }
     return total;
@@ -690,7 +718,7 @@ static void psi_adj_impl(riop_plan *p, const void *x, void *alpha, const Prox1<R
     for (int lev = 1; lev <= L; ++lev) {
         const int s = n >> (lev - 1), half = s >> 1;
         a.s = s;
-        a.TO = tile_side(half);
+        a.TO = analysis_tile(n, half, nb);
         a.last = lev == L;
         if (lev > 1) {
             a.in = ll + ll_offset(n, lev - 1);
@@ -701,18 +729,18 @@ static void psi_adj_impl(riop_plan *p, const void *x, void *alpha, const Prox1<R
         a.ll_bstride = (long)p->ll_stride;
         const int tiles = tiles_of(half, a.TO);
         TimedScope ts(p, KK_PSI_ADJ, st);
-        a.dirac_blocks = lev == 1 && a.dirac_plane >= 0 ? dirac_row_blocks(n) : 0;
+        a.dirac_blocks = lev == 1 && a.dirac_plane >= 0 ? dirac_row_blocks(n, nb) : 0;
         const dim3 grid(tiles * tiles, nb + (a.dirac_blocks > 0 ? 1 : 0));
         switch (a.TO) {
 #define ANA(T, WHOLE) hipLaunchKernelGGL((dwt_analysis<R, T, WHOLE>), grid, dim3(256), (ana_lds<R, T>()), st, a)
-            case kTO:
-                if (half % kTO == 0) ANA(kTO, true);
-                else ANA(kTO, false);
-                break;
-            case 8: ANA(8, false); break;
-            case 4: ANA(4, false); break;
-            case 2: ANA(2, false); break;
-            default: ANA(1, false); break;
+#define ANA_TILE(T)                      \
+    case T:                              \
+        if (half % T == 0) ANA(T, true); \
+        else ANA(T, false);              \
+        break;
+            ANA_TILE(16) ANA_TILE(8) ANA_TILE(4) ANA_TILE(2)
+            default: ANA(1, true);
+#undef ANA_TILE
 #undef ANA
         }
         RIOP_HIP(hipGetLastError());
@@ -762,7 +790,7 @@ template <typename R> void launch_psi(riop_plan *p, const void *alpha, void *x, 
     for (int lev = L; lev >= 1; --lev) {
         const int s = n >> (lev - 1), half = s >> 1;
         a.s = s;
-        a.TO = tile_side(half);
+        a.TO = lev == 1 ? final_tile<R>(half, nb) : level_tile(half, nb);
         a.coarsest = lev == L;
         a.ll_in = a.coarsest ? nullptr : ll + ll_offset(n, lev);
         a.ll_in_bstride = (long)p->ll_stride;
@@ -772,14 +800,14 @@ template <typename R> void launch_psi(riop_plan *p, const void *alpha, void *x, 
             a.ll_out_bstride = (long)p->ll_stride;
         }
         switch (a.TO) {
-            case kTO:
-                if (half % kTO == 0) launch_synthesis<R, kTO, true>(a, nb, lev == 1, st);
-                else launch_synthesis<R, kTO, false>(a, nb, lev == 1, st);
-                break;
-            case 8: launch_synthesis<R, 8, false>(a, nb, lev == 1, st); break;
-            case 4: launch_synthesis<R, 4, false>(a, nb, lev == 1, st); break;
-            case 2: launch_synthesis<R, 2, false>(a, nb, lev == 1, st); break;
-            default: launch_synthesis<R, 1, false>(a, nb, lev == 1, st); break;
+#define SYN_TILE(T)                                                       \
+    case T:                                                               \
+        if (half % T == 0) launch_synthesis<R, T, true>(a, nb, lev == 1, st); \
+        else launch_synthesis<R, T, false>(a, nb, lev == 1, st);          \
+        break;
+            SYN_TILE(16) SYN_TILE(8) SYN_TILE(4) SYN_TILE(2)
+            default: launch_synthesis<R, 1, true>(a, nb, lev == 1, st);
+#undef SYN_TILE
         }
         RIOP_HIP(hipGetLastError());
     }

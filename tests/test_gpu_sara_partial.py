@@ -37,3 +37,25 @@ def test_partial_tiles(n, levels, prec):
         xg, _, ghist, _ = plan.sdmm(to_dev(y, prec), eps, 2, n_cg=3)
         assert rel(host(xg), xo) <= 10 * TOL[prec]
         assert ghist[-1][0] == pytest.approx(hist[-1]["f1"], rel=10 * TOL[prec])
+
+
+# Tiles of 1 to 16, whole and partial, of each kernel: one, three and eight bases,
+# with and without the Dirac plane.
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("n,levels,mask", [
+    (16, 4, 511), (64, 3, 511), (96, 3, 140), (192, 2, 257), (192, 2, 510), (108, 1, 256), (108, 2, 257), (216, 2, 256),
+    (288, 2, 140),
+])
+def test_tile_sides(n, levels, mask, prec):
+    device()
+    announce(f"SARA tile sides n={n} levels={levels} mask={mask} {prec}")
+    from paper_1307_4370_amd import Plan
+    g = W.rng(345, n, mask)
+    q = bin(mask).count("1")
+    uv, x, alpha = W.coverage(8, g), W.random_complex((n, n), g), W.random_complex((q, n, n), g)
+    if prec == "f32":
+        x, alpha = (a.astype(np.complex64).astype(np.complex128) for a in (x, alpha))
+    plan = Plan(n, to_dev(uv, prec), J=6, levels=levels, dict_mask=mask, prec=prec, tile=8)
+    sara = wavelets.Sara(n, levels, mask)
+    assert rel(host(plan.psi_adj(to_dev(x, prec))), sara.psi_adj(x)) <= TOL[prec]
+    assert rel(host(plan.psi(to_dev(alpha, prec))), sara.psi(alpha)) <= TOL[prec]
