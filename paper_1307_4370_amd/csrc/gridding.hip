@@ -1329,18 +1329,26 @@ template <typename R> static BandChoice choose_band(const std::vector<int> &fine
 // spread; `largest`: the largest unit.  Spreading shortens each block's chain
 // and costs a staging of the region per further block, W^2 cells against M J^2
 // taps in all, and block slots for parts that are empty or nearly so.  Units of
-// at most kDegridThreads need one block in either form.  So it is done where the
-// restaged cells are few and the units too few to fill the GPU (or, in double
-// precision, whose blocks hold more registers, the parts well filled).
-// Spread / whole, cold us: 256^2, M = 131072 FP32 8.4 / 13.2 (300 units); 1024^2,
-// M = 4194304 (6900 units) FP32 68 / 57, FP64 102 / 117; tiles of 64,
-// M = 1048576 FP32 49 / 36, FP64 120 / 78 (restaged 0.23 of the taps).
+// at most kDegridThreads need one block in either form.  So it is done where all
+// parts are in flight at once, or where the restaged cells are few, more than one
+// block fits a CU and the units are too few to fill the GPU (or, in double
+// precision, whose blocks hold more registers, the parts well filled, or next to
+// nothing is staged again).
+// Spread / whole, cold us: 256^2, M = 131072 FP32 8.4 / 13.2 (300 units); 192^2, J = 6,
+// M = 110592 FP64 11.9 / 15.0 (500 parts); 1024^2, M = 4194304 (6900 units) FP32
+// 68 / 57, FP64 102 / 117; tiles of 64, M = 1048576 FP32 49 / 36, FP64 120 / 78
+// (restaged 0.23 of the taps); 1024^2, J = 12, tiles of 16 FP64 75 / 123 (0.01); 512^2,
+// J = 12, tiles of 64 (one block per CU) FP64 62 / 52.  Over 190 coverages, tiles and
+// widths the choice costs 0.7 % against the better form in FP32, 0.8 % in FP64.
 template <typename R>
 static int degrid_parts(int64_t nunits, int64_t parts, int largest, int T, int J, int64_t M) {
     const int most = (largest + kDegridThreads - 1) / kDegridThreads;
     const double W = T + J - 1, restaged = (double)(parts - nunits) * W * W, taps = (double)M * J * J;
-    const bool filled = sizeof(R) == 8 && (double)M > 0.75 * kDegridThreads * (double)parts;
-    return most <= 1 || (restaged < 0.12 * taps && (nunits < 2048 || filled)) ? most : 0;
+    const int per_cu = (int)std::min(8.0, std::floor(163840 / (W * W * sizeof(C<R>))));
+    const bool filled = (double)M > 0.7 * kDegridThreads * (double)parts;
+    const bool spread = parts <= 256 * per_cu || (sizeof(R) == 8 && restaged < 0.03 * taps) ||
+                        (per_cu > 1 && restaged < 0.12 * taps && (nunits < 4096 || (sizeof(R) == 8 && filled)));
+    return most <= 1 || spread ? most : 0;
 }
 
 template <typename R> static void build_layout_t(riop_plan *p, const void *uv, hipStream_t st) {

@@ -20,6 +20,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n,M,J,tile,one", [
     (16, 256, 8, 8, 1), (16, 257, 8, 8, 1), (32, 1024, 6, 16, 1), (32, 1025, 6, 16, 1), (64, 9000, 8, 8, 0),
     (32, 600, 8, 64, 0), (64, 5000, 8, 64, 0), (64, 5000, 16, 16, 0), (64, 9000, 12, 32, 0), (128, 40000, 6, 32, 0),
+    # More parts than are in flight at once, their restaging too costly: whole units.
+    (128, 70000, 12, 64, 0), (256, 140000, 8, 64, 0), (256, 270000, 6, 64, 0),
 ])
 def test_degrid_forms(n, M, J, tile, one, prec):
     device()
