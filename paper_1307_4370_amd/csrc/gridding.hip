@@ -1255,16 +1255,16 @@ static void scan_exclusive(const int *in, int *out, int64_t n, int *sums, hipStr
 // The constants are fitted to 984 measured launches (J = 2 .. 16, tiles 8 .. 64, 64^2
 // to 1024^2, uniform, Gaussian, narrow and clustered coverages; 5 % to 95 % of the
 // estimates lie within 0.73 .. 1.46 of the time).  Against the best height and
-// wavefront count of each coverage the choice costs 1.6 % on average, G^T G 2 %.
+// wavefront count of each coverage the choice costs 1.2 % on average, G^T G 1.8 %.
 // Measured (us, J = 8, Gaussian coverage, bands of 32 / 16 / 8 rows, FP32 with 8
 // wavefronts, then FP64): 256^2, M = 131072 25 / 17 / 12, 65 / 36 / 23; 512^2,
 // M = 262144 22 / 21 / 24, 40 / 31 / 41; 1024^2, M = 4194304 83 / 95 / 114,
 // 174 / 204 / 246.
 // One height serves both launches, taken for their sum.  Narrower bands must gain
-// 5 % (15 % for the vector path, whose estimate is coarser) unless all of them are in
-// flight at once, two workgroups per CU: then they only shorten the chain (64^2,
-// M = 2048, J = 6, 16 -> 8 rows 7.1 -> 6.4 us; 128^2, M = 16384, uniform, 32 -> 16
-// rows 9.4 -> 7.6).  Eight wavefronts, fewer workgroups per CU than six, may lose 6 %
+// 5 % (15 % for the vector path, whose estimate is coarser) unless they are few,
+// up to 8 per CU: then they mostly shorten the chain (64^2, M = 2048, J = 6, 16 -> 8
+// rows 7.1 -> 6.4 us; 128^2, M = 16384, uniform, 32 -> 16 rows 9.4 -> 7.6; 384^2,
+// M = 36865, J = 6, FP64, 32 -> 16 rows 18.4 -> 15.0).  Eight wavefronts, fewer workgroups per CU than six, may lose 6 %
 // in the estimate, which divides the measured gains from the losses best (256^2,
 // M = 131072, 8 rows 13.6 -> 12.3; 1024^2, M = 4194304, caller order, cold 98.5 ->
 // 102.7).  In one launch the
@@ -1315,7 +1315,7 @@ template <typename R> static BandChoice choose_band(const std::vector<int> &fine
             c.fused = 0.9 * us1 < us + degrid;
             if (c.fused) sum = us + us1;
         }
-        const double margin = nbands <= 512 ? 1 : (mf ? 0.95 : 0.85);
+        const double margin = nbands <= 2048 ? 1 : (mf ? 0.95 : 0.85);
         if (TB == T || sum < margin * best_us) {
             best = c;
             best_us = sum;
