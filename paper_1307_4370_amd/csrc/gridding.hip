@@ -367,8 +367,9 @@ __global__ void __launch_bounds__(kDegridThreads) degrid_kernel(GridArgs<R> a) {
     // that few loads fetch a clamped row (always the largest: 3 % slower at
     // T = 32, 10 % at T = 8).  Branches around single loads would make each wait
     // for the one before (cold, caller order: 116 -> 139 us), and the choice of a
-    // batch makes the preloads of kPerThread visibilities wait (116 -> 122): they
-    // keep the largest (measured with guarded preloads).
+    // batch makes the preloads of kPerThread visibilities wait (1024^2, M = 4194304,
+    // cold 111 -> 116): they take the largest, but for regions of 5 rows per
+    // wavefront (tiles of 8, M = 262144 warm 43 -> 39).
     constexpr int kStageRows = 5 * (sizeof(R) == 4 ? 2 : 1), kWaves = kDegridThreads >> 6;
     for (int j = threadIdx.x & 63; j < W; j += 64) {
         int gj = tb + j;
@@ -391,7 +392,7 @@ __global__ void __launch_bounds__(kDegridThreads) degrid_kernel(GridArgs<R> a) {
         };
         for (int i0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); i0 < W; i0 += kStageRows * kWaves) {
             const int left = (W - i0 + kWaves - 1) / kWaves;
-            if (PRE && PT > 1) rows(i0, std::integral_constant<int, kStageRows>{});
+            if (PRE && PT > 1 && W > 5 * kWaves) rows(i0, std::integral_constant<int, kStageRows>{});
             else if (left <= 2) rows(i0, std::integral_constant<int, 2>{});
             else if (left <= 5 || kStageRows == 5) rows(i0, std::integral_constant<int, 5>{});
             else rows(i0, std::integral_constant<int, kStageRows>{});
