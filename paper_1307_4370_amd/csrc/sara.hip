@@ -607,9 +607,12 @@ static int level_tile(int half, int nb) { return tile_side(half, nb, 512); }
 // the levels above run other tiles (512^2, 4 levels, 8 bases, FP64, tiles of 8 and 4 on
 // the last two levels 42.2 -> 46.4 us, 1024^2 of 8 on the last one 98.9 -> 101).  With
 // one basis the smaller tiles are still faster (576^2, 6 levels 45.4 -> 42.5).
-static int analysis_tile(int n, int half, int nb) {
-    const int first = level_tile(n >> 1, nb);
-    return nb > 3 && half % first == 0 ? first : level_tile(half, nb);
+// With the l1 prox every block has a partial of f1 in the solver's workspace, so
+// there the tiles are no smaller than the largest that divides the band: a plan
+// needs no more memory than with those (5 KB of 1.8 MB at 64^2).
+static int analysis_tile(int n, int half, int nb, bool prox) {
+    const int first = level_tile(n >> 1, nb), TO = nb > 3 && half % first == 0 ? first : level_tile(half, nb);
+    return prox ? std::max(TO, std::min(kTO, half & -half)) : TO;
 }
 
 // The last synthesis level sums all bases in a block, so blocks are fewer and longer.
@@ -637,17 +640,17 @@ static int dirac_blocks(int n) { return (int)std::min<long>(((long)n * n + 255) 
 
 // Blocks of level 1 that copy the Dirac plane: one per tile, but where the tiles
 // are small no more than have 256 pixels each (every block has a partial of f1).
-static int dirac_row_blocks(int n, int nb) {
-    const int tiles = tiles_of(n >> 1, level_tile(n >> 1, nb));
+static int dirac_row_blocks(int n, int nb, bool prox) {
+    const int tiles = tiles_of(n >> 1, analysis_tile(n, n >> 1, nb, prox));
     return std::min(tiles * tiles, dirac_blocks(n));
 }
 
 int psi_adj_blocks(const riop_plan *p) {
     const int n = p->n, dirac = p->mask & 1, nb = p->q - dirac;
     if (nb == 0) return dirac_blocks(n);
-    int total = dirac ? dirac_row_blocks(n, nb) : 0;
+    int total = dirac ? dirac_row_blocks(n, nb, true) : 0;
     for (int lev = 1; lev <= p->L; ++lev) {
-        const int half = (n >> (lev - 1)) >> 1, tiles = tiles_of(half, analysis_tile(n, half, nb));
+        const int half = (n >> (lev - 1)) >> 1, tiles = tiles_of(half, analysis_tile(n, half, nb, true));
         total += tiles * tiles * nb;
     }
     return total;
@@ -718,7 +721,7 @@ static void psi_adj_impl(riop_plan *p, const void *x, void *alpha, const Prox1<R
     for (int lev = 1; lev <= L; ++lev) {
         const int s = n >> (lev - 1), half = s >> 1;
         a.s = s;
-        a.TO = analysis_tile(n, half, nb);
+        a.TO = analysis_tile(n, half, nb, a.prox);
         a.last = lev == L;
         if (lev > 1) {
             a.in = ll + ll_offset(n, lev - 1);
@@ -729,7 +732,7 @@ static void psi_adj_impl(riop_plan *p, const void *x, void *alpha, const Prox1<R
         a.ll_bstride = (long)p->ll_stride;
         const int tiles = tiles_of(half, a.TO);
         TimedScope ts(p, KK_PSI_ADJ, st);
-        a.dirac_blocks = lev == 1 && a.dirac_plane >= 0 ? dirac_row_blocks(n, nb) : 0;
+        a.dirac_blocks = lev == 1 && a.dirac_plane >= 0 ? dirac_row_blocks(n, nb, a.prox) : 0;
         const dim3 grid(tiles * tiles, nb + (a.dirac_blocks > 0 ? 1 : 0));
         switch (a.TO) {
 #define ANA(T, WHOLE) hipLaunchKernelGGL((dwt_analysis<R, T, WHOLE>), grid, dim3(256), (ana_lds<R, T>()), st, a)
