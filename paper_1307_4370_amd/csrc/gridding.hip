@@ -329,10 +329,10 @@ __device__ inline void degrid_one(const GridArgs<R> &a, const R *kc, const C<R> 
 // before the first wait: the visibilities' cells and offsets (PT = 1, or FP32 in
 // caller order), then up to kStageRows region rows per wavefront at once.
 // With PT = kPerThread the preload pays only where the scattered stores dominate
-// (J = 8, M = 4194304 at 1024^2, cold caches, FP32: caller order 133 -> 107 us, plan
+// (J = 8, M = 4194304 at 1024^2, cold caches, FP32: caller order 133 -> 111 us, plan
 // order 57 -> 61), and its registers do not in FP64.
 // J = 8, one row of loads and no preload before -> now, cold: 1024^2,
-// M = 4194304 FP32 plan order 68 -> 55 us, caller order 143 -> 107, FP64 129 -> 102
+// M = 4194304 FP32 plan order 68 -> 55 us, caller order 143 -> 111, FP64 129 -> 102
 // and 218 -> 160 (there PT = 1); 256^2, M = 131072 warm 11.8 -> 7.0, FP64 16.9 -> 9.5.
 template <typename R, int J, bool USER, int PT>
 __global__ void __launch_bounds__(kDegridThreads) degrid_kernel(GridArgs<R> a) {
@@ -347,7 +347,7 @@ __global__ void __launch_bounds__(kDegridThreads) degrid_kernel(GridArgs<R> a) {
     // With PRE the thread's visibilities (cell, offsets, destination) are loaded
     // first: their latency then overlaps the region's.  Indices past the end are
     // clamped: behind a guard each visibility's loads had waited for those of the
-    // one before, since the compiler moves the first uses there (cold 117 -> 107 us).
+    // one before, since the compiler moves the first uses there (cold 117 -> 111 us).
     constexpr bool PRE = PT == 1 || (USER && sizeof(R) == 4);
     uint32_t cv[PT];
     C<R> rho[PT];
